@@ -60,10 +60,10 @@ enum { FDTD_SRC_CURRENT = 0, FDTD_SRC_VOLTAGE = 1 };
 enum { FDTD_LUMPED_R = 0, FDTD_LUMPED_C = 1 };
 /* Kernel variants for fdtd_set_kernel: two passes per step (H, then E), one
  * fused pass per step, or one temporally blocked pass per two steps (an odd
- * remaining step takes one fused pass).  FDTD_KERNEL_AUTO (the default) is
- * the two-step pass for grids with a CPML and the fused pass otherwise.  The
- * two-step pass needs 2 npml <= 128 (FP32) or 64 (FP64); thicker CPMLs take
- * the fused pass. */
+ * remaining step takes one split or fused pass, whichever is faster at the
+ * grid's size).  FDTD_KERNEL_AUTO (the default) is the two-step pass.  It
+ * needs 2 npml <= 128 (FP32) or 64 (FP64); thicker CPMLs take the fused
+ * pass. */
 enum { FDTD_KERNEL_AUTO = 0, FDTD_KERNEL_SPLIT = 1, FDTD_KERNEL_FUSED = 2, FDTD_KERNEL_TB2 = 3 };
 
 typedef struct fdtd_ctx fdtd_ctx;
@@ -154,8 +154,8 @@ int fdtd_add_source(fdtd_ctx* c, int kind, int axis, int i, int j, int k,
  * src_seg >= 0 drives that segment's current with amps[n] (A, at
  * (n + 1/2) dt; 0 after the last sample; n_amps may be 0); rec_seg >= 0
  * records that segment's current every step.  Every pass variant takes
- * oblique wires (in the two-step pass the touched edges are sources whose
- * amplitudes the wire kernels write before each pass; all variants give the
+ * oblique wires (the touched edges are sources whose amplitudes the wire
+ * kernels write before each pass; all variants give the
  * same bits).  Grids with oblique wires cannot take Debye media
  * (FDTD_EINVAL either way round) and cannot join a batch.  id (may be NULL)
  * receives the wire's index.
@@ -250,13 +250,14 @@ int fdtd_bind_workspace(fdtd_ctx* c, void* dev_ptr, size_t bytes);
 int fdtd_bind_static(fdtd_ctx* c);
 
 /* Select a kernel variant (FDTD_KERNEL_*) and tile parameters (0 = default:
- * 8 rows; 20 planes for the two-step pass, 32 otherwise): tile_y (rows per
- * tile) in {4, 8}, or 12 for FDTD_KERNEL_TB2; tile_z (planes per z chunk)
- * >= 0.  Grids with a CPML run the fused and two-step passes over tile
- * lists grouped by the CPML slabs each tile reaches; tile_z applies to the
- * tiles clear of the x and y slabs, the slab groups take chunks of
- * min(tile_z, 20) planes (two-step) or max(8, tile_z / 4) (fused).
- * Results do not depend on the choice (bitwise).  Errors: EINVAL. */
+ * by the grid's size for the two-step pass, 8 rows and 32 planes otherwise):
+ * tile_y (rows per tile) in {4, 8}, or 12 for FDTD_KERNEL_TB2; tile_z (planes
+ * per z chunk) >= 0.  The two-step pass is one launch over all tiles, the
+ * probes' included.  Grids with a CPML run the fused pass over tile lists
+ * grouped by the CPML slabs each tile reaches; tile_z applies to the tiles
+ * clear of the x and y slabs, the slab groups take chunks of
+ * max(8, tile_z / 4) planes.  Results do not depend on the choice (bitwise).
+ * Errors: EINVAL. */
 int fdtd_set_kernel(fdtd_ctx* c, int variant, int tile_y, int tile_z);
 
 /* Graph replay: graph_steps (a multiple of 4; 0 = off, the default) steps
@@ -295,7 +296,8 @@ double fdtd_algorithmic_bytes_per_step(const fdtd_ctx* c);
 
 /* Kernel timing for roofline measurement: while enabled, fdtd_step records a
  * HIP event pair on the context's stream around the update kernels of every
- * step (not around the probe-recording kernel).  fdtd_kernel_time
+ * step (not around a probe-recording kernel of its own; the two-step pass
+ * records most samples in the update's launch).  fdtd_kernel_time
  * synchronises, returns the summed event time and the number of timed steps
  * since the last call, and resets both.  Errors: EINVAL, EDEVICE. */
 int fdtd_timing(fdtd_ctx* c, int enable);

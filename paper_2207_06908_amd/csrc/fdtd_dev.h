@@ -137,9 +137,8 @@ struct OWireView {
 // Kernel launchers (fdtd_kernels.hip).  `view` points to a GridView<float>
 // (prec 32) or GridView<double> (prec 64) whose in/out pointers are already
 // resolved: the split variant (1) updates in place (in == out), the fused
-// variant (2) reads one set and writes the other, the two-step variant (3)
-// advances two steps from the input set to the output set.  `step` selects
-// the (first) source sample.  Returns 0 or a hipError_t value.
+// variant (2) reads one set and writes the other.  `step` selects the source
+// sample.  Returns 0 or a hipError_t value.
 int launch_step(int prec, const void* view, int cls16, int variant, int step, int tile_y, int tile_z,
                 void* stream);
 // Split step (H then E, in place) of a grid with Debye poles: `dview` is a
@@ -157,37 +156,32 @@ int launch_owire_e1(int prec, const void* view, int cls16, const OWireView* ow, 
 int launch_step_debye(int prec, const void* view, const void* dview, int cls16, int step, void* stream);
 // Fused one-step pass (reads one field set, writes the other) of a grid with
 // Debye poles (fdtd_debye.hip): over the 4-group tile list `tiles` / counts
-// (as for launch_lists_step, variant 2, 8-row tiles; groups 1-3 on
+// (as for launch_lists_step, 8-row tiles; groups 1-3 on
 // `stream2`) or, with tiles == nullptr, over 64 x 8 tiles of tile_z planes.
 int launch_fused_debye(int prec, const void* view, const void* dview, int cls16, int step, int tile_z,
                        const void* tiles, const int* counts, void* stream, void* stream2);
 
-// Fused (variant 2) or two-step (variant 3) pass of one grid over a tile
-// list: `tiles` is a device array of int4 in 4 groups of counts[q] tiles, by
-// the CPML slabs a tile reaches (halo included): 0 neither x nor y slabs, 1 x
-// slabs only, 2 y slabs only, 3 both.  Every group carries z CPML code.
-//   variant 2: (i0, j0, k0, k1); 32 x tile_y tiles in groups 1 and 3,
-//              64 x tile_y in groups 0 and 2;
-//   variant 3: (i0 | iw << 16, j0 | jh << 16, k0, k1) with iw <= 60,
-//              jh <= tile_y.
+// Fused pass of one grid over a tile list: `tiles` is a device array of int4
+// (i0, j0, k0, k1) in 4 groups of counts[q] tiles, by the CPML slabs a tile
+// reaches (halo included): 0 neither x nor y slabs, 1 x slabs only, 2 y slabs
+// only, 3 both.  Every group carries z CPML code; tiles are 32 x tile_y in
+// groups 1 and 3, 64 x tile_y in groups 0 and 2.
 // Group 0 runs on `stream`, groups 1-3 on `stream2` (the caller orders the
 // two streams around the call; they write disjoint tiles).  counts[4] tiles
-// after group 3 (fused: 32 x tile_y) read an oblique wire's source
-// amplitudes: they run last on `stream2`, after it waits for the event
-// `ev_src` (nullptr: no wait) that follows the wire kernels; in variant 3 the
-// first counts[5] of them are clear of the x and y slabs and run as z-only
-// tiles.  Variant 3 also records the probes of `step` on `stream2`, after
-// that wait.
-int launch_lists_step(int prec, const void* view, int cls16, int variant, int step, int tile_y, const void* tiles,
+// after group 3 (32 x tile_y) read an oblique wire's source amplitudes: they
+// run last on `stream2`, after it waits for the event `ev_src` (nullptr: no
+// wait) that follows the wire kernels.
+int launch_lists_step(int prec, const void* view, int cls16, int step, int tile_y, const void* tiles,
                       const int* counts, void* stream, void* stream2, void* ev_src);
-// Record the probes of step `step` from the view's output set.
+// Record the probes of step `step` from the view's input set.
 int launch_probes(int prec, const void* view, int step, void* stream);
 
-// After a two-step pass (variant 3) from view.fi to view.fo: record the
-// probes of steps `step` (recomputed from the input set; only if `first`)
-// and `step` + 1.  A two-step pass over tile lists records `step` itself
-// (launch_lists_step), so the caller passes first = 0 after it.
-int launch_probes2(int prec, const void* view, int cls16, int step, int first, void* stream);
+// Two-step pass of a whole grid in one launch (k_tb2): 60 x ty tiles (ty 4, 8
+// or 12) over kz planes, taken by the XCDs in runs of `run` tiles.  The
+// launch also records the probes of `step` and, with prev != 0, those of
+// `step` - 1 (the input set's); those of `step` + 1 are left to the next
+// pass's prev or to launch_probes.
+int launch_tb2_pass(int prec, const void* view, int cls16, int step, int ty, int kz, int run, int prev, void* stream);
 
 // Batched step over a tile list.  `views` is a device array of GridView (one
 // per grid, already resolved for this step's field-set parity), `tiles` a

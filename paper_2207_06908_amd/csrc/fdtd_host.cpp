@@ -122,10 +122,9 @@ struct fdtd_ctx {
   // interior tiles first, then the CPML tiles; rebuilt when TY or TZ change
   size_t off_tiles = 0, max_tiles = 0;
   std::vector<int> tl;
-  // tile counts of the 4 CPML groups, of group 4 (tiles that read an oblique
-  // wire's amplitudes) and of its first part, the tiles clear of the x and y
-  // slabs (two-step pass only)
-  int tl_cnt[6] = {0, 0, 0, 0, 0, 0}, tl_var = -1, tl_ty = -1, tl_kz = -1;
+  // tile counts of the 4 CPML groups and of group 4 (tiles that read an
+  // oblique wire's amplitudes)
+  int tl_cnt[5] = {0, 0, 0, 0, 0}, tl_ty = -1, tl_kz = -1;
   // the CPML tile groups run on a second stream, concurrently with the
   // clear tiles: fork and join events around each pass
   hipStream_t aux = nullptr;
@@ -138,6 +137,7 @@ struct fdtd_ctx {
   // bound state
   char* ws = nullptr;
   int cur = 0;
+  bool probe_due = false;            // the probes of the last step are still to be recorded (within fdtd_step)
   long long steps_done = 0;
   int variant = FDTD_KERNEL_AUTO, tile_y = 0, tile_z = 0;
   // graph replay (fdtd_set_graph): G steps captured once per parity of the
@@ -1302,13 +1302,13 @@ std::vector<Seg> segments(int n, int np, int w, int align, int w_out) {
   return s;
 }
 
-// Two-step pieces: [0, n) split into w-wide pieces, those in [a, b) clear
-// of the CPML including the h-cell halo (a - h >= np, piece end + h <= n - np);
-// a is a multiple of w so that the pieces below it are full width.
 // The two-step tiles keep the z CPML table (P_NROW rows of 2 npml values)
 // in LDS, room for 2 npml <= 128 values (FP32) or 64 (FP64).
 bool tb2_cpml_fits(int npml, int precision) { return 2 * npml <= (precision == 64 ? 64 : 128); }
 
+// Two-step pieces: [0, n) split into w-wide pieces, those in [a, b) clear
+// of the CPML including the h-cell halo (a - h >= np, piece end + h <= n - np);
+// a is a multiple of w so that the pieces below it are full width.
 std::vector<Seg> segments_tb2(int n, int np, int w, int h) {
   std::vector<Seg> s;
   int a = (np + h + w - 1) / w * w, b = a;
@@ -1320,32 +1320,20 @@ std::vector<Seg> segments_tb2(int n, int np, int w, int h) {
   return s;
 }
 
-// z chunk (planes) of the tiles that read an oblique wire's amplitudes.
-// They start only once the wire kernels are done, so many short blocks finish
-// the pass sooner than a few tall ones: on the lattice-tower scene, one
-// plane gave 94.6k Mcell-updates/s, two 93.3k, four 85.8k, eight 74.4k and
-// whole chunks 52.2k (the single slanted wire: 101.0k, 101.1k, 99.2k,
-// 96.4k, 93.7k).
-constexpr int G4_CHUNK = 1;
-
-// Tile lists of the fused and two-step passes for a grid with a CPML (see
-// fdtd_ctx::tl and launch_lists_step).
-int ensure_tiles(fdtd_ctx* c, int variant, int ty, int kz) {
-  if (c->tl_var == variant && c->tl_ty == ty && c->tl_kz == kz) return FDTD_OK;
-  const bool tb2 = variant == FDTD_KERNEL_TB2;
+// Tile list of the fused pass for a grid with a CPML (see fdtd_ctx::tl and
+// launch_lists_step).
+int ensure_tiles(fdtd_ctx* c, int ty, int kz) {
+  if (c->tl_ty == ty && c->tl_kz == kz) return FDTD_OK;
   const int np = c->P.npml, nz = c->N[2];
-  const std::vector<Seg> xs = tb2 ? segments_tb2(c->N[0], np, 60, 2) : segments(c->N[0], np, 64, 32, 32);
-  const std::vector<Seg> ys = tb2 ? segments_tb2(c->N[1], np, ty, 2) : segments(c->N[1], np, ty, ty, ty);
+  const std::vector<Seg> xs = segments(c->N[0], np, 64, 32, 32);
+  const std::vector<Seg> ys = segments(c->N[1], np, ty, ty, ty);
   // z chunks are not split at the slabs: the z CPML branch depends on the
   // plane only, which every thread of a block shares, so the tiles clear of
   // the x and y slabs carry z CPML code at little cost
   // The CPML groups hold few tiles; shorter chunks give their launches
   // enough blocks to fill the device.
   std::vector<Seg> zs[2];
-  // Two-step slab groups: at most 20 planes.  On a 512 x 512 x 384 grid,
-  // slab chunks of 18-22 planes ran 1-4% faster than 14, 16, 24-30 or 48
-  // (measured; the cause is not pinned down).
-  const int kzp = tb2 ? std::min(kz, 20) : std::max(8, kz / 4);
+  const int kzp = std::max(8, kz / 4);
   for (int z = 0; z < nz; z += kz) zs[0].push_back({z, std::min(z + kz, nz), true});
   for (int z = 0; z < nz; z += kzp) zs[1].push_back({z, std::min(z + kzp, nz), true});
   std::vector<int> grp[4];
@@ -1355,9 +1343,7 @@ int ensure_tiles(fdtd_ctx* c, int variant, int ty, int kz) {
         for (const Seg& x : xs) {
           const int q = (x.in ? 0 : 1) | (y.in ? 0 : 2);
           if ((q == 0) != (pass == 0)) continue;
-          if (tb2) {
-            grp[q].insert(grp[q].end(), {x.a | (x.b - x.a) << 16, y.a | (y.b - y.a) << 16, z.a, z.b});
-          } else if (q & 1) {
+          if (q & 1) {
             for (int xx = x.a; xx < x.b; xx += 32) grp[q].insert(grp[q].end(), {xx, y.a, z.a, z.b});
           } else {
             grp[q].insert(grp[q].end(), {x.a, y.a, z.a, z.b});
@@ -1366,9 +1352,10 @@ int ensure_tiles(fdtd_ctx* c, int variant, int ty, int kz) {
   // Group 4: the tiles whose region (halo and pipeline planes included) holds
   // an oblique wire's source edge.  They read the source amplitudes that the
   // wire kernels write before the pass, so they run after those kernels on
-  // the second stream (with the all-axes instantiation; fused tiles 32 wide),
-  // while the other tiles start at once.
-  std::vector<int> grp4, grp4x;  // group 4: from the z-only group, from the others
+  // the second stream (32-wide tiles of one plane, with the all-axes
+  // instantiation: they start late, so many short blocks finish the pass
+  // sooner), while the other tiles start at once.
+  std::vector<int> grp4;
   if (!c->ow_ekey.empty()) {
     const long long nxl = c->N[0], sxy = nxl * c->N[1];
     std::vector<std::array<int, 3>> pts;
@@ -1378,30 +1365,23 @@ int ensure_tiles(fdtd_ctx* c, int variant, int ty, int kz) {
     }
     for (int q = 0; q < 4; ++q) {
       std::vector<int> keep;
-      const int tw = tb2 ? 0 : (q & 1) ? 32 : 64;
+      const int w = (q & 1) ? 32 : 64;
       for (size_t t = 0; t < grp[q].size(); t += 4) {
         const int* v = &grp[q][t];
-        const int x0 = v[0] & 0xffff, y0 = v[1] & (tb2 ? 0xffff : ~0);
-        const int w = tb2 ? v[0] >> 16 : tw, h = tb2 ? v[1] >> 16 : ty;
         bool hit = false;
         for (const auto& p : pts)
-          hit = hit || (p[0] >= x0 - 2 && p[0] < x0 + w + 2 && p[1] >= y0 - 2 && p[1] < y0 + h + 2 &&
+          hit = hit || (p[0] >= v[0] - 2 && p[0] < v[0] + w + 2 && p[1] >= v[1] - 2 && p[1] < v[1] + ty + 2 &&
                         p[2] >= v[2] - 2 && p[2] < v[3] + 2);
         if (!hit) {
           keep.insert(keep.end(), v, v + 4);
           continue;
         }
-        // chunks of G4_CHUNK planes (fused tiles 32 wide)
-        std::vector<int>& dst = (tb2 && q == 0) ? grp4 : grp4x;
-        for (int z = v[2]; z < v[3]; z += G4_CHUNK)
-          for (int xx = 0; xx < (tw == 64 ? 2 : 1); ++xx)
-            dst.insert(dst.end(), {v[0] + 32 * xx, v[1], z, std::min(z + G4_CHUNK, v[3])});
+        for (int z = v[2]; z < v[3]; ++z)
+          for (int xx = 0; xx < w; xx += 32) grp4.insert(grp4.end(), {v[0] + xx, v[1], z, z + 1});
       }
       grp[q].swap(keep);
     }
   }
-  c->tl_cnt[5] = (int)(grp4.size() / 4);
-  grp4.insert(grp4.end(), grp4x.begin(), grp4x.end());
   size_t nt = grp4.size() / 4;
   for (int q = 0; q < 4; ++q) nt += grp[q].size() / 4;
   if (nt > c->max_tiles) return fail(c, FDTD_EINVAL, "tile list larger than its reservation");
@@ -1417,9 +1397,66 @@ int ensure_tiles(fdtd_ctx* c, int variant, int ty, int kz) {
   e = hipMemcpyAsync(c->ws + c->off_tiles, c->tl.data(), c->tl.size() * sizeof(int), hipMemcpyHostToDevice,
                      c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "tile list upload");
-  c->tl_var = variant;
   c->tl_ty = ty;
   c->tl_kz = kz;
+  return FDTD_OK;
+}
+
+// Launch shape of a whole-grid two-step pass (launch_tb2_pass): what
+// fdtd_set_kernel asks for, or by the grid's size.
+//  - 12-row tiles from 40M cells (FP32): they read 1.33 rows a row, 8-row
+//    ones 1.5, but their x-y corner tiles spill at the 128 registers that 16
+//    waves leave, which small grids, nearly all slabs, feel.  us per step,
+//    12 rows / 8 rows: 512 x 512 x 384 764 / 800, 396 x 400 x 293 391 / 403,
+//    304 x 305 x 230 222 / 213, 96 x 96 x 80 22 / 15.
+//  - Planes per chunk: one block runs on a CU at a time, so up to 256 blocks
+//    take one chunk's march (its planes and about 4 of pipeline), and more
+//    take it nb / 256 times and half a round for the ragged end.  Chunks past
+//    40 planes (20 in 12-row tiles) no longer gain: the blocks of an XCD
+//    drift apart and share fewer halo lines in its L2 (512 x 512 x 384, 12
+//    rows: 20 planes 764, 32 808, 64 860 us).
+//  - An XCD takes about three rows of tiles in a row (neighbours in x and y
+//    share its L2), an odd number of tiles, so that the slower tiles of the
+//    x slabs do not meet the same CUs in every round (203 x 157 x 131, 4
+//    tiles a row: 12 in a row 59, 5 and 7 50 us; 512 x 512 x 384: 27 764, 9
+//    782, 36 797, 1 824 us).
+struct Tb2Shape {
+  int ty, kz, run;
+};
+Tb2Shape tb2_shape(const fdtd_ctx* c) {
+  Tb2Shape s;
+  s.ty = c->tile_y ? c->tile_y : c->P.precision == 32 && c->ncell >= (40ll << 20) ? 12 : 8;
+  const int ntx = (c->N[0] + 59) / 60, nty = (c->N[1] + s.ty - 1) / s.ty, nz = c->N[2];
+  s.kz = c->tile_z;
+  if (s.kz == 0) {
+    const long long probes = (long long)c->probes.size() / 3 + 1;  // blocks that record probes
+    double best = 0;
+    for (int kz = 2; kz <= (s.ty == 12 ? 20 : 40); ++kz) {
+      const int chunks = (nz + kz - 1) / kz, d = (nz + chunks - 1) / chunks;
+      const long long nb = (long long)ntx * nty * chunks + probes;
+      const double cost = (nb <= 256 ? 1.0 : (double)nb / 256.0 + 0.5) * (d + 4);
+      if (s.kz == 0 || cost < best) {
+        best = cost;
+        s.kz = d;
+      }
+    }
+  }
+  s.run = (3 * ntx) | 1;
+  return s;
+}
+
+// Record the probes of step - 1 from the current field set, where the
+// two-step pass that made it left them (launch_tb2_pass).
+int record_due(fdtd_ctx* c, hipStream_t st, int step, const int* dstep) {
+  if (!c->probe_due) return FDTD_OK;
+  c->probe_due = false;
+  GridView<float> p32 = c->v32[c->cur][c->cur];
+  GridView<double> p64 = c->v64[c->cur][c->cur];
+  p32.dstep = dstep;
+  p64.dstep = dstep;
+  const int e = launch_probes(c->P.precision, c->P.precision == 64 ? (const void*)&p64 : (const void*)&p32, step - 1,
+                              (void*)st);
+  if (e) return fail(c, FDTD_EDEVICE, std::string("probe launch: ") + hipGetErrorString((hipError_t)e));
   return FDTD_OK;
 }
 
@@ -1428,6 +1465,10 @@ int ensure_tiles(fdtd_ctx* c, int variant, int ty, int kz) {
 // dstep for a launch captured into a graph.  With slot >= 0 the end event of
 // the update kernels is recorded before the probes.
 int launch_pass(fdtd_ctx* c, hipStream_t st, int variant, bool lists, int lty, int step, const int* dstep, int slot) {
+  if (variant != FDTD_KERNEL_TB2) {
+    int rc = record_due(c, st, step, dstep);
+    if (rc) return rc;
+  }
   const int in = c->cur, out = variant == FDTD_KERNEL_SPLIT ? c->cur : 1 - c->cur;
   GridView<float> v32 = c->v32[in][out], p32 = c->v32[out][out];
   GridView<double> v64 = c->v64[in][out], p64 = c->v64[out][out];
@@ -1479,7 +1520,7 @@ int launch_pass(fdtd_ctx* c, hipStream_t st, int variant, bool lists, int lty, i
       e = launch_fused_debye(c->P.precision, view, dview, c->cls16, step, c->tile_z, c->ws + c->off_tiles,
                              c->tl_cnt, (void*)st, (void*)c->aux);
     else
-      e = launch_lists_step(c->P.precision, view, c->cls16, variant, step, lty, c->ws + c->off_tiles, c->tl_cnt,
+      e = launch_lists_step(c->P.precision, view, c->cls16, step, lty, c->ws + c->off_tiles, c->tl_cnt,
                             (void*)st, (void*)c->aux, ev_src);
     if (!e) {
       he = hipEventRecord(c->ev_join, c->aux);
@@ -1491,6 +1532,10 @@ int launch_pass(fdtd_ctx* c, hipStream_t st, int variant, bool lists, int lty, i
             ? launch_step_debye(c->P.precision, view, dview, c->cls16, step, (void*)st)
             : launch_fused_debye(c->P.precision, view, dview, c->cls16, step, c->tile_z, nullptr, nullptr, (void*)st,
                                  nullptr);
+  } else if (variant == FDTD_KERNEL_TB2) {
+    const Tb2Shape sh = tb2_shape(c);
+    e = launch_tb2_pass(c->P.precision, view, c->cls16, step, sh.ty, sh.kz, sh.run, c->probe_due ? 1 : 0, (void*)st);
+    c->probe_due = !c->probes.empty();
   } else {
     e = launch_step(c->P.precision, view, c->cls16, variant, step, c->tile_y, c->tile_z, (void*)st);
   }
@@ -1499,10 +1544,7 @@ int launch_pass(fdtd_ctx* c, hipStream_t st, int variant, bool lists, int lty, i
     hipError_t he = hipEventRecord(c->ev1[slot], st);
     if (he != hipSuccess) return hip_fail(c, he, "hipEventRecord");
   }
-  if (variant == FDTD_KERNEL_TB2)
-    e = launch_probes2(c->P.precision, view, c->cls16, step, lists ? 0 : 1, (void*)st);
-  else
-    e = launch_probes(c->P.precision, pview, step, (void*)st);
+  e = variant == FDTD_KERNEL_TB2 ? 0 : launch_probes(c->P.precision, pview, step, (void*)st);
   if (e) return fail(c, FDTD_EDEVICE, std::string("probe launch: ") + hipGetErrorString((hipError_t)e));
   return FDTD_OK;
 }
@@ -1533,6 +1575,8 @@ int capture_graph(fdtd_ctx* c, int variant, bool lists, int lty) {
     rc = launch_pass(c, c->cap_stream, variant, lists, lty, off, dstep, -1);
     if (variant != FDTD_KERNEL_SPLIT) c->cur ^= 1;
   }
+  if (rc == FDTD_OK) rc = record_due(c, c->cap_stream, G, dstep);
+  c->probe_due = false;
   c->cur = cur0;
   hipGraph_t gr = nullptr;
   he = hipStreamEndCapture(c->cap_stream, &gr);
@@ -1558,12 +1602,11 @@ int fdtd_step(fdtd_ctx* c, int n) {
   if (!c || n < 0) return fail(c, FDTD_EINVAL, "bad step count");
   if (!c->ws) return fail(c, FDTD_ESTATE, "no workspace bound");
   if (c->steps_done + n > c->P.max_steps) return fail(c, FDTD_ERANGE, "beyond max_steps");
-  // AUTO: the two-step pass over CPML tile lists for grids with a CPML (the
-  // fastest on such grids), the fused pass otherwise.  The two-step tiles hold
-  // the z CPML table in LDS: thicker layers take the fused pass.
+  // AUTO: the two-step pass.  Its tiles hold the z CPML table in LDS: thicker
+  // layers take the fused pass.
   const bool listable = c->P.npml > 0 && c->N[0] < 65536 && c->N[1] < 65536;
   const bool tb2_ok = tb2_cpml_fits(c->P.npml, c->P.precision);
-  int chosen = c->variant != FDTD_KERNEL_AUTO ? c->variant : listable ? FDTD_KERNEL_TB2 : FDTD_KERNEL_FUSED;
+  int chosen = c->variant != FDTD_KERNEL_AUTO ? c->variant : FDTD_KERNEL_TB2;
   if (chosen == FDTD_KERNEL_TB2 && !tb2_ok) chosen = FDTD_KERNEL_FUSED;
   if (c->npole && !c->owr.empty()) return fail(c, FDTD_EINVAL, "oblique wires in a grid with Debye media");
   // Debye media: the split pass, or the fused pass when asked for (the pole
@@ -1572,26 +1615,29 @@ int fdtd_step(fdtd_ctx* c, int n) {
   // 512 x 512 x 384 cells and slower on every smaller grid measured (its
   // CPML slab groups dominate there).
   if (c->npole) chosen = c->variant == FDTD_KERNEL_FUSED ? FDTD_KERNEL_FUSED : FDTD_KERNEL_SPLIT;
-  const int lty = c->npole ? 8 : c->tile_y == 4 ? 4 : (c->tile_y == 12 && chosen == FDTD_KERNEL_TB2) ? 12 : 8;
+  c->probe_due = false;
   const int G = c->graph_steps;
-  const long long key = ((long long)chosen * 16 + lty) * 65536 + c->tile_z;
+  const long long key = ((long long)chosen * 16 + c->tile_y) * 65536 + c->tile_z;
   if (G > 0 && key != c->graph_key) {
     drop_graphs(c);
     c->graph_key = key;
   }
   for (int t = 0; t < n;) {
-    // the two-step pass needs two steps; an odd remainder takes one fused step
-    const int variant = (chosen == FDTD_KERNEL_TB2 && n - t < 2) ? FDTD_KERNEL_FUSED : chosen;
+    // the two-step pass needs two steps; an odd remainder takes one step of
+    // its own: the split pass on grids whose fused tiles leave the device
+    // idle (us per step, split / fused: 48^3 8.6 / 38, 256 x 256 x 192 with
+    // a CPML 226 / 304, 384 x 384 x 288 681 / 714, 512 x 512 x 384 1,708 /
+    // 1,412; without one 96^3 16 / 40, 256^3 237 / 190)
+    const int odd = c->ncell < (listable ? 64ll << 20 : 8ll << 20) ? FDTD_KERNEL_SPLIT : FDTD_KERNEL_FUSED;
+    const int variant = (chosen == FDTD_KERNEL_TB2 && n - t < 2) ? odd : chosen;
     const int adv = variant == FDTD_KERNEL_TB2 ? 2 : 1;
-    // grids with a CPML run the fused and two-step passes over tile lists
-    const bool lists = (variant == FDTD_KERNEL_FUSED || variant == FDTD_KERNEL_TB2) && listable;
-    const int lkz = std::max(8, c->tile_z > 0 ? c->tile_z : (variant == FDTD_KERNEL_TB2 ? 20 : 32));
-    // 12-row tiles exist for the two-step pass only (an odd last step's fused
-    // pass takes 8 rows)
-    // (Debye grids: 8 rows)
-    const int vty = c->npole ? 8 : c->tile_y == 4 ? 4 : (c->tile_y == 12 && variant == FDTD_KERNEL_TB2) ? 12 : 8;
+    // grids with a CPML run the fused pass over tile lists (8 rows in Debye
+    // media and after 12-row two-step tiles)
+    const bool lists = variant == FDTD_KERNEL_FUSED && listable;
+    const int lkz = std::max(8, c->tile_z > 0 ? c->tile_z : 32);
+    const int vty = c->npole || c->tile_y != 4 ? 8 : 4;
     if (lists) {
-      int rc = ensure_tiles(c, variant, vty, lkz);
+      int rc = ensure_tiles(c, vty, lkz);
       if (rc) return rc;
       if (!c->aux) {
         hipError_t he = hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking);
@@ -1603,6 +1649,10 @@ int fdtd_step(fdtd_ctx* c, int n) {
       }
     }
     const bool replay = G > 0 && n - t >= G && variant == chosen;
+    if (replay) {
+      int rc = record_due(c, c->stream, (int)c->steps_done, nullptr);
+      if (rc) return rc;
+    }
     int slot = -1;
     if (c->timing) {
       slot = c->ev_next;
@@ -1646,7 +1696,7 @@ int fdtd_step(fdtd_ctx* c, int n) {
     c->steps_done += done;
     t += done;
   }
-  return FDTD_OK;
+  return record_due(c, c->stream, (int)c->steps_done, nullptr);
 }
 
 int fdtd_set_graph(fdtd_ctx* c, int graph_steps) {

@@ -385,9 +385,9 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
     if (inB && kin && k >= k0 - 1) {
       auto stage_b = [&](const int l[3]) {
         if (PML) psi_load(g, 0, l, x, y, k, psen);
-        e_core_pf<T, PML>(pf, g, l, n0 + sxy * (unsigned)k, coef(cc), h1c[0], h1c[1], h1c[2], sm.sh1[0][v - 1][u],
-                       h1p[0], sm.sh1[1][v][u - 1], h1p[1], sm.sh1[2][v][u - 1], sm.sh1[2][v - 1][u], e0c, step,
-                       psen, e1c, srcr.first(k), srcr.last(k));
+        e_core_pf<T, PML>(pf, l, coef(cc), h1c[0], h1c[1], h1c[2], sm.sh1[0][v - 1][u], h1p[0], sm.sh1[1][v][u - 1],
+                          h1p[1], sm.sh1[2][v][u - 1], sm.sh1[2][v - 1][u], e0c, psen, e1c);
+        e_sources(&g, srcr.first(k), srcr.last(k), n0 + sxy * (unsigned)k, step, e1c);
       };
       if (lz >= 0) {
         const int l[3] = {lx, ly, lz};
@@ -430,9 +430,9 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
     nst = n0 + sxy * (unsigned)km;
     if (pend) {
       int l[3] = {lx, ly, PZ ? slab_pos(km, nz, g.npml) : -1};
-      e_core_pf<T, PML>(pf, g, l, nst, coef(cp), h2c[0], h2c[1], h2c[2], sm.sh2[0][v - 1][u], h2p[0], sm.sh2[1][v][u - 1],
-                     h2p[1], sm.sh2[2][v][u - 1], sm.sh2[2][v - 1][u], e1p, step + 1, pse, e2, srcr.first(km),
-                     srcr.last(km));
+      e_core_pf<T, PML>(pf, l, coef(cp), h2c[0], h2c[1], h2c[2], sm.sh2[0][v - 1][u], h2p[0], sm.sh2[1][v][u - 1],
+                        h2p[1], sm.sh2[2][v][u - 1], sm.sh2[2][v - 1][u], e1p, pse, e2);
+      e_sources(&g, srcr.first(km), srcr.last(km), nst, step + 1, e2);
       if (!DEFER) {
         stg(g.fo[0], nst, e2[0]);
         stg(g.fo[1], nst, e2[1]);
@@ -464,31 +464,354 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
   flush();
 }
 
-template <typename T, typename CI, bool PML, int TY>
-__global__ __launch_bounds__(64 * (TY + 4)) void k_tb2(GridView<T> g, int step, int kz, int ntx, int nty) {
-  step = gstep(g, step);
-  __shared__ TB2Smem<T, TY> sm;
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int tile_x = tile % ntx, rest = tile / ntx;
-  const int k0 = (rest / nty) * kz;
-  tb2_tile<T, CI, PML, TY, 7>(g, sm, tile_x * 60, (rest % nty) * TY, 60, TY, k0, min(k0 + kz, g.nz), step);
+// ---------------------------------------------------------------------------
+// The two-step tile of k_tb2: 64 x (TY + 4) points around a 60 x TY output
+// tile, two barriers per plane.  Iteration k runs two phases, a barrier after
+// each:
+//   X  H^{n+1/2} of plane k (stage A) and E^{n+2} of plane k-2 (stage D);
+//   Y  E^{n+1} of plane k (B) and H^{n+3/2} of plane k-1 (C).
+// The two stages of a phase do not depend on each other.  Neighbours along x
+// are lanes of the same wave (cross-lane moves), those along z stay in the
+// thread's registers, and only the components that y neighbours need go
+// through LDS: E^n (x, z) for A, H^{n+1/2} (x, z) for B, E^{n+1} (x, z) for C,
+// H^{n+3/2} (x, z) for D.
+//
+// One block runs on a CU at a time (58 KB of LDS, up to 16 waves of at most
+// 128 registers), and with everything in the caches a plane costs what its
+// instructions cost, so the loop is built to issue few: uniform bases with
+// one 32-bit offset per plane; points and planes outside the grid are not
+// branched around (their coefficients are the table's zero row); registers
+// rotate by name over three unrolled iterations, not by copies; what is
+// needed rarely is read again where it is needed (ColdView).  A lane outside a stage's region
+// computes a value that no lane inside reads.
+//
+// Measured (us per step, against one launch per CPML group of 8-row tiles
+// with three barriers, four LDS planes and 2.5 times the instructions):
+// 512 x 512 x 384 with a 10-cell CPML 789 (891), 203 x 157 x 131 52 (116),
+// 96 x 96 x 80 15 (82), 48^3 without one 4.3 (38, the fused pass).  In the
+// caches a plane of an 8-row tile takes 0.92 us clear of the CPML and 1.9 us
+// in it; on the largest grid 12 rows take 2.1 us, bound by the 5 TB/s that
+// the tiles draw through the L2s (a copy reaches 5.1).
+// ---------------------------------------------------------------------------
+
+template <typename T, int TY>
+struct MarchSmem {
+  static constexpr int R = TY + 4;
+  static constexpr int PZ = 512 / sizeof(T);  // longest z profile row held here (2 npml)
+  T e0[2][R][64];       // E^n (x, z), plane k
+  T h1[2][R][64];       // H^{n+1/2} (x, z), plane k
+  T e1[2][2][R][64];    // E^{n+1} (x, z), planes k and k-1
+  T h2[2][R][64];       // H^{n+3/2} (x, z), plane k-2
+  T stab[257 * K_STRIDE];  // a row of zeros, then the classes' coefficients
+  T px[P_NROW][64];     // CPML profile at each lane's x
+  T pz[P_NROW * PZ];    // the z table
+};
+
+template <typename T, int TY>
+struct ProfMarch {
+  const MarchSmem<T, TY>& sm;
+  int tn, u;
+  T ye[3], yh[3];  // the y profile at this wave's row (uniform)
+  template <int U>
+  __device__ __forceinline__ Prof3<T> at(int row, int l) const {
+    if (U == 0) return {sm.px[row][u], sm.px[row + 1][u], sm.px[row + 2][u]};
+    if (U == 1) return row == P_BE ? Prof3<T>{ye[0], ye[1], ye[2]} : Prof3<T>{yh[0], yh[1], yh[2]};
+    const int q = row * tn + l;
+    return {sm.pz[q], sm.pz[q + tn], sm.pz[q + 2 * tn]};
+  }
+};
+
+// A wave-uniform value in a scalar register.
+__device__ __forceinline__ float uniform(float v) {
+  return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
+}
+__device__ __forceinline__ double uniform(double v) {
+  const unsigned long long b = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// Tile list: (i0 | iw << 16, j0 | jh << 16, k0, k1) per block.  FP32: at
-// most 80 VGPRs (6 waves per SIMD), so that two blocks share a CU.  The
-// corner tiles get there as LEAN tiles, which also lets them run beside the
-// z-only tiles rather than wait for a free CU.
-template <typename T, typename CI, bool PML, int TY, int AX>
-__global__ __launch_bounds__(64 * (TY + 4), (sizeof(T) == 8 ? 1 : 6)) void k_tb2_list(GridView<T> g,
-                                                                                      const int4* __restrict__ tiles,
-                                                                                      int step) {
-  step = gstep(g, step);
-  __shared__ TB2Smem<T, TY> sm;
-  const int4 t = tiles[xcd_runs(blockIdx.x, gridDim.x)];
-  constexpr bool LEAN = AX == 7 && sizeof(T) == 4;
-  tb2_tile<T, CI, PML, TY, AX, !LEAN, LEAN>(g, sm, t.x & 0xffff, t.y & 0xffff, t.x >> 16, t.y >> 16, t.z, t.w,
-                                           step);
+// The value of lane u + 1 (CTRL 0x130, wave_shl:1) or u - 1 (0x138,
+// wave_shr:1); 0 past the wave's ends.  Every lane must be active.
+template <int CTRL>
+__device__ __forceinline__ float lane_shift(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
 }
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+template <typename T>
+__device__ __forceinline__ T next_lane(T v) { return lane_shift<0x130>(v); }
+template <typename T>
+__device__ __forceinline__ T prev_lane(T v) { return lane_shift<0x138>(v); }
+
+// Element access by a byte offset from a uniform base.
+template <typename T>
+__device__ __forceinline__ T ldb(const T* base, unsigned off) {
+  typedef __attribute__((address_space(1))) const T GT;
+  return *(GT*)((const __attribute__((address_space(1))) char*)base + off);
+}
+template <typename T>
+__device__ __forceinline__ void stb(T* base, unsigned off, T v) {
+  typedef __attribute__((address_space(1))) T GT;
+  *(GT*)((__attribute__((address_space(1))) char*)base + off) = v;
+}
+
+// A view whose members are read where they are used (by scalar loads), not
+// kept in scalar registers over the whole march.
+template <typename T>
+struct ColdView {
+  typedef const __attribute__((address_space(4))) GridView<T>* P;
+  P p;
+  __device__ __forceinline__ P operator->() const {
+    P q = p;
+    asm volatile("" : "+s"(q));
+    return q;
+  }
+};
+
+// The state of one thread's point, registers named by plane modulo 3.
+template <typename T>
+struct MarchRegs {
+  T e0[3][3];       // E^n
+  T h0[3][3];       // H^{n-1/2}
+  T h1[3][3];       // H^{n+1/2}
+  T e1[3][3];       // E^{n+1}
+  T h2[3][3];       // H^{n+3/2}
+  T e2[3];          // E^{n+2} of D
+  T ph[3][3][2];    // CPML state, H-type [plane][axis][component]
+  T pe[3][3][2];    // E-type
+  unsigned co[3];   // LDS row (in values) of the class
+};
+
+// One tile: outputs [i0, i0 + iw) x [j0, j0 + jh) x [k0, k1) with iw <= 60,
+// jh <= TY; AX masks the axes whose CPML slabs the tile's region reaches.
+//
+// Points outside the grid read the column (0, 0), whose E is 0 (it lies on
+// two walls); planes below the grid read plane 0, planes above it the last
+// one, with E set to 0.  With the zero row as their coefficients their E
+// stays 0, as the upper walls need; their H only meets the lower walls'
+// zero coefficients.
+template <typename T, typename CI, int TY, int AX>
+struct March {
+  static constexpr int TX = 60, NT = 64 * (TY + 4);
+  static constexpr bool LDS_TAB = sizeof(CI) == 1;
+  static constexpr bool PML = AX != 0, SX = AX & 1, SY = AX & 2, SZ = AX & 4;
+  static constexpr unsigned S = sizeof(T), NONE = 0xFFFFFFFFu;
+
+  MarchSmem<T, TY>& sm;
+  ColdView<T> g;
+  const T* fi[6];
+  T* fo[6];
+  const CI* cls;
+  int nz, np, u, v, step, k0, k1;
+  int lx, ly;
+  unsigned n0, n0s, sxy;           // column index, its byte offset; nodes per plane
+  bool dom, inD;
+  unsigned qx, qy;
+  SrcRange srcr;
+  ProfMarch<T, TY> pf;
+  MarchRegs<T> r;
+  unsigned craw;
+
+  // coefficients [F, F + N) of a class row
+  template <int F, int N>
+  __device__ __forceinline__ void coef(unsigned row, T* cf) const {
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+      cf[F + q] = LDS_TAB ? sm.stab[row + F + q] : row == NONE ? T(0) : ldg(g->ctab, row + F + q);
+  }
+  // the row of a class id; the zero row for points and planes outside the grid
+  __device__ __forceinline__ unsigned row_of(unsigned c, bool in) const {
+    return LDS_TAB ? (in ? (c + 1u) * K_STRIDE : 0u) : (in ? c * K_STRIDE : NONE);
+  }
+  __device__ __forceinline__ void slab3(int k, int l[3]) const {
+    const bool in = k >= 0 && k < nz;
+    l[0] = SX && in ? lx : -1;
+    l[1] = SY && in ? ly : -1;
+    l[2] = SZ && in ? slab_pos(k, nz, np) : -1;
+  }
+  // Both kinds of CPML state of plane k: H-type into ph, E-type into pe
+  // (values outside the slabs are not used); and back from plane k's.
+  template <bool LOAD>
+  __device__ __forceinline__ void psi(int k, T ph[3][2], T pe[3][2]) const {
+    const int lz = SZ ? slab_pos(k, nz, np) : -1;
+    auto move = [&](int a, size_t plane, unsigned q) {
+      const size_t el = g->pel[a];
+      const T* pi = g->pib[a] + plane;
+      T* po = g->pob[a] + plane;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        if (LOAD) {
+          pe[a][c] = ldg(pi + el * c, q);
+          ph[a][c] = ldg(pi + el * (2 + c), q);
+        } else {
+          stg(po + el * c, q, pe[a][c]);
+          stg(po + el * (2 + c), q, ph[a][c]);
+        }
+      }
+    };
+    if (SX && lx >= 0) move(0, (size_t)(2 * np) * (size_t)(unsigned)g->ny * (size_t)k, qx);
+    if (SY && ly >= 0) move(1, (size_t)(2 * np) * (size_t)(unsigned)g->nx * (size_t)k, qy);
+    if (SZ && lz >= 0) move(2, (size_t)sxy * (size_t)lz, n0);
+  }
+
+  // H of plane k (A and C): e and en the E of planes k and k + 1, le the
+  // plane's E (x, z) in LDS.
+  __device__ __forceinline__ void stage_h(int k, unsigned row, const T e[3], const T en[3], const T (*le)[TY + 4][64],
+                                          const T hold[3], T ps[3][2], T hn[3]) const {
+    T cf[K_STRIDE];
+    coef<K_DBX, 3>(row, cf);
+    int l[3];
+    slab3(k, l);
+    h_core_pf<T, PML>(pf, l, cf, e[0], e[1], e[2], le[0][v + 1][u], en[0], next_lane(e[1]), en[1], next_lane(e[2]),
+                      le[1][v + 1][u], hold, ps, hn);
+  }
+  // E of plane k (B and D): h and hp the H of planes k and k - 1, lh the
+  // plane's H (x, z) in LDS.
+  __device__ __forceinline__ void stage_e(int k, unsigned row, const T h[3], const T hp[3], const T (*lh)[TY + 4][64],
+                                          const T eold[3], int st, T ps[3][2], T en[3]) const {
+    T cf[K_STRIDE];
+    coef<K_CAX, 6>(row, cf);
+    int l[3];
+    slab3(k, l);
+    e_core_pf<T, PML>(pf, l, cf, h[0], h[1], h[2], lh[0][v - 1][u], hp[0], prev_lane(h[1]), hp[1], prev_lane(h[2]),
+                      lh[1][v - 1][u], eold, ps, en);
+    if (k >= srcr.klo && k <= srcr.khi)  // uniform
+      e_sources(g, srcr.lo, srcr.hi, dom ? n0 + sxy * (unsigned)k : NONE, st, en);
+  }
+
+  // Iteration k, the registers of plane k in slot Q; with TAIL only what is
+  // left after the last plane: D and the outputs of plane k1 - 1.
+  template <int Q, bool TAIL>
+  __device__ __forceinline__ void iter(int k) {
+    constexpr int N1 = (Q + 1) % 3, P1 = (Q + 2) % 3, P2 = N1;  // slots of planes k+1, k-1 and k-2
+    if (!TAIL) {
+      // loads: class and H of plane k+1, E of plane k+2 (plane k-1's slot)
+      r.co[Q] = row_of(craw, dom && k >= 0 && k < nz);
+      if (k + 1 >= nz) r.e0[N1][0] = r.e0[N1][1] = r.e0[N1][2] = T(0);
+      const unsigned ph = (unsigned)min(max(k + 1, 0), nz - 1) * sxy, pe = (unsigned)min(max(k + 2, 0), nz - 1) * sxy;
+      craw = ldg(cls, n0 + ph);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) r.h0[N1][c] = ldb(fi[3 + c], n0s + ph * S);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) r.e0[P1][c] = ldb(fi[c], n0s + pe * S);
+      // X: A of plane k, D of plane k-2
+      if (v <= TY + 2) {
+        stage_h(k, r.co[Q], r.e0[Q], r.e0[N1], sm.e0, r.h0[Q], r.ph[Q], r.h1[Q]);
+        sm.h1[0][v][u] = r.h1[Q][0];
+        sm.h1[1][v][u] = r.h1[Q][2];
+      }
+    }
+    if (v >= 2 && v <= TY + 1 && k - 2 >= k0)
+      stage_e(k - 2, r.co[P2], r.h2[P2], r.h2[Q], sm.h2, r.e1[P2], step + 1, r.pe[P2], r.e2);
+    if (!TAIL) __syncthreads();
+    // the outputs of plane k-2
+    if (inD && k - 2 >= k0) {
+      const unsigned o = n0s + (unsigned)(k - 2) * sxy * S;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) stb(fo[c], o, r.e2[c]);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) stb(fo[3 + c], o, r.h2[P2][c]);
+      if (PML) psi<false>(k - 2, r.ph[P2], r.pe[P2]);
+    }
+    if (TAIL) return;
+    if (PML && k + 1 >= 0 && k + 1 < nz) psi<true>(k + 1, r.ph[N1], r.pe[N1]);
+    // Y: B of plane k, C of plane k-1
+    const int s1 = k & 1, s1m = s1 ^ 1;
+    if (v >= 1 && v <= TY + 2 && k >= k0 - 1) {
+      stage_e(k, r.co[Q], r.h1[Q], r.h1[P1], sm.h1, r.e0[Q], step, r.pe[Q], r.e1[Q]);
+      if (v <= TY + 1 && k >= k0) {
+        stage_h(k - 1, r.co[P1], r.e1[P1], r.e1[Q], sm.e1[s1m], r.h1[P1], r.ph[P1], r.h2[P1]);
+        sm.h2[0][v][u] = r.h2[P1][0];
+        sm.h2[1][v][u] = r.h2[P1][2];
+      }
+      sm.e1[s1][0][v][u] = r.e1[Q][0];
+      sm.e1[s1][1][v][u] = r.e1[Q][2];
+    }
+    sm.e0[0][v][u] = k + 1 >= nz ? T(0) : r.e0[N1][0];
+    sm.e0[1][v][u] = k + 1 >= nz ? T(0) : r.e0[N1][2];
+    __syncthreads();
+  }
+
+  __device__ __forceinline__ March(const GridView<T>& gv, ColdView<T> cold, MarchSmem<T, TY>& sm_, int i0, int j0,
+                                   int iw, int jh, int k0_, int k1_, int step_)
+      : sm(sm_), g(cold), nz(gv.nz), np(gv.npml), step(step_), k0(k0_), k1(k1_),
+        pf{sm_, 0, 0, {T(0), T(0), T(0)}, {T(0), T(0), T(0)}} {
+    const int tid = threadIdx.x, nx = gv.nx, ny = gv.ny;
+    u = tid & 63;
+    v = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (LDS_TAB) {
+      if (tid < K_STRIDE) sm.stab[tid] = T(0);
+      for (int q = tid; q < gv.ncls * K_STRIDE; q += NT) sm.stab[K_STRIDE + q] = ldg(gv.ctab, (unsigned)q);
+    }
+    const int x = i0 - 2 + u, y = j0 - 2 + v;
+    dom = x >= 0 && x < nx && y >= 0 && y < ny;
+    inD = dom && u >= 2 && u < 2 + iw && v >= 2 && v < 2 + jh;
+    sxy = (unsigned)gv.sxy;
+    n0 = dom ? (unsigned)x + (unsigned)nx * (unsigned)y : 0u;
+    n0s = n0 * S;
+    lx = SX && dom ? slab_pos(x, nx, np) : -1;
+    ly = SY && y >= 0 && y < ny ? slab_pos(y, ny, np) : -1;  // uniform across the wave
+    srcr = src_wave(gv, n0, dom && u >= 1 && u <= TX + 2 && v >= 1 && v <= TY + 2, k0 - 1, k1);
+    pf.tn = 2 * np;
+    pf.u = u;
+    if (PML) {
+      const int tn = 2 * np;
+      if (SX && v == 0) {
+        const int xl = x >= 0 && x < nx ? slab_pos(x, nx, np) : -1;
+        for (int q = 0; q < P_NROW; ++q) sm.px[q][u] = xl >= 0 ? ldg(gv.prof[0], (unsigned)(q * tn + xl)) : T(0);
+      }
+      if (SY && ly >= 0)
+        for (int q = 0; q < 3; ++q) {
+          pf.ye[q] = uniform(ldg(gv.prof[1], (unsigned)((P_BE + q) * tn + ly)));
+          pf.yh[q] = uniform(ldg(gv.prof[1], (unsigned)((P_BH + q) * tn + ly)));
+        }
+      if (SZ)
+        for (int q = tid; q < P_NROW * tn; q += NT) sm.pz[q] = ldg(gv.prof[2], (unsigned)q);
+      qx = SX ? (unsigned)max(lx, 0) + 2u * np * (unsigned)(dom ? y : 0) : 0u;
+      qy = SY ? (unsigned)(dom ? x : 0) + (unsigned)nx * (unsigned)max(ly, 0) : 0u;
+    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      fi[c] = gv.fi[c];
+      fo[c] = gv.fo[c];
+    }
+    cls = (const CI*)gv.cls;
+    // plane kb, and E of plane kb + 1
+    const int kb = k0 - 2;
+    const unsigned pa = (unsigned)max(kb, 0) * sxy, pb = (unsigned)min(max(kb + 1, 0), nz - 1) * sxy;
+    craw = ldg(cls, n0 + pa);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      r.h0[0][c] = ldb(fi[3 + c], n0s + pa * S);
+      r.e0[0][c] = ldb(fi[c], n0s + pa * S);
+      r.e0[1][c] = ldb(fi[c], n0s + pb * S);
+    }
+    if (PML && kb >= 0) psi<true>(kb, r.ph[0], r.pe[0]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) r.h1[q][c] = r.e1[q][c] = r.h2[q][c] = r.e2[c] = T(0);
+    r.co[1] = r.co[2] = row_of(0, false);
+    sm.e0[0][v][u] = r.e0[0][0];
+    sm.e0[1][v][u] = r.e0[0][2];
+    __syncthreads();
+    for (int k = kb;;) {
+      iter<0, false>(k);
+      if (++k > k1) { iter<1, true>(k); break; }
+      iter<1, false>(k);
+      if (++k > k1) { iter<2, true>(k); break; }
+      iter<2, false>(k);
+      if (++k > k1) { iter<0, true>(k); break; }
+    }
+  }
+};
 
 // Probes of a two-step pass: the intermediate step's values are recomputed
 // point by point from the input set (which the pass leaves untouched) with
@@ -538,59 +861,134 @@ __device__ __forceinline__ void e1_at(const GridView<T>& g, int x, int y, int k,
                  sr.hi);
 }
 
-// Probes: one block of PR_NT threads per probe.  Thread `tid` sums terms
-// tid, tid + PR_NT, ... of the probe in order; the lanes of each wave are
-// then summed by a shuffle tree and the four wave sums in order.  Every probe
-// kernel sums in this one FP64 order, so that all variants, and a batch and
-// its grids run alone, agree bit for bit.
+// Probes: PR_NT threads per probe (a block, or one of several groups of a
+// larger block).  Thread `t` of the group sums terms t, t + PR_NT, ... of the
+// probe in order; the lanes of each wave are then summed by a shuffle tree
+// and the four wave sums in order.  Every probe kernel sums in this one FP64
+// order, so that all variants, and a batch and its grids run alone, agree bit
+// for bit.
 constexpr int PR_NT = 256;
 
-// Block sum of `a` in the fixed order; `red` holds 4 doubles of LDS.  The
-// total is returned to every thread.
-__device__ __forceinline__ double probe_block_sum(double a, double* red) {
+// Sum of `a` over the group's threads in the fixed order; `red` holds the
+// group's 4 doubles of LDS.  The total is returned to every thread.
+__device__ __forceinline__ double probe_sum(double a, int t, double* red) {
   for (int o = 32; o > 0; o >>= 1) a += __shfl_down(a, o, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+  if ((t & 63) == 0) red[t >> 6] = a;
   __syncthreads();
   return ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-// Probe p of a two-step pass, one block: sample `step` (S1: recomputed from
-// the input set, which the pass leaves untouched) and sample `step` + 1 (S2:
-// read from the output set).  `red` holds 8 doubles of LDS.
-template <typename T, typename CI, bool PML, bool S1 = true, bool S2 = true>
-__device__ __forceinline__ void probe_tb2(const GridView<T>& g, int p, int step, double* red) {
+// Probe p of a two-step pass: sample `step`, recomputed from the input set
+// (which the pass leaves untouched), and with S2 sample `step` + 1, read from
+// the output set.  Thread t of the group; groups past the last probe (p = -1)
+// only keep the block's barriers.  `red` holds the group's 8 doubles of LDS.
+template <typename T, typename CI, bool PML, bool S2>
+__device__ __forceinline__ void probe_tb2(const GridView<T>& g, int p, int step, int t, double* red) {
   double a1 = 0.0, a2 = 0.0;
-  for (int t = g.pr_off[p] + (int)threadIdx.x; t < g.pr_off[p + 1]; t += PR_NT) {
-    const int c = g.term_comp[t];
-    const unsigned n = (unsigned)g.term_idx[t];
-    if (S1) {
-      const int x = (int)(n % g.nx), y = (int)((n / g.nx) % g.ny), k = (int)(n / g.sxy);
-      T v3[3];
-      if (c < 3) e1_at<T, CI, PML>(g, x, y, k, step, v3);
-      else h1_at<T, CI, PML>(g, x, y, k, v3);
-      const int cc = c < 3 ? c : c - 3;
-      const T v1 = cc == 0 ? v3[0] : cc == 1 ? v3[1] : v3[2];
-      a1 += g.term_w[t] * (double)v1;
-    }
+  const int q0 = p < 0 ? 0 : g.pr_off[p], q1 = p < 0 ? 0 : g.pr_off[p + 1];
+  for (int q = q0 + t; q < q1; q += PR_NT) {
+    const int c = g.term_comp[q];
+    const unsigned n = (unsigned)g.term_idx[q];
+    const int x = (int)(n % g.nx), y = (int)((n / g.nx) % g.ny), k = (int)(n / g.sxy);
+    T v3[3];
+    if (c < 3) e1_at<T, CI, PML>(g, x, y, k, step, v3);
+    else h1_at<T, CI, PML>(g, x, y, k, v3);
+    const int cc = c < 3 ? c : c - 3;
+    const T v1 = cc == 0 ? v3[0] : cc == 1 ? v3[1] : v3[2];
+    a1 += g.term_w[q] * (double)v1;
     if (S2) {
       const T* f = c == 0 ? g.fo[0] : c == 1 ? g.fo[1] : c == 2 ? g.fo[2] : c == 3 ? g.fo[3] : c == 4 ? g.fo[4] : g.fo[5];
-      a2 += g.term_w[t] * (double)ldg((const T*)f, n);
+      a2 += g.term_w[q] * (double)ldg((const T*)f, n);
     }
   }
-  if (S1) a1 = probe_block_sum(a1, red);
-  if (S2) a2 = probe_block_sum(a2, red + 4);
-  if (threadIdx.x == 0) {
-    if (S1) g.pr_out[(long long)p * g.max_steps + step] = a1;
+  a1 = probe_sum(a1, t, red);
+  if (S2) a2 = probe_sum(a2, t, red + 4);
+  if (t == 0 && p >= 0) {
+    g.pr_out[(long long)p * g.max_steps + step] = a1;
     if (S2) g.pr_out[(long long)p * g.max_steps + step + 1] = a2;
   }
 }
 
-template <typename T, typename CI, bool PML, bool S1 = true, bool S2 = true>
-__global__ __launch_bounds__(PR_NT) void k_probes_tb2(GridView<T> g, int step) {
+// Probe p at sample `step` from the view's input fields (p = -1: none).
+template <typename T>
+__device__ __forceinline__ void probe_one(const GridView<T>& g, int p, int step, int t, double* red) {
+  double acc = 0.0;
+  const int q0 = p < 0 ? 0 : g.pr_off[p], q1 = p < 0 ? 0 : g.pr_off[p + 1];
+  for (int q = q0 + t; q < q1; q += PR_NT) {
+    const int c = g.term_comp[q];
+    const T* f = c == 0 ? g.fi[0] : c == 1 ? g.fi[1] : c == 2 ? g.fi[2] : c == 3 ? g.fi[3] : c == 4 ? g.fi[4] : g.fi[5];
+    acc += g.term_w[q] * (double)ldg(f, (unsigned)g.term_idx[q]);
+  }
+  acc = probe_sum(acc, t, red);
+  if (t == 0 && p >= 0) g.pr_out[(long long)p * g.max_steps + step] = acc;
+}
+
+// One tile of a two-step pass by the code its CPML needs: tiles whose region
+// (halo and pipeline planes included) is clear of some slabs leave their code
+// out.  FP64 tiles in the CPML would spill in March's registers; they take
+// the one-plane-at-a-time tile.
+template <typename T, int TY>
+union TileSmem {
+  MarchSmem<T, TY> m;
+  TB2Smem<T, TY> t;
+};
+template <int TY>
+union TileSmem<float, TY> {
+  MarchSmem<float, TY> m;
+};
+template <typename T, typename CI, bool PML, int TY, bool FULL>
+__device__ __forceinline__ void tb2_any(const GridView<T>& g, ColdView<T> cold, TileSmem<T, TY>& sm, int i0, int j0,
+                                        int iw, int jh, int k0, int k1, int step) {
+  if constexpr (!PML) {
+    March<T, CI, TY, 0>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
+  } else {
+    const int n = g.npml;
+    const bool cx = i0 - 2 >= n && i0 + 62 <= g.nx - n, cy = j0 - 2 >= n && j0 + TY + 2 <= g.ny - n,
+               cz = k0 - 2 >= n && k1 < g.nz - n;
+    if (FULL && cx && cy && cz) {
+      March<T, CI, TY, 0>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
+    } else if constexpr (sizeof(T) == 8) {
+      tb2_tile<T, CI, true, TY, 7, false, true>(g, sm.t, i0, j0, iw, jh, k0, k1, step);
+    } else {
+      if (FULL && cx && cy) March<T, CI, TY, 4>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
+      else if (cy) March<T, CI, TY, 5>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
+      else if (FULL && cx) March<T, CI, TY, 6>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
+      else March<T, CI, TY, 7>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
+    }
+  }
+}
+
+// Registers a lane may use: FP32 tiles with CPML code take what one block per
+// CU leaves them, tiles without it stay below 80 so that two 12-wave blocks
+// share a CU.
+constexpr int tb2_waves(int size, bool pml, int ty) { return size == 8 ? 1 : pml || ty == 12 ? (ty + 4) / 4 : 6; }
+
+// A whole two-step pass in one launch: blocks 0 .. npb - 1 each record a few
+// probes (sample `step` recomputed from the input set and, with `prev`, the
+// previous pass's second sample, step - 1, which is the input set itself),
+// the others march one 60 x TY tile over kz planes.  The probes of a pass's
+// last step are left to the next pass or to k_probes after the last one.
+// `run`: tiles that an XCD takes in a row (xcd_runs).
+template <typename T, typename CI, bool PML, int TY>
+__global__ __launch_bounds__(64 * (TY + 4), tb2_waves(sizeof(T), PML, TY)) void k_tb2(GridView<T> g, int step, int kz,
+                                                                                   int ntx, int nty, int npb,
+                                                                                   int prev, int run) {
   step = gstep(g, step);
-  __shared__ double red[8];
-  if ((int)blockIdx.x >= g.n_probe) return;  // uniform per block
-  probe_tb2<T, CI, PML, S1, S2>(g, blockIdx.x, step, red);
+  __shared__ TileSmem<T, TY> sm;
+  constexpr int GRP = 64 * (TY + 4) / PR_NT;  // probes per block
+  __shared__ double red[12 * GRP];
+  if ((int)blockIdx.x < npb) {  // uniform per block
+    const int grp = (int)threadIdx.x / PR_NT, t = (int)threadIdx.x % PR_NT, q = (int)blockIdx.x * GRP + grp;
+    const int p = q < g.n_probe ? q : -1;
+    probe_tb2<T, CI, PML, false>(g, p, step, t, red + 12 * grp);
+    if (prev) probe_one(g, p, step - 1, t, red + 12 * grp + 8);
+    return;
+  }
+  const int tile = xcd_runs((int)blockIdx.x - npb, (int)gridDim.x - npb, run);
+  const int tile_x = tile % ntx, rest = tile / ntx, k0 = (rest / nty) * kz;
+  // the view is the kernel's first argument: read again where it is needed
+  const ColdView<T> cold{(typename ColdView<T>::P)__builtin_amdgcn_kernarg_segment_ptr()};
+  tb2_any<T, CI, PML, TY, true>(g, cold, sm, tile_x * 60, (rest % nty) * TY, 60, TY, k0, min(k0 + kz, g.nz), step);
 }
 
 // Batched two-step probes: entry q of the list is (grid, probe).
@@ -601,7 +999,7 @@ __global__ __launch_bounds__(PR_NT) void k_probes_tb2_batch(const GridView<T>* _
   __shared__ double red[8];
   if ((int)blockIdx.x >= n) return;  // uniform per block
   const int2 e = plist[blockIdx.x];
-  probe_tb2<T, CI, true>(views[e.x], e.y, *d_step + offset, red);
+  probe_tb2<T, CI, true, true>(views[e.x], e.y, *d_step + offset, (int)threadIdx.x, red);
 }
 
 // Batched two-step pass: tile (grid, i0 | iw << 16, j0 | jh << 16,
@@ -668,27 +1066,15 @@ __global__ void k_qreset(int* ctr) {
 
 // ---------------------------------------------------------------------------
 // probes of a one-step pass: one block per probe, the fixed FP64 order of
-// probe_block_sum
+// probe_sum
 // ---------------------------------------------------------------------------
-
-template <typename T>
-__device__ __forceinline__ void probe_one(const GridView<T>& g, int p, int step, double* red) {
-  double acc = 0.0;
-  for (int t = g.pr_off[p] + (int)threadIdx.x; t < g.pr_off[p + 1]; t += PR_NT) {
-    const int c = g.term_comp[t];
-    const T* f = c == 0 ? g.fi[0] : c == 1 ? g.fi[1] : c == 2 ? g.fi[2] : c == 3 ? g.fi[3] : c == 4 ? g.fi[4] : g.fi[5];
-    acc += g.term_w[t] * (double)ldg(f, (unsigned)g.term_idx[t]);
-  }
-  acc = probe_block_sum(acc, red);
-  if (threadIdx.x == 0) g.pr_out[(long long)p * g.max_steps + step] = acc;
-}
 
 template <typename T>
 __global__ __launch_bounds__(PR_NT) void k_probes(GridView<T> g, int step) {
   step = gstep(g, step);
   __shared__ double red[4];
   if ((int)blockIdx.x >= g.n_probe) return;  // uniform per block
-  probe_one(g, blockIdx.x, step, red);
+  probe_one(g, blockIdx.x, step, (int)threadIdx.x, red);
 }
 
 // Batched probes: entry q of the list is (grid, probe); one block each.
@@ -699,7 +1085,7 @@ __global__ __launch_bounds__(PR_NT) void k_probes_batch(const GridView<T>* __res
   __shared__ double red[4];
   if ((int)blockIdx.x >= n) return;  // uniform per block
   const int2 e = plist[blockIdx.x];
-  probe_one(views[e.x], e.y, *d_step + offset, red);
+  probe_one(views[e.x], e.y, *d_step + offset, (int)threadIdx.x, red);
 }
 
 __global__ void k_add(int* p, int v) {
@@ -975,61 +1361,9 @@ hipError_t launch_lists(const GridView<T>& g, int step, const int4* tiles, const
   return hipGetLastError();
 }
 
-template <typename T, typename CI, int TY>
-hipError_t launch_lists_tb2(const GridView<T>& g, int step, const int4* tiles, const int* counts, hipStream_t st,
-                            hipStream_t st2, void* ev_src) {
-  if (sizeof(CI) == 1 && g.ncls > 256) return hipErrorInvalidValue;
-  constexpr bool D = sizeof(T) == 8;
-  const dim3 blk(64 * (TY + 4));
-  const int4* t1 = tiles + counts[0];
-  const int4* t2 = t1 + counts[1];
-  const int4* t3 = t2 + counts[2];
-  if (counts[0] > 0)
-    hipLaunchKernelGGL((k_tb2_list<T, CI, true, TY, D ? 7 : 4>), dim3((unsigned)counts[0]), blk, 0, st, g, tiles,
-                       step);
-  // Second stream: the few corner tiles first, beside the z-only ones; the
-  // y-slab tiles last, to fill the end of the pass.
-  if (counts[3] > 0)
-    hipLaunchKernelGGL((k_tb2_list<T, CI, true, TY, 7>), dim3((unsigned)counts[3]), blk, 0, st2, g, t3, step);
-  if (counts[1] > 0)
-    hipLaunchKernelGGL((k_tb2_list<T, CI, true, TY, D ? 7 : 5>), dim3((unsigned)counts[1]), blk, 0, st2, g, t1, step);
-  if (counts[2] > 0)
-    hipLaunchKernelGGL((k_tb2_list<T, CI, true, TY, D ? 7 : 6>), dim3((unsigned)counts[2]), blk, 0, st2, g, t2, step);
-  // tiles that read an oblique wire's source amplitudes, once the wire
-  // kernels (on a third stream) have written them
-  if (ev_src) {
-    const hipError_t we = hipStreamWaitEvent(st2, (hipEvent_t)ev_src, 0);
-    if (we != hipSuccess) return we;
-  }
-  // (those clear of the x and y slabs, listed first, as z-only tiles)
-  const int4* t4 = t3 + counts[3];
-  if (counts[5] > 0)
-    hipLaunchKernelGGL((k_tb2_list<T, CI, true, TY, D ? 7 : 4>), dim3((unsigned)counts[5]), blk, 0, st2, g, t4, step);
-  if (counts[4] > counts[5])
-    hipLaunchKernelGGL((k_tb2_list<T, CI, true, TY, 7>), dim3((unsigned)(counts[4] - counts[5])), blk, 0, st2, g,
-                       t4 + counts[5], step);
-  // The probes' first sample, recomputed from the input set (which no group
-  // writes), runs on the second stream beside the clear tiles; the caller
-  // reads the second sample after the join (launch_probes2 with first = 0).
-  if (g.n_probe > 0)
-    hipLaunchKernelGGL((k_probes_tb2<T, CI, true, true, false>), dim3((unsigned)g.n_probe), dim3(PR_NT), 0, st2, g,
-                       step);
-  return hipGetLastError();
-}
-
 template <typename T>
-hipError_t lists_any(const GridView<T>& g, int cls16, int variant, int step, int ty, const int4* tiles,
-                     const int* counts, hipStream_t st, hipStream_t st2, void* ev) {
-  if (variant == 3) {
-    if (ty == 4)
-      return cls16 ? launch_lists_tb2<T, uint16_t, 4>(g, step, tiles, counts, st, st2, ev)
-                   : launch_lists_tb2<T, uint8_t, 4>(g, step, tiles, counts, st, st2, ev);
-    if (ty == 12)
-      return cls16 ? launch_lists_tb2<T, uint16_t, 12>(g, step, tiles, counts, st, st2, ev)
-                   : launch_lists_tb2<T, uint8_t, 12>(g, step, tiles, counts, st, st2, ev);
-    return cls16 ? launch_lists_tb2<T, uint16_t, 8>(g, step, tiles, counts, st, st2, ev)
-                 : launch_lists_tb2<T, uint8_t, 8>(g, step, tiles, counts, st, st2, ev);
-  }
+hipError_t lists_any(const GridView<T>& g, int cls16, int step, int ty, const int4* tiles, const int* counts,
+                     hipStream_t st, hipStream_t st2, void* ev) {
   if (ty == 4)
     return cls16 ? launch_lists<T, uint16_t, 4>(g, step, tiles, counts, st, st2, ev)
                  : launch_lists<T, uint8_t, 4>(g, step, tiles, counts, st, st2, ev);
@@ -1038,47 +1372,61 @@ hipError_t lists_any(const GridView<T>& g, int cls16, int variant, int step, int
 }
 
 template <typename T, typename CI, bool PML, int TY>
-hipError_t launch_tb2(const GridView<T>& g, int step, int kz, hipStream_t st) {
+hipError_t launch_tb2(const GridView<T>& g, int step, int kz, int run, int prev, hipStream_t st) {
+  constexpr int GRP = 64 * (TY + 4) / PR_NT;
   const int ntx = (g.nx + 59) / 60, nty = (g.ny + TY - 1) / TY, ntz = (g.nz + kz - 1) / kz;
-  const long long nb = (long long)ntx * nty * ntz;
+  const int npb = (g.n_probe + GRP - 1) / GRP;
+  const long long nb = (long long)ntx * nty * ntz + npb;
   if (nb > 0x7fffffff || (sizeof(CI) == 1 && g.ncls > 256)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_tb2<T, CI, PML, TY>), dim3((unsigned)nb), dim3(64 * (TY + 4)), 0, st, g, step, kz, ntx,
-                     nty);
+  hipLaunchKernelGGL((k_tb2<T, CI, PML, TY>), dim3((unsigned)nb), dim3(64 * (TY + 4)), 0, st, g, step, kz, ntx, nty,
+                     npb, prev, run);
   return hipGetLastError();
 }
 
 template <typename T, typename CI>
-hipError_t step_tb2(const GridView<T>& g, int step, int tile_y, int tile_z, hipStream_t st) {
-  const int kz = tile_z > 0 ? tile_z : 64;
+hipError_t step_tb2(const GridView<T>& g, int step, int ty, int kz, int run, int prev, hipStream_t st) {
   const bool pml = g.npml > 0;
-  if (tile_y == 4)
-    return pml ? launch_tb2<T, CI, true, 4>(g, step, kz, st) : launch_tb2<T, CI, false, 4>(g, step, kz, st);
-  if (tile_y == 12)
-    return pml ? launch_tb2<T, CI, true, 12>(g, step, kz, st) : launch_tb2<T, CI, false, 12>(g, step, kz, st);
-  return pml ? launch_tb2<T, CI, true, 8>(g, step, kz, st) : launch_tb2<T, CI, false, 8>(g, step, kz, st);
+  if (ty == 4)
+    return pml ? launch_tb2<T, CI, true, 4>(g, step, kz, run, prev, st)
+               : launch_tb2<T, CI, false, 4>(g, step, kz, run, prev, st);
+  if (ty == 12)
+    return pml ? launch_tb2<T, CI, true, 12>(g, step, kz, run, prev, st)
+               : launch_tb2<T, CI, false, 12>(g, step, kz, run, prev, st);
+  return pml ? launch_tb2<T, CI, true, 8>(g, step, kz, run, prev, st)
+             : launch_tb2<T, CI, false, 8>(g, step, kz, run, prev, st);
+}
+
+int launch_tb2_pass(int prec, const void* view, int cls16, int step, int ty, int kz, int run, int prev,
+                    void* stream) {
+  hipStream_t st = (hipStream_t)stream;
+  if (prec == 64) {
+    const GridView<double>& g = *(const GridView<double>*)view;
+    return (int)(cls16 ? step_tb2<double, uint16_t>(g, step, ty, kz, run, prev, st)
+                       : step_tb2<double, uint8_t>(g, step, ty, kz, run, prev, st));
+  }
+  const GridView<float>& g = *(const GridView<float>*)view;
+  return (int)(cls16 ? step_tb2<float, uint16_t>(g, step, ty, kz, run, prev, st)
+                     : step_tb2<float, uint8_t>(g, step, ty, kz, run, prev, st));
 }
 
 template <typename T>
 hipError_t step_any(const GridView<T>& g, int cls16, int variant, int step, int tile_y, int tile_z,
                     hipStream_t st) {
-  if (variant == 3)
-    return cls16 ? step_tb2<T, uint16_t>(g, step, tile_y, tile_z, st)
-                 : step_tb2<T, uint8_t>(g, step, tile_y, tile_z, st);
   if (variant == 2)
     return cls16 ? step_fused<T, uint16_t>(g, step, tile_y, tile_z, st)
                  : step_fused<T, uint8_t>(g, step, tile_y, tile_z, st);
   return cls16 ? step_split<T, uint16_t>(g, step, st) : step_split<T, uint8_t>(g, step, st);
 }
 
-int launch_lists_step(int prec, const void* view, int cls16, int variant, int step, int tile_y, const void* tiles,
+int launch_lists_step(int prec, const void* view, int cls16, int step, int tile_y, const void* tiles,
                       const int* counts, void* stream, void* stream2, void* ev_src) {
   hipStream_t st = (hipStream_t)stream, st2 = (hipStream_t)stream2;
   const int4* t = (const int4*)tiles;
-  const int ty = tile_y == 4 ? 4 : (tile_y == 12 && variant == 3) ? 12 : 8;
-  hipError_t e = prec == 64 ? lists_any<double>(*(const GridView<double>*)view, cls16, variant, step, ty, t, counts,
-                                                st, st2, ev_src)
-                            : lists_any<float>(*(const GridView<float>*)view, cls16, variant, step, ty, t, counts,
-                                               st, st2, ev_src);
+  const int ty = tile_y == 4 ? 4 : 8;
+  hipError_t e = prec == 64 ? lists_any<double>(*(const GridView<double>*)view, cls16, step, ty, t, counts, st, st2,
+                                                ev_src)
+                            : lists_any<float>(*(const GridView<float>*)view, cls16, step, ty, t, counts, st, st2,
+                                               ev_src);
   return (int)e;
 }
 
@@ -1098,30 +1446,6 @@ hipError_t probes_any(const GridView<T>& g, int step, hipStream_t st) {
   if (g.n_probe <= 0) return hipSuccess;
   hipLaunchKernelGGL((k_probes<T>), dim3((unsigned)g.n_probe), dim3(PR_NT), 0, st, g, step);
   return hipGetLastError();
-}
-
-template <typename T>
-hipError_t probes2_any(const GridView<T>& g, int cls16, int step, bool first, hipStream_t st) {
-  if (g.n_probe <= 0) return hipSuccess;
-  const dim3 grd((unsigned)g.n_probe), blk(PR_NT);
-  const bool pml = g.npml > 0;
-  if (!first) {  // the second sample only (two-step tile lists, which have a CPML)
-    if (cls16) hipLaunchKernelGGL((k_probes_tb2<T, uint16_t, true, false, true>), grd, blk, 0, st, g, step);
-    else hipLaunchKernelGGL((k_probes_tb2<T, uint8_t, true, false, true>), grd, blk, 0, st, g, step);
-  } else if (cls16) {
-    if (pml) hipLaunchKernelGGL((k_probes_tb2<T, uint16_t, true>), grd, blk, 0, st, g, step);
-    else hipLaunchKernelGGL((k_probes_tb2<T, uint16_t, false>), grd, blk, 0, st, g, step);
-  } else {
-    if (pml) hipLaunchKernelGGL((k_probes_tb2<T, uint8_t, true>), grd, blk, 0, st, g, step);
-    else hipLaunchKernelGGL((k_probes_tb2<T, uint8_t, false>), grd, blk, 0, st, g, step);
-  }
-  return hipGetLastError();
-}
-
-int launch_probes2(int prec, const void* view, int cls16, int step, int first, void* stream) {
-  hipStream_t st = (hipStream_t)stream;
-  if (prec == 64) return (int)probes2_any<double>(*(const GridView<double>*)view, cls16, step, first != 0, st);
-  return (int)probes2_any<float>(*(const GridView<float>*)view, cls16, step, first != 0, st);
 }
 
 int launch_probes(int prec, const void* view, int step, void* stream) {

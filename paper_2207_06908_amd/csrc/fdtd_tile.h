@@ -105,14 +105,12 @@ __device__ __forceinline__ void h_core_pf(const PF& pf, const int l[3], const T*
   hnew[2] = h_new(hold[2], cf[K_DBZ], a_hz, b_hz);
 }
 
-// E^{n+1} of node n from H^{n+1/2} at the node (hx, hy, hz), at x-1 (hy_i,
-// hz_i), y-1 (hx_j, hz_j) and k-1 (hx_k, hy_k), then the sources of `step`;
-// ps is the node's E-type CPML state, advanced in place.
+// E^{n+1} of one node from H^{n+1/2} at the node (hx, hy, hz), at x-1 (hy_i,
+// hz_i), y-1 (hx_j, hz_j) and k-1 (hx_k, hy_k), before any source; ps is the
+// node's E-type CPML state, advanced in place.
 template <typename T, bool PML, typename PF>
-__device__ __forceinline__ void e_core_pf(const PF& pf, const GridView<T>& g, const int l[3], unsigned n,
-                                          const T* cf, T hx, T hy, T hz, T hx_j, T hx_k, T hy_i, T hy_k, T hz_i,
-                                          T hz_j, const T eold[3], int step, T ps[3][2], T enew[3], int slo,
-                                          int shi) {
+__device__ __forceinline__ void e_core_pf(const PF& pf, const int l[3], const T* cf, T hx, T hy, T hz, T hx_j, T hx_k,
+                                          T hy_i, T hy_k, T hz_i, T hz_j, const T eold[3], T ps[3][2], T enew[3]) {
   T a_ex = hz - hz_j, b_ex = hy - hy_k;  // Ex: dHz/dy - dHy/dz
   T a_ey = hx - hx_k, b_ey = hz - hz_i;  // Ey: dHx/dz - dHz/dx
   T a_ez = hy - hy_i, b_ez = hx - hx_j;  // Ez: dHy/dx - dHx/dy
@@ -136,14 +134,19 @@ __device__ __forceinline__ void e_core_pf(const PF& pf, const GridView<T>& g, co
   enew[0] = e_new(eold[0], cf[K_CAX], cf[K_CBX], a_ex, b_ex);
   enew[1] = e_new(eold[1], cf[K_CAY], cf[K_CBY], a_ey, b_ey);
   enew[2] = e_new(eold[2], cf[K_CAZ], cf[K_CBZ], a_ez, b_ez);
-  // ideal current sources: E -= Cb I / dx^2 (precomputed per step), from the
-  // entries [slo, shi) of the source list (empty where none can apply).  The
-  // tile kernels pass a range that is uniform across the wave, so that the
-  // scan reads the list with scalar loads.
+}
+
+// Ideal current sources of node n in step `step`: E -= Cb I / dx^2
+// (precomputed per step), from the entries [slo, shi) of the source list
+// (empty where none can apply).  g is a view or anything that dereferences to
+// one.  The tile kernels pass a range that is uniform across the wave, so
+// that the scan reads the list with scalar loads.
+template <typename T, typename G>
+__device__ __forceinline__ void e_sources(const G& g, int slo, int shi, unsigned n, int step, T enew[3]) {
   for (int s = slo; s < shi; ++s) {
-    if ((unsigned)ldg(g.src_idx, (unsigned)s) != n) continue;
-    const T v = ldg(g.src_amp, (unsigned)s * (unsigned)g.max_steps + (unsigned)step);
-    const int comp = ldg(g.src_comp, (unsigned)s);
+    if ((unsigned)ldg(g->src_idx, (unsigned)s) != n) continue;
+    const T v = ldg(g->src_amp, (unsigned)s * (unsigned)g->max_steps + (unsigned)step);
+    const int comp = ldg(g->src_comp, (unsigned)s);
     enew[0] = comp == 0 ? enew[0] - v : enew[0];
     enew[1] = comp == 1 ? enew[1] - v : enew[1];
     enew[2] = comp == 2 ? enew[2] - v : enew[2];
@@ -160,8 +163,8 @@ template <typename T, bool PML>
 __device__ __forceinline__ void e_core(const GridView<T>& g, const int l[3], unsigned n, const T* cf, T hx, T hy,
                                        T hz, T hx_j, T hx_k, T hy_i, T hy_k, T hz_i, T hz_j, const T eold[3],
                                        int step, T ps[3][2], T enew[3], int slo, int shi) {
-  e_core_pf<T, PML>(ProfG<T>{g}, g, l, n, cf, hx, hy, hz, hx_j, hx_k, hy_i, hy_k, hz_i, hz_j, eold, step, ps, enew,
-                    slo, shi);
+  e_core_pf<T, PML>(ProfG<T>{g}, l, cf, hx, hy, hz, hx_j, hx_k, hy_i, hy_k, hz_i, hz_j, eold, ps, enew);
+  e_sources(&g, slo, shi, n, step, enew);
 }
 
 // Sources of column n0 (= x + nx*y) as a range [lo, hi) of the grouped
@@ -292,19 +295,15 @@ __device__ __forceinline__ void debye_point(const DebyeView<T>& d, int cid, unsi
 // ---------------------------------------------------------------------------
 
 // Block b of nb (dealt to the 8 XCDs round robin) takes list entry
-// xcd_runs(b, nb): each XCD gets runs of XCD_RUN consecutive entries, interleaved
-// with the other XCDs' runs.  Neighbouring tiles then share an L2 while every
-// XCD's reads stay spread over the whole grid.  Blocks past the last full
-// round of runs keep their own index, so the map is one to one.  On the
-// 512 x 512 x 384 two-step pass (Mcell-updates/s, same process), runs of 9
-// gave 112.3k, 4 112.1k, 2 110.7k, 1 (plain order) 107.8k, 18 111.9k,
-// 36 110.5k, 72 107.6k, and one run per XCD (xcd_tile) 106.0k.
-constexpr int XCD_RUN = 9;
-__device__ __forceinline__ int xcd_runs(int b, int nb) {
-  const int nf = nb / (8 * XCD_RUN) * (8 * XCD_RUN);
+// xcd_runs(b, nb, run): each XCD gets runs of `run` consecutive entries,
+// interleaved with the other XCDs' runs.  Neighbouring tiles then share an L2
+// while every XCD's reads stay spread over the whole grid.  Blocks past the
+// last full round of runs keep their own index, so the map is one to one.
+__device__ __forceinline__ int xcd_runs(int b, int nb, int run) {
+  const int nf = nb / (8 * run) * (8 * run);
   if (b >= nf) return b;
-  const int x = b & 7, t = b >> 3, g = t / XCD_RUN;
-  return (g * 8 + x) * XCD_RUN + (t - g * XCD_RUN);
+  const int x = b & 7, t = b >> 3, g = t / run;
+  return (g * 8 + x) * run + (t - g * run);
 }
 
 // Blocks are dealt round-robin to the 8 XCDs; give each XCD a contiguous run
