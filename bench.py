@@ -137,14 +137,12 @@ def bench_batch(warmup: int = 100, graph_steps: int = 100, tune: bool = True):
         S.apply(sc, g)
         grids.append(g)
     tile = (32, 8, 32)
-    persistent = True
     b = fdtd.Batch(grids, tile=tile, graph_steps=graph_steps)
     if tune:
         b.bind()
         c = autotune.tune_batch(b, autotune.batch_key([(s.nx, s.ny, s.nz) for s in scs], scs[0].npml))
         tile = (c["tile_x"], c["tile_y"], c["tile_z"])
         autotune.apply_batch(b, c, graph_steps)
-        persistent = c.get("persistent", True)
     b.run(warmup)
     torch.cuda.synchronize()
     b.timing(True)
@@ -155,9 +153,7 @@ def bench_batch(warmup: int = 100, graph_steps: int = 100, tune: bool = True):
     achieved = bytes_step * steps / (ms / 1e3) / 1e9
     out = {"workload": f"{len(scs)} independent electrode grids, 32-96^3 (x grown to fit the electrode), "
                        f"dx 0.25 m, 8-cell CPML, {steps} steps, HIP graph of {graph_steps} steps",
-           "kernel": (("k_tb2_batch_q: two persistent work-queue launches per two-step pass (tiles clear of "
-                        "the y slabs; the rest)" if persistent
-                       else "k_tb2_batch: one launch per CPML group and two-step pass") if tile[0] == 60
+           "kernel": ("k_tb2_batch: one launch per two-step pass" if tile[0] == 60
                       else "k_fused_batch: one launch per step"),
            "tile": list(tile),
            "cells": cells, "value": round(cells * steps / (ms / 1e3) / 1e6, 1), "unit": "Mcell-updates/s",
@@ -273,8 +269,8 @@ def bench_oblique(steps: int = 400, warmup: int = 20):
     ms = e0.elapsed_time(e1)
     out = {"workload": "512x512x384 Yee FDTD as above plus a slanted 5 cm conductor (20 x 12 x 30 cells, "
                        "37 segments), driven at its base",
-           "kernel": "k_tb2_list (two-step pass over CPML groups; the wire's edges are sources whose amplitudes "
-                     "k_owire_cur/k_owire_q/k_owire_amp/k_owire_e1 write on a third stream)",
+           "kernel": "k_tb2 (two-step pass; the wire's edges are sources whose amplitudes "
+                     "k_owire_cur/k_owire_q/k_owire_amp/k_owire_e1 write before it)",
            "steps": steps, "value": round(sc.cells * steps / (ms / 1e3) / 1e6, 1), "unit": "Mcell-updates/s",
            "ms_per_step": round(ms / steps, 5)}
     del g
@@ -305,8 +301,8 @@ def bench_tower(steps: int = 400, warmup: int = 20):
     out = {"workload": "512x512x384 Yee FDTD grid and soil as above; a 30 m lattice tower of oblique wires (4 legs "
                        f"cut at a ring, a 4-wire ring, 2 cross-arms; {len(sc.owires)} wires, {segs} segments, "
                        f"{len(sc.ojunctions)} junctions) struck through a channel wire by 10 kA 1/50 us",
-           "kernel": "k_tb2_list (two-step pass over CPML groups; the wires' edges are sources written by "
-                     "k_owire_cur/k_owire_q/k_owire_junc/k_owire_amp/k_owire_e1 on a third stream)",
+           "kernel": "k_tb2 (two-step pass; the wires' edges are sources written by "
+                     "k_owire_cur/k_owire_q/k_owire_junc/k_owire_amp/k_owire_e1 before it)",
            "steps": steps, "value": round(sc.cells * steps / (ms / 1e3) / 1e6, 1), "unit": "Mcell-updates/s",
            "ms_per_step": round(ms / steps, 5)}
     del g
@@ -439,7 +435,7 @@ def main():
     ap.add_argument("--warmup", type=int, default=50)
     ap.add_argument("--variant", default="tuned", choices=["tuned", "auto", "split", "fused", "tb2"],
                     help="tuned: launch shape from the autotuner (cached); auto: the library default "
-                         "(two-step pass, 60x8 tiles, TZ 28, on this grid with a CPML)")
+                         "(two-step pass, 60x12 tiles, TZ 20, on this grid)")
     ap.add_argument("--tile-y", type=int, default=0)
     ap.add_argument("--tile-z", type=int, default=0)
     ap.add_argument("--cpu-steps", type=int, default=100)
@@ -495,7 +491,7 @@ def main():
     cells = sc.cells
     value = cells * a.steps / (ms / 1e3) / 1e6
     vname = "tb2" if a.variant == "auto" else a.variant
-    ty = a.tile_y or 8
+    ty = a.tile_y or (12 if vname == "tb2" else 8)
     tz = a.tile_z or (20 if vname == "tb2" else 32)
     traffic = MEASURED_TRAFFIC.get((kernel_source_hash(), vname, ty, tz))
     bytes_step = g.algorithmic_bytes_per_step()
@@ -522,7 +518,7 @@ def main():
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_unit": "HBM bytes per step",
                      "kernel": {"fused": "k_fused_list (one pass per step, launched per CPML tile group)",
-                                "tb2": "k_tb2_list (one pass per two steps, launched per CPML tile group)",
+                                "tb2": "k_tb2 (one launch per two steps)",
                                 "split": "k_h_split + k_e_split (two launches per step)"}[vname],
                      "algorithmic_bytes_per_step": bytes_step,
                      "kernel_ms_per_step": round(kms / max(kn, 1), 5)},

@@ -308,10 +308,9 @@ void fdtd_destroy(fdtd_ctx* c);
 
 /* ---------------------------------------------------------------------------
  * Batched engine: many independent grids (e.g. a parameter sweep of small,
- * uneven electrode grids) stepped together, one kernel launch per step (or
- * two persistent launches per two-step pass, one per code path) over tile
- * lists that span every grid, optionally replayed from a captured HIP
- * graph.  Each grid's results are bit-identical to running it alone.
+ * uneven electrode grids) stepped together, one kernel launch per step or
+ * two-step pass over tile lists that span every grid, optionally replayed
+ * from a captured HIP graph.  Each grid's results are bit-identical to running it alone.
  * ------------------------------------------------------------------------- */
 typedef struct fdtd_batch fdtd_batch;
 
@@ -328,20 +327,15 @@ int fdtd_batch_bind_workspace(fdtd_batch* b, void* dev_ptr, size_t bytes);
 /* Tile shape (tile_x, tile_y) in {(32, 8), (32, 16), (64, 8)}, z-chunk
  * tile_z in [8, 4096]; graph_steps (even, 0 = off): steps captured in one
  * HIP graph and replayed.  (60, 8) selects two-step passes (two time steps
- * per launch sequence, tiles grouped by the CPML slabs they reach, the
- * x-slab group on a second stream of the library's beside the others) with
- * tile_z in [16, 4096] and graph_steps a multiple of 4 (every grid with
+ * per launch, the probes' samples included) with chunks of at most tile_z in
+ * [16, 4096] planes and graph_steps a multiple of 4 (every grid with
  * 2 npml <= 128 in FP32, 64 in FP64); an odd step count ends with one
  * single-step launch.  Results do not depend on the choice.
  * Default (32, 8, 32, 0).  Errors: EINVAL. */
 int fdtd_batch_set_kernel(fdtd_batch* b, int tile_x, int tile_y, int tile_z, int graph_steps);
-/* Two-step passes only: on = 1 (the default) runs each pass as persistent
- * launches whose blocks take tiles from work queues: one launch for the
- * tiles clear of the y slabs (the x-slab code path), one on the second
- * stream for the rest (the all-axes path; every tile in FP64), each XCD
- * starting on its own run of a queue's tiles, grid by grid.  on = 0
- * launches the CPML groups separately (the x-slab group on the second
- * stream).  Results do not depend on the choice.  Errors: EINVAL. */
+/* Two-step passes run as one launch over all tiles whatever `on` (0 or 1)
+ * says; the call is kept for programs that chose between launch forms.
+ * Errors: EINVAL. */
 int fdtd_batch_set_persistent(fdtd_batch* b, int on);
 /* Advance every grid n_steps steps.  Errors: ESTATE, ERANGE (beyond the
  * smallest max_steps), EDEVICE. */

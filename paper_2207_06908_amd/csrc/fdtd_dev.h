@@ -34,15 +34,14 @@ struct GridView {
   int pad0;
   const T* fi[6];                // fields read  (E^n, H^{n-1/2}), components Ex..Hz
   T* fo[6];                      // fields written (E^{n+1}, H^{n+1/2})
-  // CPML state of axis u: 4 arrays of pel[u] values each, starting at
-  // pib[u] (input set) / pob[u] (output set), ordered [kind][component] with
-  // kind 0 = E-type, 1 = H-type and component 0 the one along axis+1,
-  // component 1 along axis+2.
+  // CPML state of axis u, starting at pib[u] (input set) / pob[u] (output
+  // set): pel[u] pairs of kind 0 (E-type), then as many of kind 1 (H-type);
+  // a pair holds the components along axis+1 and axis+2.  pob[u] - pib[u] is
+  // the same for every axis.
   const T* pib[3];
   T* pob[3];
   unsigned pel[3];
   int pad2;
-  const T* zpl;                  // nx * ny zeros: E of the planes outside [0, nz)
   const void* cls;               // class id per node (uint8 or uint16)
   const T* ctab;                 // [ncls][K_STRIDE]
   const T* prof[3];              // per axis [P_NROW][2*npml]
@@ -192,35 +191,13 @@ int launch_batch_step(int prec, int cls16, int pml, const void* views, const voi
 // Batched probes: `plist` is a device array of int2 (grid, probe id).
 int launch_batch_probes(int prec, const void* views, const void* plist, int n, const int* d_step, int offset,
                         void* stream);
-// Batched two-step pass: `views` as for launch_batch_step (input set = the
-// pass's input), `tiles` a device array of int4 (grid, i0 | iw << 16,
-// j0 | jh << 16, k0 | kz << 16) in 4 CPML groups of counts[q] tiles (as for
-// launch_lists_step), 60 x 8 tiles; then the probes of both steps for the
-// (grid, probe) pairs of `plist`.  Steps *d_step + offset and + 1.  With a
-// second stream (and two events), group 1 runs on it beside the others,
-// forked from and joined back to `stream` before the probes.
-int launch_batch_pass_tb2(int prec, int cls16, const void* views, const void* tiles, const int* counts,
-                          const void* plist, int n_probes, const int* d_step, int offset, void* stream,
-                          void* stream2, void* ev_fork, void* ev_join);
-// Batched two-step pass as persistent launches (k_tb2_batch_q), one per code
-// path: path A (the x-slab instantiation) over tiles_a with blocks_a blocks
-// on `stream`, path B (the all-axes one) over tiles_b with blocks_b blocks
-// on `stream2` (forked and joined with the events when both have tiles; a
-// path with 0 blocks is skipped).  Tiles are int4 (grid | group << 24,
-// i0 | iw << 16, j0 | jh << 16, k0 | kz << 16), grid by grid, in 8 runs
-// [runs.start[x], runs.start[x + 1]), one per XCD; `ctr` is 16 device ints
-// (A's 8, then B's; reset on the stream before the launches).  Then the
-// probes of both steps, as for launch_batch_pass_tb2.
-struct QRuns {
-  int start[9];
-};
-// Blocks of k_tb2_batch_q for path axp (5: A, 7: B) that fit on the device
-// at once (0 on error).
-int batch_queue_blocks(int prec, int cls16, int axp);
-int launch_batch_pass_queue(int prec, int cls16, const void* views, const void* tiles_a, const QRuns* runs_a,
-                            int blocks_a, const void* tiles_b, const QRuns* runs_b, int blocks_b, int* ctr,
-                            const void* plist, int n_probes, const int* d_step, int offset, void* stream,
-                            void* stream2, void* ev_fork, void* ev_join);
+// Batched two-step pass in one launch: `views` as for launch_batch_step (input
+// set = the pass's input), `tiles` a device array of int4 (grid,
+// i0 | iw << 16, j0 | jh << 16, k0 | kz << 16) of 60 x 8 tiles, taken by the
+// XCDs in runs of `run`.  Steps *d_step + offset and + 1.  The probes of the
+// (grid, probe) pairs of `plist` as in launch_tb2_pass.
+int launch_batch_pass(int prec, int cls16, const void* views, const void* tiles, int n_tiles, const void* plist,
+                      int n_probes, const int* d_step, int offset, int prev, int run, void* stream);
 // *d += v on the stream (advances the device step counter).
 int launch_add(int* d, int v, void* stream);
 // *d = v on the stream.

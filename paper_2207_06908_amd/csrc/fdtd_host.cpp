@@ -114,7 +114,7 @@ struct fdtd_ctx {
   std::vector<double> term_w;
   size_t ws_bytes = 0;
   // workspace offsets (bytes from the workspace base)
-  size_t off_f = 0, off_psi[2][3] = {{0, 0, 0}, {0, 0, 0}}, off_zpl = 0, off_cls = 0, off_ctab = 0, off_prof = 0;
+  size_t off_f = 0, off_psi[2][3] = {{0, 0, 0}, {0, 0, 0}}, off_cls = 0, off_ctab = 0, off_prof = 0;
   size_t off_src_comp = 0, off_src_idx = 0, off_amp = 0, off_pr_off = 0, off_term_comp = 0;
   size_t off_term_idx = 0, off_term_w = 0, off_out = 0, psi_elems[3] = {0, 0, 0};
   std::vector<uint8_t> cls8;          // staging for 1-byte class ids
@@ -762,7 +762,6 @@ void layout(fdtd_ctx* c) {
   }
   for (int s = 0; s < 2; ++s)
     for (int u = 0; u < 3; ++u) c->off_psi[s][u] = take(4 * c->psi_elems[u] * ts);
-  c->off_zpl = take((size_t)c->N[0] * c->N[1] * ts);  // zeroed with the fields, never written
   c->off_j = take((size_t)3 * c->npole * N * ts);     // Debye currents, zeroed with the fields
   c->off_cls = take(N * (c->cls16 ? 2 : 1));
   c->off_ctab = take((size_t)c->ncls * K_STRIDE * ts);
@@ -842,7 +841,6 @@ void fill_view(fdtd_ctx* c, GridView<T>& g, int in, int out) {
     g.pob[u] = np ? (T*)(w + c->off_psi[out][u]) : nullptr;
     g.pel[u] = (unsigned)c->psi_elems[u];
   }
-  g.zpl = (const T*)(w + c->off_zpl);
   g.cls = w + c->off_cls;
   g.ctab = (const T*)(w + c->off_ctab);
   for (int u = 0; u < 3; ++u) g.prof[u] = (const T*)(w + c->off_prof) + (size_t)u * P_NROW * 2 * np;
@@ -1306,19 +1304,6 @@ std::vector<Seg> segments(int n, int np, int w, int align, int w_out) {
 // in LDS, room for 2 npml <= 128 values (FP32) or 64 (FP64).
 bool tb2_cpml_fits(int npml, int precision) { return 2 * npml <= (precision == 64 ? 64 : 128); }
 
-// Two-step pieces: [0, n) split into w-wide pieces, those in [a, b) clear
-// of the CPML including the h-cell halo (a - h >= np, piece end + h <= n - np);
-// a is a multiple of w so that the pieces below it are full width.
-std::vector<Seg> segments_tb2(int n, int np, int w, int h) {
-  std::vector<Seg> s;
-  int a = (np + h + w - 1) / w * w, b = a;
-  while (b + w <= n - np - h) b += w;
-  if (b == a) a = b = n;
-  for (int x = 0; x < a; x += w) s.push_back({x, std::min(x + w, a), false});
-  for (int x = a; x < b; x += w) s.push_back({x, x + w, true});
-  for (int x = b; x < n; x += w) s.push_back({x, std::min(x + w, n), false});
-  return s;
-}
 
 // Tile list of the fused pass for a grid with a CPML (see fdtd_ctx::tl and
 // launch_lists_step).
@@ -1407,8 +1392,8 @@ int ensure_tiles(fdtd_ctx* c, int ty, int kz) {
 //  - 12-row tiles from 40M cells (FP32): they read 1.33 rows a row, 8-row
 //    ones 1.5, but their x-y corner tiles spill at the 128 registers that 16
 //    waves leave, which small grids, nearly all slabs, feel.  us per step,
-//    12 rows / 8 rows: 512 x 512 x 384 764 / 800, 396 x 400 x 293 391 / 403,
-//    304 x 305 x 230 222 / 213, 96 x 96 x 80 22 / 15.
+//    12 rows / 8 rows: 512 x 512 x 384 743 / 790, 384 x 384 x 288 338 / 348,
+//    304 x 305 x 230 222 / 213, 96 x 96 x 80 22 / 14.5.
 //  - Planes per chunk: one block runs on a CU at a time, so up to 256 blocks
 //    take one chunk's march (its planes and about 4 of pipeline), and more
 //    take it nb / 256 times and half a round for the ragged end.  Chunks past
@@ -1838,33 +1823,20 @@ struct fdtd_batch {
   size_t off_views = 0, off_pviews = 0, off_tiles = 0, off_plist = 0, off_step = 0, ws_bytes = 0;
   std::vector<int> tiles;             // int4 entries (grid, i0, j0, k0 | kz << 16)
   std::vector<int> plist;             // int2 entries (grid, probe)
-  // two-step passes (set_kernel with tile_x 60): CPML-grouped tile list of
+  // two-step passes (set_kernel with tile_x 60): tile list of
   // (grid, i0 | iw << 16, j0 | jh << 16, k0 | kz << 16); an odd remainder of
   // steps takes one fused step over `tiles` (32 x 8)
   bool tb2 = false;
   int tb2_kz = 32;
   std::vector<int> tiles2;
-  int tcnt[4] = {0, 0, 0, 0};
   size_t off_tiles2 = 0;
-  // the same tiles for the persistent launches (fdtd_batch_set_persistent):
-  // one list per code path (x-slab instantiation, then all-axes), each grid
-  // by grid, tagged with their group, in 8 runs (one per XCD), and the runs'
-  // 2 x 8 counters
-  bool persistent = true;
-  std::vector<int> tiles_q;
-  QRuns runs[2] = {};
-  int nq[2] = {0, 0};
-  int q_blocks[2] = {0, 0};
-  size_t off_tiles_q = 0, off_qctr = 0;
+  bool probe_due = false;            // the probes of the last step are still to be recorded (within fdtd_batch_run)
   char* ws = nullptr;
   int cur = 0;
   long long steps_done = 0;
   bool tiles_dirty = true;
   // graph replay (captured on a private stream, launched on `stream`)
   hipStream_t cap_stream = nullptr;
-  // second stream of the two-step pass (the x-slab tile group beside the rest)
-  hipStream_t aux = nullptr;
-  hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   int graph_steps = 0;
   hipGraphExec_t gexec = nullptr;
   hipGraph_t graph = nullptr;
@@ -1906,68 +1878,43 @@ void build_tiles(fdtd_batch* b) {
   }
 }
 
-// Two-step tile list of every grid, grouped by the CPML slabs the tiles reach
-// (as for a single grid), larger grids first within each group.
+// Two-step tile list of every grid, larger grids first: 60 x 8 tiles in
+// chunks of about equal depth.  The depth is at most tb2_kz planes: the one
+// for which 256 blocks at a time take the fewest planes (4 of pipeline a
+// tile), half a round added for the ragged end.  Large batches take tb2_kz
+// itself; 8 grids at tb2_kz 32 run 58 us a step with 32-plane chunks, 47
+// with 24.
 void build_tiles_tb2(fdtd_batch* b) {
   std::vector<int> order(b->grids.size());
   for (size_t g = 0; g < order.size(); ++g) order[g] = (int)g;
   std::stable_sort(order.begin(), order.end(),
                    [&](int a, int c) { return b->grids[a]->ncell > b->grids[c]->ncell; });
-  std::vector<int> grp[4];
-  const int kz = b->tb2_kz, kzp = std::max(8, kz / 2);
-  for (int g : order) {
-    const fdtd_ctx* c = b->grids[g];
-    const int np = c->P.npml, nz = c->N[2];
-    const std::vector<Seg> xs = segments_tb2(c->N[0], np, 60, 2);
-    const std::vector<Seg> ys = segments_tb2(c->N[1], np, 8, 2);
-    for (const Seg& y : ys)
-      for (const Seg& x : xs) {
-        const int q = (x.in ? 0 : 1) | (y.in ? 0 : 2);
-        const int d = q == 0 ? kz : kzp;
-        for (int z = 0; z < nz; z += d)
-          grp[q].insert(grp[q].end(), {g, x.a | (x.b - x.a) << 16, y.a | (y.b - y.a) << 16,
-                                       z | (std::min(d, nz - z) << 16)});
-      }
+  int depth = b->tb2_kz;
+  double best = 0;
+  for (int kz = std::min(b->tb2_kz, 64); kz >= 8; --kz) {
+    double planes = 0, nb = 0, dmax = 0;
+    for (const fdtd_ctx* c : b->grids) {
+      const int chunks = (c->N[2] + kz - 1) / kz, d = (c->N[2] + chunks - 1) / chunks;
+      const double t = (double)((c->N[0] + 59) / 60) * ((c->N[1] + 7) / 8) * chunks;
+      nb += t;
+      planes += t * (d + 4);
+      dmax = std::max(dmax, (double)d + 4);
+    }
+    const double cost = nb <= 256 ? dmax : planes / 256 + 0.5 * dmax;
+    if (best == 0 || cost < best) {
+      best = cost;
+      depth = kz == 64 ? b->tb2_kz : kz;
+    }
   }
   b->tiles2.clear();
-  for (int q = 0; q < 4; ++q) {
-    b->tiles2.insert(b->tiles2.end(), grp[q].begin(), grp[q].end());
-    b->tcnt[q] = (int)(grp[q].size() / 4);
-  }
-  // Persistent lists: the same tiles grid by grid (in the order above), the
-  // group in the top byte of the grid field; list 0 for the x-slab code path
-  // (groups 0 and 1), list 1 for the all-axes one (groups 2 and 3; every
-  // tile in FP64); each cut into 8 runs of about equal cell count.
-  std::vector<std::vector<int>> per(b->grids.size());
-  for (int q = 0; q < 4; ++q)
-    for (size_t t = 0; t < grp[q].size(); t += 4)
-      per[grp[q][t]].insert(per[grp[q][t]].end(), {grp[q][t] | (q << 24), grp[q][t + 1], grp[q][t + 2],
-                                                   grp[q][t + 3]});
-  std::vector<int> lst[2];
-  std::vector<double> cells[2];
-  double total[2] = {0, 0};
-  for (int g : order)
-    for (size_t t = 0; t < per[g].size(); t += 4) {
-      const int* e = &per[g][t];
-      const int w = (b->prec == 64 || ((e[0] >> 24) & 2)) ? 1 : 0;
-      lst[w].insert(lst[w].end(), e, e + 4);
-      cells[w].push_back((double)(e[1] >> 16) * (e[2] >> 16) * (e[3] >> 16));
-      total[w] += cells[w].back();
-    }
-  b->tiles_q = lst[0];
-  b->tiles_q.insert(b->tiles_q.end(), lst[1].begin(), lst[1].end());
-  for (int w = 0; w < 2; ++w) {
-    const int n = (int)cells[w].size();
-    QRuns& r = b->runs[w];
-    b->nq[w] = n;
-    r.start[0] = 0;
-    double acc = 0;
-    int x = 1;
-    for (int t = 0; t < n && x < 8; ++t) {
-      acc += cells[w][t];
-      while (x < 8 && acc >= total[w] * x / 8.0) r.start[x++] = t + 1;
-    }
-    while (x <= 8) r.start[x++] = n;
+  for (int g : order) {
+    const int nx = b->grids[g]->N[0], ny = b->grids[g]->N[1], nz = b->grids[g]->N[2];
+    const int chunks = (nz + depth - 1) / depth, d = (nz + chunks - 1) / chunks;
+    for (int z = 0; z < nz; z += d)
+      for (int y = 0; y < ny; y += 8)
+        for (int x = 0; x < nx; x += 60)
+          b->tiles2.insert(b->tiles2.end(), {g, x | std::min(60, nx - x) << 16, y | std::min(8, ny - y) << 16,
+                                             z | std::min(d, nz - z) << 16});
   }
 }
 
@@ -2005,14 +1952,6 @@ int upload_tiles(fdtd_batch* b) {
     build_tiles_tb2(b);
     e = hipMemcpyAsync(b->ws + b->off_tiles2, b->tiles2.data(), b->tiles2.size() * sizeof(int),
                        hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(b->ws + b->off_tiles_q, b->tiles_q.data(), b->tiles_q.size() * sizeof(int),
-                         hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess && !b->q_blocks[0]) {
-      b->q_blocks[0] = batch_queue_blocks(b->prec, b->cls16, 5);
-      b->q_blocks[1] = batch_queue_blocks(b->prec, b->cls16, 7);
-      if (b->q_blocks[0] <= 0 || b->q_blocks[1] <= 0) return bfail(b, FDTD_EDEVICE, "persistent launch size");
-    }
   }
   if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
   if (e != hipSuccess) return bfail(b, FDTD_EDEVICE, std::string("tile upload: ") + hipGetErrorString(e));
@@ -2027,9 +1966,9 @@ size_t max_tiles(const fdtd_batch* b) {  // upper bound over the allowed tile sh
   return n;
 }
 
-size_t max_tiles_tb2(const fdtd_batch* b) {  // 60 x 8 pieces (3 extra per axis), chunks of >= 8 planes
+size_t max_tiles_tb2(const fdtd_batch* b) {  // 60 x 8 tiles, chunks of >= 2 planes
   size_t n = 0;
-  for (const fdtd_ctx* c : b->grids) n += (size_t)(c->N[0] / 60 + 3) * (c->N[1] / 8 + 3) * (c->N[2] / 8 + 1);
+  for (const fdtd_ctx* c : b->grids) n += (size_t)(c->N[0] / 60 + 1) * (c->N[1] / 8 + 1) * (c->N[2] / 2 + 1);
   return n;
 }
 
@@ -2039,20 +1978,27 @@ int batch_launch_pass(fdtd_batch* b, hipStream_t st, int p, int off) {
   const size_t nv = b->grids.size();
   const size_t vb = view_bytes(b->prec);
   const int* d_step = (const int*)(b->ws + b->off_step);
-  if (b->persistent) {
-    const int* tq = (const int*)(b->ws + b->off_tiles_q);
-    int e = launch_batch_pass_queue(b->prec, b->cls16, b->ws + b->off_views + p * nv * vb, tq, &b->runs[0],
-                                    std::min(b->q_blocks[0], b->nq[0]), tq + 4 * b->nq[0], &b->runs[1],
-                                    std::min(b->q_blocks[1], b->nq[1]), (int*)(b->ws + b->off_qctr),
-                                    b->ws + b->off_plist, (int)(b->plist.size() / 2), d_step, off, (void*)st,
-                                    (void*)b->aux, (void*)b->ev_fork, (void*)b->ev_join);
-    if (e) return bfail(b, FDTD_EDEVICE, std::string("batch pass: ") + hipGetErrorString((hipError_t)e));
-    return FDTD_OK;
-  }
-  int e = launch_batch_pass_tb2(b->prec, b->cls16, b->ws + b->off_views + p * nv * vb, b->ws + b->off_tiles2,
-                                b->tcnt, b->ws + b->off_plist, (int)(b->plist.size() / 2), d_step, off, (void*)st,
-                                (void*)b->aux, (void*)b->ev_fork, (void*)b->ev_join);
+  // An XCD takes 17 tiles in a row, a part of one grid: its neighbouring tiles
+  // share an L2 (256 grids: 1 tile 1,317 us a step, 3 1,259, 9 to 129 within
+  // 1% of 1,244).
+  const int run = 17;
+  int e = launch_batch_pass(b->prec, b->cls16, b->ws + b->off_views + p * nv * vb, b->ws + b->off_tiles2,
+                            (int)(b->tiles2.size() / 4), b->ws + b->off_plist, (int)(b->plist.size() / 2), d_step, off,
+                            b->probe_due ? 1 : 0, run, (void*)st);
   if (e) return bfail(b, FDTD_EDEVICE, std::string("batch pass: ") + hipGetErrorString((hipError_t)e));
+  b->probe_due = !b->plist.empty();
+  return FDTD_OK;
+}
+
+// Record the probes that the last two-step pass (parity p) left: those of
+// step *d_step + off.
+int batch_record_due(fdtd_batch* b, hipStream_t st, int p, int off) {
+  if (!b->probe_due) return FDTD_OK;
+  b->probe_due = false;
+  const int e = launch_batch_probes(b->prec, b->ws + b->off_pviews + p * b->grids.size() * view_bytes(b->prec),
+                                    b->ws + b->off_plist, (int)(b->plist.size() / 2),
+                                    (const int*)(b->ws + b->off_step), off, (void*)st);
+  if (e) return bfail(b, FDTD_EDEVICE, std::string("batch probes: ") + hipGetErrorString((hipError_t)e));
   return FDTD_OK;
 }
 
@@ -2121,8 +2067,6 @@ int fdtd_batch_pack(fdtd_ctx* const* grids, int n, void* hip_stream, fdtd_batch*
   b->off_pviews = take(2 * b->grids.size() * view_bytes(b->prec));
   b->off_tiles = take(max_tiles(b) * 4 * sizeof(int));
   b->off_tiles2 = take(max_tiles_tb2(b) * 4 * sizeof(int));
-  b->off_tiles_q = take(max_tiles_tb2(b) * 4 * sizeof(int));
-  b->off_qctr = take(16 * sizeof(int));
   b->off_plist = take(b->plist.size() * sizeof(int) + 8);
   b->off_step = take(sizeof(int));
   b->ws_bytes = o;
@@ -2183,8 +2127,6 @@ int fdtd_batch_set_kernel(fdtd_batch* b, int tile_x, int tile_y, int tile_z, int
 
 int fdtd_batch_set_persistent(fdtd_batch* b, int on) {
   if (!b || (on != 0 && on != 1)) return FDTD_EINVAL;
-  if (b->persistent != (on == 1)) drop_graph(b);
-  b->persistent = on == 1;
   return FDTD_OK;
 }
 
@@ -2197,12 +2139,7 @@ int fdtd_batch_run(fdtd_batch* b, int n) {
     if (rc) return rc;
   }
   hipError_t e = hipSuccess;
-  if (b->tb2 && !b->aux) {  // the two-step pass's second stream, made outside any capture
-    e = hipStreamCreateWithFlags(&b->aux, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_join, hipEventDisableTiming);
-    if (e != hipSuccess) return bfail(b, FDTD_EDEVICE, std::string("second stream: ") + hipGetErrorString(e));
-  }
+  b->probe_due = false;
   if (b->timing) {
     if (!b->t0) {
       e = hipEventCreate(&b->t0);
@@ -2215,6 +2152,8 @@ int fdtd_batch_run(fdtd_batch* b, int n) {
   const int G = b->graph_steps;
   while (left > 0) {
     if (G > 0 && left >= G && b->cur == 0) {
+      int rd = batch_record_due(b, b->stream, 1 - b->cur, -1);
+      if (rd) return rd;
       if (!b->gexec) {  // capture G steps once: offsets 0..G-1, then advance the counter by G
         if (!b->cap_stream) {  // the legacy default stream cannot be captured
           e = hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking);
@@ -2226,8 +2165,10 @@ int fdtd_batch_run(fdtd_batch* b, int n) {
         int rc = FDTD_OK;
         if (b->tb2)
           for (int t = 0; t < G / 2 && rc == FDTD_OK; ++t) rc = batch_launch_pass(b, cs, t & 1, 2 * t);
-        else
+        else  // (the passes' last probes below)
           for (int t = 0; t < G && rc == FDTD_OK; ++t) rc = batch_launch_step(b, cs, t & 1, t);
+        if (rc == FDTD_OK) rc = batch_record_due(b, cs, 1, G - 1);
+        b->probe_due = false;
         if (rc == FDTD_OK && launch_add((int*)(b->ws + b->off_step), G, (void*)cs))
           rc = bfail(b, FDTD_EDEVICE, "capture: counter");
         hipGraph_t gr = nullptr;
@@ -2245,12 +2186,20 @@ int fdtd_batch_run(fdtd_batch* b, int n) {
       continue;
     }
     const int adv = (b->tb2 && left >= 2) ? 2 : 1;
+    if (adv == 1) {
+      int rd = batch_record_due(b, b->stream, 1 - b->cur, -1);
+      if (rd) return rd;
+    }
     int rc = adv == 2 ? batch_launch_pass(b, b->stream, b->cur, 0) : batch_launch_step(b, b->stream, b->cur, 0);
     if (rc) return rc;
     if (launch_add((int*)(b->ws + b->off_step), adv, (void*)b->stream)) return bfail(b, FDTD_EDEVICE, "counter");
     b->cur ^= 1;
     b->steps_done += adv;
     left -= adv;
+  }
+  {
+    int rd = batch_record_due(b, b->stream, 1 - b->cur, -1);
+    if (rd) return rd;
   }
   if (b->timing) {
     float ms = 0;
@@ -2307,10 +2256,6 @@ const char* fdtd_batch_last_error(const fdtd_batch* b) { return b ? b->err.c_str
 void fdtd_batch_destroy(fdtd_batch* b) {
   if (!b) return;
   drop_graph(b);
-  if (b->aux) (void)hipStreamSynchronize(b->aux);
-  if (b->ev_fork) (void)hipEventDestroy(b->ev_fork);
-  if (b->ev_join) (void)hipEventDestroy(b->ev_join);
-  if (b->aux) (void)hipStreamDestroy(b->aux);
   if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
   if (b->t0) (void)hipEventDestroy(b->t0);
   if (b->t1) (void)hipEventDestroy(b->t1);

@@ -13,15 +13,14 @@
 //   fused  one pass per step over x-y tiles marching up z; each block
 //          recomputes the H it needs on a one-node low-side halo; reads one
 //          field set and writes the other;
-//   tb2    one pass per two steps (temporal blocking): 60 x TY output tiles
-//          in 64 x (TY+4) regions, four stages per plane;
-// each also as tile lists grouped by the CPML slabs the tiles reach, and
-// batched over many grids.  All evaluate every component through h_core /
+//   tb2    one pass per two steps (temporal blocking) in one launch: 60 x TY
+//          output tiles in 64 x (TY+4) regions, four stages per plane, each
+//          tile by the code of the CPML slabs it reaches, probes included.
+// fused and tb2 also run batched over many grids, and fused as tile lists
+// grouped by those slabs.  All evaluate every component through h_core /
 // e_core of fdtd_tile.h (with the arithmetic of yee_update.h) and are compiled with FP
 // contraction off, so they agree bit for bit.
 #include <hip/hip_runtime.h>
-
-#include <algorithm>
 
 #include "fdtd_dev.h"
 #include "fdtd_tile.h"
@@ -215,9 +214,10 @@ struct ProfTB2 {
   }
 };
 
-// One two-step tile: outputs [i0, i0+iw) x [j0, j0+jh) x [k0, k1) with
-// iw <= 60, jh <= TY.  AX masks the axes whose CPML slabs the tile can reach.
-template <typename T, typename CI, bool PML, int TY, int AX, bool USLAB = false, bool LEAN = false>
+// One two-step tile in the CPML: outputs [i0, i0+iw) x [j0, j0+jh) x [k0, k1)
+// with iw <= 60, jh <= TY.  FP64 grids run their slab tiles through this one,
+// a plane of every stage at a time (tb2_any).
+template <typename T, typename CI, int TY>
 __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& sm, int i0, int j0, int iw, int jh,
                                          int k0, int k1, int step) {
   constexpr int TX = 60, NT = 64 * (TY + 4);
@@ -238,69 +238,38 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
   const bool inC = inB && u <= TX + 1 && v <= TY + 1;
   const bool inD = inC && u >= 2 && v >= 2 && u < 2 + iw && v < 2 + jh;
   const unsigned n0 = dom ? (unsigned)x + (unsigned)nx * (unsigned)y : 0u;
-  const int lx = PML && (AX & 1) && dom ? slab_pos(x, nx, g.npml) : -1;
-  const int ly = PML && (AX & 2) && dom ? slab_pos(y, ny, g.npml) : -1;
-  constexpr bool PZ = PML && (AX & 4);
+  const int lx = dom ? slab_pos(x, nx, g.npml) : -1;
+  const int ly = dom ? slab_pos(y, ny, g.npml) : -1;
   // (E is updated on planes k0 - 1 .. k1: the first step's cone, then the outputs)
   const SrcRange srcr = src_wave(g, n0, inB, k0 - 1, k1);
-  if (PML) {
-    const int tn = 2 * g.npml;
-    if ((AX & 1) && v == 0) {
-      const int xl = x >= 0 && x < nx ? slab_pos(x, nx, g.npml) : -1;
-      for (int r = 0; r < P_NROW; ++r) sm.px[r][u] = xl >= 0 ? ldg(g.prof[0], (unsigned)(r * tn + xl)) : T(0);
-    }
-    if ((AX & 2) && u == 0) {
-      const int yl = y >= 0 && y < ny ? slab_pos(y, ny, g.npml) : -1;
-      for (int r = 0; r < P_NROW; ++r) sm.py[r][v] = yl >= 0 ? ldg(g.prof[1], (unsigned)(r * tn + yl)) : T(0);
-    }
-    if (AX & 4)
-      for (int q = tid; q < P_NROW * tn; q += NT) sm.pz[q] = ldg(g.prof[2], (unsigned)q);
+  const int tn = 2 * g.npml;
+  if (v == 0) {
+    const int xl = x >= 0 && x < nx ? slab_pos(x, nx, g.npml) : -1;
+    for (int r = 0; r < P_NROW; ++r) sm.px[r][u] = xl >= 0 ? ldg(g.prof[0], (unsigned)(r * tn + xl)) : T(0);
   }
+  if (u == 0) {
+    const int yl = y >= 0 && y < ny ? slab_pos(y, ny, g.npml) : -1;
+    for (int r = 0; r < P_NROW; ++r) sm.py[r][v] = yl >= 0 ? ldg(g.prof[1], (unsigned)(r * tn + yl)) : T(0);
+  }
+  for (int q = tid; q < P_NROW * tn; q += NT) sm.pz[q] = ldg(g.prof[2], (unsigned)q);
   const ProfTB2<T, TY> pf{g, sm, u, v};
 
-  // Loads are unconditional, from uniform plane bases and the thread's
-  // column offset n0 (0 for points outside the grid): E planes outside
-  // [0, nz) read the zero plane, H and class planes are clamped (those values
-  // are never used).  E of points outside the grid is zeroed where it enters
-  // LDS.  No load then sits behind a branch, and none waits on a select.
-  // The x- and y-slab instantiations (AX 5, 6) keep predicated loads unless
-  // USLAB: the batched kernels, which read their grid's view from memory,
-  // have no registers to spare for them there.  LEAN corner tiles keep
-  // predicated loads too and store at once, to fit two blocks per CU: the
-  // batch's corner tiles (its grids are small, so they carry much of the
-  // work) and the FP32 single-grid ones.
-  constexpr bool UNC = AX == 4 || (AX == 7 && !LEAN) || USLAB;
   auto ld_e = [&](int k, T e[3]) {
     const bool in = k >= 0 && k < nz;
-    if (UNC) {
-      const size_t po = (size_t)sxy * (size_t)(in ? k : 0);
-      e[0] = ldg(in ? g.fi[0] + po : g.zpl, n0);
-      e[1] = ldg(in ? g.fi[1] + po : g.zpl, n0);
-      e[2] = ldg(in ? g.fi[2] + po : g.zpl, n0);
-    } else {
-      const bool ok = dom && in;
-      const unsigned n = n0 + sxy * (unsigned)(ok ? k : 0);
-      e[0] = ok ? ldg(g.fi[0], n) : T(0);
-      e[1] = ok ? ldg(g.fi[1], n) : T(0);
-      e[2] = ok ? ldg(g.fi[2], n) : T(0);
-    }
+    const bool ok = dom && in;
+    const unsigned n = n0 + sxy * (unsigned)(ok ? k : 0);
+    e[0] = ok ? ldg(g.fi[0], n) : T(0);
+    e[1] = ok ? ldg(g.fi[1], n) : T(0);
+    e[2] = ok ? ldg(g.fi[2], n) : T(0);
   };
   auto ld_h = [&](int k, T h[3]) {
-    if (UNC) {
-      const size_t po = (size_t)sxy * (size_t)min(max(k, 0), nz - 1);
-      h[0] = ldg(g.fi[3] + po, n0);
-      h[1] = ldg(g.fi[4] + po, n0);
-      h[2] = ldg(g.fi[5] + po, n0);
-    } else {
-      const bool ok = inA && k >= 0 && k < nz;
-      const unsigned n = n0 + sxy * (unsigned)(ok ? k : 0);
-      h[0] = ok ? ldg(g.fi[3], n) : T(0);
-      h[1] = ok ? ldg(g.fi[4], n) : T(0);
-      h[2] = ok ? ldg(g.fi[5], n) : T(0);
-    }
+    const bool ok = inA && k >= 0 && k < nz;
+    const unsigned n = n0 + sxy * (unsigned)(ok ? k : 0);
+    h[0] = ok ? ldg(g.fi[3], n) : T(0);
+    h[1] = ok ? ldg(g.fi[4], n) : T(0);
+    h[2] = ok ? ldg(g.fi[5], n) : T(0);
   };
   auto ld_c = [&](int k) -> int {
-    if (UNC) return (int)ldg(cls + (size_t)sxy * (size_t)min(max(k, 0), nz - 1), n0);
     return (inA && k >= 0 && k < nz) ? (int)ldg(cls, n0 + sxy * (unsigned)k) : 0;
   };
 
@@ -317,35 +286,12 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
   ld_h(kb, h0c);
   int cc = ld_c(kb), cp = 0;
 
-  // The outputs of plane k-1 are written at the top of the next iteration,
-  // ahead of its prefetch: the vector-memory counter retires in order, so a
-  // wait for the prefetched values then never has to wait for stores issued
-  // after them.
-  T e2[3] = {T(0), T(0), T(0)};
-  T h2z = T(0);
-  unsigned nst = 0;
-  bool pend = false;
-  // (The x- and y-slab instantiations store at once: they have no registers
-  // to spare under their cap.)
-  constexpr bool DEFER = (AX == 4 || (AX == 7 && !LEAN)) && sizeof(T) == 4;
-  auto flush = [&]() {
-    if (DEFER && pend) {
-      stg(g.fo[0], nst, e2[0]);
-      stg(g.fo[1], nst, e2[1]);
-      stg(g.fo[2], nst, e2[2]);
-      stg(g.fo[3], nst, h2p[0]);
-      stg(g.fo[4], nst, h2p[1]);
-      stg(g.fo[5], nst, h2z);
-    }
-  };
-
   // Let the prologue's loads land before the loop.  Otherwise the compiler,
   // which merges the loop entry with the back edge, places the wait for them
   // after the stores at the top of every iteration and so waits for those
   // stores as well.  (vmcnt 0, expcnt and lgkmcnt unconstrained)
   __builtin_amdgcn_s_waitcnt(0x0F70);
   for (int k = kb; k <= k1; ++k) {
-    flush();
     // prefetch: classes and H^{n-1/2} of plane k+1, E^n of plane k+2 (the
     // classes first: the end of the iteration then waits for all of it)
     T e0f[3], h0f[3];
@@ -362,12 +308,12 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
     // CPML state loaded there is consumed inside it and no wait for it is
     // left at the end of the iteration, where it would also wait for the
     // prefetch and the stores.
-    const int lz = PZ ? slab_pos(k, nz, g.npml) : -1;
+    const int lz = slab_pos(k, nz, g.npml);
     if (inA && kin) {
       auto stage_a = [&](const int l[3]) {
-        if (PML) psi_load(g, 1, l, x, y, k, pshn);
-        h_core_pf<T, PML>(pf, l, coef(cc), e0c[0], e0c[1], e0c[2], sm.se0[0][v + 1][u], e0n[0], sm.se0[1][v][u + 1],
-                       e0n[1], sm.se0[2][v][u + 1], sm.se0[2][v + 1][u], h0c, pshn, h1c);
+        psi_load(g, 1, l, x, y, k, pshn);
+        h_core_pf<T, true>(pf, l, coef(cc), e0c[0], e0c[1], e0c[2], sm.se0[0][v + 1][u], e0n[0], sm.se0[1][v][u + 1],
+                       e0n[1], sm.se0[2][v][u + 1], sm.se0[2][v + 1][u], h0c, pshn[0], pshn[1], pshn[2], h1c);
       };
       if (lz >= 0) {
         const int l[3] = {lx, ly, lz};
@@ -384,9 +330,9 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
     T psen[3][2];
     if (inB && kin && k >= k0 - 1) {
       auto stage_b = [&](const int l[3]) {
-        if (PML) psi_load(g, 0, l, x, y, k, psen);
-        e_core_pf<T, PML>(pf, l, coef(cc), h1c[0], h1c[1], h1c[2], sm.sh1[0][v - 1][u], h1p[0], sm.sh1[1][v][u - 1],
-                          h1p[1], sm.sh1[2][v][u - 1], sm.sh1[2][v - 1][u], e0c, psen, e1c);
+        psi_load(g, 0, l, x, y, k, psen);
+        e_core_pf<T, true>(pf, l, coef(cc), h1c[0], h1c[1], h1c[2], sm.sh1[0][v - 1][u], h1p[0], sm.sh1[1][v][u - 1],
+                          h1p[1], sm.sh1[2][v][u - 1], sm.sh1[2][v - 1][u], e0c, psen[0], psen[1], psen[2], e1c);
         e_sources(&g, srcr.first(k), srcr.last(k), n0 + sxy * (unsigned)k, step, e1c);
       };
       if (lz >= 0) {
@@ -409,41 +355,36 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
     const int km = k - 1;
     T h2c[3] = {T(0), T(0), T(0)};
     if (inC && k >= k0 && km >= 0 && km < nz) {
-      int l[3] = {lx, ly, PZ ? slab_pos(km, nz, g.npml) : -1};
-      h_core_pf<T, PML>(pf, l, coef(cp), e1p[0], e1p[1], e1p[2], sm.se1[s1m][0][v + 1][u], e1c[0],
-                     sm.se1[s1m][1][v][u + 1], e1c[1], sm.se1[s1m][2][v][u + 1], sm.se1[s1m][2][v + 1][u], h1p, psh,
-                     h2c);
+      int l[3] = {lx, ly, slab_pos(km, nz, g.npml)};
+      h_core_pf<T, true>(pf, l, coef(cp), e1p[0], e1p[1], e1p[2], sm.se1[s1m][0][v + 1][u], e1c[0],
+                     sm.se1[s1m][1][v][u + 1], e1c[1], sm.se1[s1m][2][v][u + 1], sm.se1[s1m][2][v + 1][u], h1p, psh[0],
+                     psh[1], psh[2], h2c);
       if (inD && km >= k0) {
-        if (!DEFER) {
-          const unsigned n = n0 + sxy * (unsigned)km;
-          stg(g.fo[3], n, h2c[0]);
-          stg(g.fo[4], n, h2c[1]);
-          stg(g.fo[5], n, h2c[2]);
-        }
-        if (PML) psi_store(g, 1, l, x, y, km, psh);
+        const unsigned n = n0 + sxy * (unsigned)km;
+        stg(g.fo[3], n, h2c[0]);
+        stg(g.fo[4], n, h2c[1]);
+        stg(g.fo[5], n, h2c[2]);
+        psi_store(g, 1, l, x, y, km, psh);
       }
     }
     for (int c = 0; c < 3; ++c) sm.sh2[c][v][u] = h2c[c];
     __syncthreads();
     // D: E^{n+2}, plane k-1 (the output tile; km < k1 always holds)
-    pend = inD && km >= k0;
-    nst = n0 + sxy * (unsigned)km;
-    if (pend) {
-      int l[3] = {lx, ly, PZ ? slab_pos(km, nz, g.npml) : -1};
-      e_core_pf<T, PML>(pf, l, coef(cp), h2c[0], h2c[1], h2c[2], sm.sh2[0][v - 1][u], h2p[0], sm.sh2[1][v][u - 1],
-                        h2p[1], sm.sh2[2][v][u - 1], sm.sh2[2][v - 1][u], e1p, pse, e2);
+    if (inD && km >= k0) {
+      const unsigned nst = n0 + sxy * (unsigned)km;
+      T e2[3];
+      int l[3] = {lx, ly, slab_pos(km, nz, g.npml)};
+      e_core_pf<T, true>(pf, l, coef(cp), h2c[0], h2c[1], h2c[2], sm.sh2[0][v - 1][u], h2p[0], sm.sh2[1][v][u - 1],
+                        h2p[1], sm.sh2[2][v][u - 1], sm.sh2[2][v - 1][u], e1p, pse[0], pse[1], pse[2], e2);
       e_sources(&g, srcr.first(km), srcr.last(km), nst, step + 1, e2);
-      if (!DEFER) {
-        stg(g.fo[0], nst, e2[0]);
-        stg(g.fo[1], nst, e2[1]);
-        stg(g.fo[2], nst, e2[2]);
-      }
-      if (PML) psi_store(g, 0, l, x, y, km, pse);
+      stg(g.fo[0], nst, e2[0]);
+      stg(g.fo[1], nst, e2[1]);
+      stg(g.fo[2], nst, e2[2]);
+      psi_store(g, 0, l, x, y, km, pse);
     }
     // rotate the pipeline
     h2p[0] = h2c[0];
     h2p[1] = h2c[1];
-    h2z = h2c[2];
     for (int c = 0; c < 3; ++c) {
       h1p[c] = h1c[c];
       e1p[c] = e1c[c];
@@ -451,17 +392,15 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
       e0n[c] = e0f[c];
       h0c[c] = h0f[c];
     }
-    if (PML)
-      for (int a = 0; a < 3; ++a) {
-        psh[a][0] = pshn[a][0];
-        psh[a][1] = pshn[a][1];
-        pse[a][0] = psen[a][0];
-        pse[a][1] = psen[a][1];
-      }
+    for (int a = 0; a < 3; ++a) {
+      psh[a][0] = pshn[a][0];
+      psh[a][1] = pshn[a][1];
+      pse[a][0] = psen[a][0];
+      pse[a][1] = psen[a][1];
+    }
     cp = cc;
     cc = cf1;
   }
-  flush();
 }
 
 // ---------------------------------------------------------------------------
@@ -487,10 +426,10 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
 //
 // Measured (us per step, against one launch per CPML group of 8-row tiles
 // with three barriers, four LDS planes and 2.5 times the instructions):
-// 512 x 512 x 384 with a 10-cell CPML 789 (891), 203 x 157 x 131 52 (116),
-// 96 x 96 x 80 15 (82), 48^3 without one 4.3 (38, the fused pass).  In the
-// caches a plane of an 8-row tile takes 0.92 us clear of the CPML and 1.9 us
-// in it; on the largest grid 12 rows take 2.1 us, bound by the 5 TB/s that
+// 512 x 512 x 384 with a 10-cell CPML 743 (891), 203 x 157 x 131 44 (116),
+// 96 x 96 x 80 14.5 (82), 48^3 without one 4.3 (38, the fused pass).  In the
+// caches a plane of an 8-row tile takes 0.92 us clear of the CPML and 1.7 us
+// in it; on the largest grid 12 rows take 2 us, bound by the 5 TB/s that
 // the tiles draw through the L2s (a copy reaches 5.1).
 // ---------------------------------------------------------------------------
 
@@ -507,15 +446,21 @@ struct MarchSmem {
   T pz[P_NROW * PZ];    // the z table
 };
 
+// CPML profile values of a tile's points: a lane's x values in registers
+// (tiles of up to 8 rows, which have them to spare) or LDS, the row's y
+// values in scalar registers, z from LDS.
 template <typename T, int TY>
 struct ProfMarch {
+  static constexpr bool XREG = TY <= 8;
   const MarchSmem<T, TY>& sm;
   int tn, u;
-  T ye[3], yh[3];  // the y profile at this wave's row (uniform)
+  T x[XREG ? P_NROW : 1];
+  T y[P_NROW];  // uniform across the wave
   template <int U>
   __device__ __forceinline__ Prof3<T> at(int row, int l) const {
+    if (U == 0 && XREG) return row == P_BE ? Prof3<T>{x[0], x[1], x[2]} : Prof3<T>{x[3], x[4], x[5]};
     if (U == 0) return {sm.px[row][u], sm.px[row + 1][u], sm.px[row + 2][u]};
-    if (U == 1) return row == P_BE ? Prof3<T>{ye[0], ye[1], ye[2]} : Prof3<T>{yh[0], yh[1], yh[2]};
+    if (U == 1) return row == P_BE ? Prof3<T>{y[0], y[1], y[2]} : Prof3<T>{y[3], y[4], y[5]};
     const int q = row * tn + l;
     return {sm.pz[q], sm.pz[q + tn], sm.pz[q + 2 * tn]};
   }
@@ -550,18 +495,6 @@ __device__ __forceinline__ T next_lane(T v) { return lane_shift<0x130>(v); }
 template <typename T>
 __device__ __forceinline__ T prev_lane(T v) { return lane_shift<0x138>(v); }
 
-// Element access by a byte offset from a uniform base.
-template <typename T>
-__device__ __forceinline__ T ldb(const T* base, unsigned off) {
-  typedef __attribute__((address_space(1))) const T GT;
-  return *(GT*)((const __attribute__((address_space(1))) char*)base + off);
-}
-template <typename T>
-__device__ __forceinline__ void stb(T* base, unsigned off, T v) {
-  typedef __attribute__((address_space(1))) T GT;
-  *(GT*)((__attribute__((address_space(1))) char*)base + off) = v;
-}
-
 // A view whose members are read where they are used (by scalar loads), not
 // kept in scalar registers over the whole march.
 template <typename T>
@@ -575,6 +508,26 @@ struct ColdView {
   }
 };
 
+// A copy of the view behind p, read by scalar loads: p is the same for the
+// whole block, which the compiler does not see where a table of views is
+// indexed by a loaded value (it would hold every pointer in vector registers).
+template <typename T>
+__device__ __forceinline__ GridView<T> uniform_view(const GridView<T>* p) {
+  static_assert(sizeof(GridView<T>) % 8 == 0, "copied in 8-byte words");
+  constexpr int N = sizeof(GridView<T>) / 8;
+  const uint64_t a = (uint64_t)(uintptr_t)p;
+  const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a) |
+                     (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)) << 32;
+  typedef const __attribute__((address_space(4))) uint64_t* W;
+  const W w = (W)u;
+  struct {
+    uint64_t q[N];
+  } v;
+#pragma unroll
+  for (int i = 0; i < N; ++i) v.q[i] = w[i];
+  return __builtin_bit_cast(GridView<T>, v);
+}
+
 // The state of one thread's point, registers named by plane modulo 3.
 template <typename T>
 struct MarchRegs {
@@ -584,8 +537,9 @@ struct MarchRegs {
   T e1[3][3];       // E^{n+1}
   T h2[3][3];       // H^{n+3/2}
   T e2[3];          // E^{n+2} of D
-  T ph[3][3][2];    // CPML state, H-type [plane][axis][component]
-  T pe[3][3][2];    // E-type
+  typedef T Pair __attribute__((ext_vector_type(2)));
+  Pair ph[3][3];    // CPML state, H-type [plane][axis]
+  Pair pe[3][3];    // E-type
   unsigned co[3];   // LDS row (in values) of the class
 };
 
@@ -604,6 +558,7 @@ struct March {
   static constexpr bool PML = AX != 0, SX = AX & 1, SY = AX & 2, SZ = AX & 4;
   static constexpr unsigned S = sizeof(T), NONE = 0xFFFFFFFFu;
 
+  typedef typename MarchRegs<T>::Pair Pair;
   MarchSmem<T, TY>& sm;
   ColdView<T> g;
   const T* fi[6];
@@ -613,7 +568,13 @@ struct March {
   int lx, ly;
   unsigned n0, n0s, sxy;           // column index, its byte offset; nodes per plane
   bool dom, inD;
-  unsigned qx, qy;
+  // CPML state: bases, the output set's distance (values), and per axis the
+  // column's byte offset, the step per plane (x, y) and the H-type pairs'
+  // distance
+  const T* pib[3];
+  ptrdiff_t pout;
+  unsigned qx, qy, qz, dx, dy, dkind[3];
+  int lz[3];                       // z slab position of the planes in the three slots
   SrcRange srcr;
   ProfMarch<T, TY> pf;
   MarchRegs<T> r;
@@ -630,58 +591,64 @@ struct March {
   __device__ __forceinline__ unsigned row_of(unsigned c, bool in) const {
     return LDS_TAB ? (in ? (c + 1u) * K_STRIDE : 0u) : (in ? c * K_STRIDE : NONE);
   }
-  __device__ __forceinline__ void slab3(int k, int l[3]) const {
-    const bool in = k >= 0 && k < nz;
-    l[0] = SX && in ? lx : -1;
-    l[1] = SY && in ? ly : -1;
-    l[2] = SZ && in ? slab_pos(k, nz, np) : -1;
+  // Both kinds of CPML state of plane k (z slab position lz): H-type into
+  // ph, E-type into pe (values outside the slabs are not used); and back.
+  template <int A, bool LOAD>
+  __device__ __forceinline__ void psi_axis(bool on, unsigned off, Pair& ph, Pair& pe) const {
+    const Pair* p = (const Pair*)(LOAD ? pib[A] : pib[A] + pout);
+    Pair h = ph, e = pe;
+    if (on && LOAD) {
+      e = ldb(p, off);
+      h = ldb(p, off + dkind[A]);
+    } else if (on) {
+      stb((Pair*)p, off, e);
+      stb((Pair*)p, off + dkind[A], h);
+    }
+    if (LOAD) {
+      pe = e;
+      ph = h;
+    }
   }
-  // Both kinds of CPML state of plane k: H-type into ph, E-type into pe
-  // (values outside the slabs are not used); and back from plane k's.
   template <bool LOAD>
-  __device__ __forceinline__ void psi(int k, T ph[3][2], T pe[3][2]) const {
-    const int lz = SZ ? slab_pos(k, nz, np) : -1;
-    auto move = [&](int a, size_t plane, unsigned q) {
-      const size_t el = g->pel[a];
-      const T* pi = g->pib[a] + plane;
-      T* po = g->pob[a] + plane;
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        if (LOAD) {
-          pe[a][c] = ldg(pi + el * c, q);
-          ph[a][c] = ldg(pi + el * (2 + c), q);
-        } else {
-          stg(po + el * c, q, pe[a][c]);
-          stg(po + el * (2 + c), q, ph[a][c]);
-        }
-      }
-    };
-    if (SX && lx >= 0) move(0, (size_t)(2 * np) * (size_t)(unsigned)g->ny * (size_t)k, qx);
-    if (SY && ly >= 0) move(1, (size_t)(2 * np) * (size_t)(unsigned)g->nx * (size_t)k, qy);
-    if (SZ && lz >= 0) move(2, (size_t)sxy * (size_t)lz, n0);
+  __device__ __forceinline__ void psi(int k, int lzk, Pair (&ph)[3], Pair (&pe)[3]) const {
+    if (SX) psi_axis<0, LOAD>(lx >= 0, qx + (unsigned)k * dx, ph[0], pe[0]);
+    if (SY) psi_axis<1, LOAD>(ly >= 0, qy + (unsigned)k * dy, ph[1], pe[1]);
+    if (SZ) psi_axis<2, LOAD>(lzk >= 0, qz + (unsigned)lzk * (sxy * 2u * S), ph[2], pe[2]);
   }
 
   // H of plane k (A and C): e and en the E of planes k and k + 1, le the
   // plane's E (x, z) in LDS.
-  __device__ __forceinline__ void stage_h(int k, unsigned row, const T e[3], const T en[3], const T (*le)[TY + 4][64],
-                                          const T hold[3], T ps[3][2], T hn[3]) const {
+  __device__ __forceinline__ void stage_h(int lzk, unsigned row, const T e[3], const T en[3], const T (*le)[TY + 4][64],
+                                          const T hold[3], Pair (&pp)[3], T hn[3]) const {
     T cf[K_STRIDE];
     coef<K_DBX, 3>(row, cf);
-    int l[3];
-    slab3(k, l);
+    T p0[2], p1[2], p2[2];
+    if (SX) p0[0] = pp[0].x, p0[1] = pp[0].y;
+    if (SY) p1[0] = pp[1].x, p1[1] = pp[1].y;
+    if (SZ) p2[0] = pp[2].x, p2[1] = pp[2].y;
+    const int l[3] = {SX ? lx : -1, SY ? ly : -1, SZ ? lzk : -1};
     h_core_pf<T, PML>(pf, l, cf, e[0], e[1], e[2], le[0][v + 1][u], en[0], next_lane(e[1]), en[1], next_lane(e[2]),
-                      le[1][v + 1][u], hold, ps, hn);
+                      le[1][v + 1][u], hold, p0, p1, p2, hn);
+    if (SX) pp[0] = Pair{p0[0], p0[1]};
+    if (SY) pp[1] = Pair{p1[0], p1[1]};
+    if (SZ) pp[2] = Pair{p2[0], p2[1]};
   }
   // E of plane k (B and D): h and hp the H of planes k and k - 1, lh the
   // plane's H (x, z) in LDS.
-  __device__ __forceinline__ void stage_e(int k, unsigned row, const T h[3], const T hp[3], const T (*lh)[TY + 4][64],
-                                          const T eold[3], int st, T ps[3][2], T en[3]) const {
+  __device__ __forceinline__ void stage_e(int k, int lzk, unsigned row, const T h[3], const T hp[3], const T (*lh)[TY + 4][64],
+                                          const T eold[3], int st, Pair (&pp)[3], T en[3]) const {
     T cf[K_STRIDE];
     coef<K_CAX, 6>(row, cf);
-    int l[3];
-    slab3(k, l);
+    T p0[2], p1[2], p2[2];
+    if (SX) p0[0] = pp[0].x, p0[1] = pp[0].y;
+    if (SY) p1[0] = pp[1].x, p1[1] = pp[1].y;
+    if (SZ) p2[0] = pp[2].x, p2[1] = pp[2].y;
+    const int l[3] = {SX ? lx : -1, SY ? ly : -1, SZ ? lzk : -1};
     e_core_pf<T, PML>(pf, l, cf, h[0], h[1], h[2], lh[0][v - 1][u], hp[0], prev_lane(h[1]), hp[1], prev_lane(h[2]),
-                      lh[1][v - 1][u], eold, ps, en);
+                      lh[1][v - 1][u], eold, p0, p1, p2, en);
+    if (SX) pp[0] = Pair{p0[0], p0[1]};
+    if (SY) pp[1] = Pair{p1[0], p1[1]};
+    if (SZ) pp[2] = Pair{p2[0], p2[1]};
     if (k >= srcr.klo && k <= srcr.khi)  // uniform
       e_sources(g, srcr.lo, srcr.hi, dom ? n0 + sxy * (unsigned)k : NONE, st, en);
   }
@@ -703,13 +670,13 @@ struct March {
       for (int c = 0; c < 3; ++c) r.e0[P1][c] = ldb(fi[c], n0s + pe * S);
       // X: A of plane k, D of plane k-2
       if (v <= TY + 2) {
-        stage_h(k, r.co[Q], r.e0[Q], r.e0[N1], sm.e0, r.h0[Q], r.ph[Q], r.h1[Q]);
+        stage_h(lz[Q], r.co[Q], r.e0[Q], r.e0[N1], sm.e0, r.h0[Q], r.ph[Q], r.h1[Q]);
         sm.h1[0][v][u] = r.h1[Q][0];
         sm.h1[1][v][u] = r.h1[Q][2];
       }
     }
     if (v >= 2 && v <= TY + 1 && k - 2 >= k0)
-      stage_e(k - 2, r.co[P2], r.h2[P2], r.h2[Q], sm.h2, r.e1[P2], step + 1, r.pe[P2], r.e2);
+      stage_e(k - 2, lz[P2], r.co[P2], r.h2[P2], r.h2[Q], sm.h2, r.e1[P2], step + 1, r.pe[P2], r.e2);
     if (!TAIL) __syncthreads();
     // the outputs of plane k-2
     if (inD && k - 2 >= k0) {
@@ -718,16 +685,26 @@ struct March {
       for (int c = 0; c < 3; ++c) stb(fo[c], o, r.e2[c]);
 #pragma unroll
       for (int c = 0; c < 3; ++c) stb(fo[3 + c], o, r.h2[P2][c]);
-      if (PML) psi<false>(k - 2, r.ph[P2], r.pe[P2]);
+      if (PML) psi<false>(k - 2, lz[P2], r.ph[P2], r.pe[P2]);
     }
-    if (TAIL) return;
-    if (PML && k + 1 >= 0 && k + 1 < nz) psi<true>(k + 1, r.ph[N1], r.pe[N1]);
+    if (TAIL) {
+      // (keeps the compiler from merging the three slots' tails, which would
+      // put the registers they store into memory)
+      asm volatile("" ::"i"(Q));
+      return;
+    }
+    if (PML && k + 1 < nz) {  // (planes outside the grid keep finite values that no output sees)
+      lz[N1] = SZ ? slab_pos(k + 1, nz, np) : -1;
+      if (k + 1 >= 0) psi<true>(k + 1, lz[N1], r.ph[N1], r.pe[N1]);
+    } else if (PML) {
+      lz[N1] = -1;
+    }
     // Y: B of plane k, C of plane k-1
     const int s1 = k & 1, s1m = s1 ^ 1;
     if (v >= 1 && v <= TY + 2 && k >= k0 - 1) {
-      stage_e(k, r.co[Q], r.h1[Q], r.h1[P1], sm.h1, r.e0[Q], step, r.pe[Q], r.e1[Q]);
+      stage_e(k, lz[Q], r.co[Q], r.h1[Q], r.h1[P1], sm.h1, r.e0[Q], step, r.pe[Q], r.e1[Q]);
       if (v <= TY + 1 && k >= k0) {
-        stage_h(k - 1, r.co[P1], r.e1[P1], r.e1[Q], sm.e1[s1m], r.h1[P1], r.ph[P1], r.h2[P1]);
+        stage_h(lz[P1], r.co[P1], r.e1[P1], r.e1[Q], sm.e1[s1m], r.h1[P1], r.ph[P1], r.h2[P1]);
         sm.h2[0][v][u] = r.h2[P1][0];
         sm.h2[1][v][u] = r.h2[P1][2];
       }
@@ -742,7 +719,7 @@ struct March {
   __device__ __forceinline__ March(const GridView<T>& gv, ColdView<T> cold, MarchSmem<T, TY>& sm_, int i0, int j0,
                                    int iw, int jh, int k0_, int k1_, int step_)
       : sm(sm_), g(cold), nz(gv.nz), np(gv.npml), step(step_), k0(k0_), k1(k1_),
-        pf{sm_, 0, 0, {T(0), T(0), T(0)}, {T(0), T(0), T(0)}} {
+        pf{sm_, 0, 0, {}, {}} {
     const int tid = threadIdx.x, nx = gv.nx, ny = gv.ny;
     u = tid & 63;
     v = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -763,19 +740,31 @@ struct March {
     pf.u = u;
     if (PML) {
       const int tn = 2 * np;
-      if (SX && v == 0) {
+      if (SX) {
         const int xl = x >= 0 && x < nx ? slab_pos(x, nx, np) : -1;
-        for (int q = 0; q < P_NROW; ++q) sm.px[q][u] = xl >= 0 ? ldg(gv.prof[0], (unsigned)(q * tn + xl)) : T(0);
-      }
-      if (SY && ly >= 0)
-        for (int q = 0; q < 3; ++q) {
-          pf.ye[q] = uniform(ldg(gv.prof[1], (unsigned)((P_BE + q) * tn + ly)));
-          pf.yh[q] = uniform(ldg(gv.prof[1], (unsigned)((P_BH + q) * tn + ly)));
+#pragma unroll
+        for (int q = 0; q < P_NROW; ++q) {
+          if (pf.XREG) pf.x[q] = xl >= 0 ? ldg(gv.prof[0], (unsigned)(q * tn + xl)) : T(0);
+          else if (v == 0) sm.px[q][u] = xl >= 0 ? ldg(gv.prof[0], (unsigned)(q * tn + xl)) : T(0);
         }
+      }
+#pragma unroll
+      for (int q = 0; q < P_NROW; ++q) pf.y[q] = SY && ly >= 0 ? uniform(ldg(gv.prof[1], (unsigned)(q * tn + ly))) : T(0);
       if (SZ)
         for (int q = tid; q < P_NROW * tn; q += NT) sm.pz[q] = ldg(gv.prof[2], (unsigned)q);
-      qx = SX ? (unsigned)max(lx, 0) + 2u * np * (unsigned)(dom ? y : 0) : 0u;
-      qy = SY ? (unsigned)(dom ? x : 0) + (unsigned)nx * (unsigned)max(ly, 0) : 0u;
+      constexpr unsigned P = 2 * S;  // bytes of a pair
+      dx = 2u * np * (unsigned)ny * P;
+      dy = 2u * np * (unsigned)nx * P;
+      qx = SX ? ((unsigned)max(lx, 0) + 2u * np * (unsigned)(dom ? y : 0)) * P : 0u;
+      qy = SY ? ((unsigned)(dom ? x : 0) + (unsigned)nx * (unsigned)max(ly, 0)) * P : 0u;
+      qz = n0 * P;
+      pout = gv.pob[0] - gv.pib[0];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        pib[a] = gv.pib[a];
+        asm volatile("" : "+s"(pib[a]));  // (kept, not read again in every plane)
+        dkind[a] = gv.pel[a] * P;
+      }
     }
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
@@ -793,7 +782,15 @@ struct March {
       r.e0[0][c] = ldb(fi[c], n0s + pa * S);
       r.e0[1][c] = ldb(fi[c], n0s + pb * S);
     }
-    if (PML && kb >= 0) psi<true>(kb, r.ph[0], r.pe[0]);
+    if (PML) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) r.ph[q][a] = r.pe[q][a] = Pair{T(0), T(0)};
+      lz[0] = SZ && kb >= 0 ? slab_pos(kb, nz, np) : -1;
+      lz[1] = lz[2] = -1;
+      if (kb >= 0) psi<true>(kb, lz[0], r.ph[0], r.pe[0]);
+    }
 #pragma unroll
     for (int q = 0; q < 3; ++q)
 #pragma unroll
@@ -936,7 +933,7 @@ template <int TY>
 union TileSmem<float, TY> {
   MarchSmem<float, TY> m;
 };
-template <typename T, typename CI, bool PML, int TY, bool FULL>
+template <typename T, typename CI, bool PML, int TY>
 __device__ __forceinline__ void tb2_any(const GridView<T>& g, ColdView<T> cold, TileSmem<T, TY>& sm, int i0, int j0,
                                         int iw, int jh, int k0, int k1, int step) {
   if constexpr (!PML) {
@@ -945,14 +942,14 @@ __device__ __forceinline__ void tb2_any(const GridView<T>& g, ColdView<T> cold, 
     const int n = g.npml;
     const bool cx = i0 - 2 >= n && i0 + 62 <= g.nx - n, cy = j0 - 2 >= n && j0 + TY + 2 <= g.ny - n,
                cz = k0 - 2 >= n && k1 < g.nz - n;
-    if (FULL && cx && cy && cz) {
+    if (cx && cy && cz) {
       March<T, CI, TY, 0>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
     } else if constexpr (sizeof(T) == 8) {
-      tb2_tile<T, CI, true, TY, 7, false, true>(g, sm.t, i0, j0, iw, jh, k0, k1, step);
+      tb2_tile<T, CI, TY>(g, sm.t, i0, j0, iw, jh, k0, k1, step);
     } else {
-      if (FULL && cx && cy) March<T, CI, TY, 4>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
+      if (cx && cy) March<T, CI, TY, 4>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
       else if (cy) March<T, CI, TY, 5>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
-      else if (FULL && cx) March<T, CI, TY, 6>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
+      else if (cx) March<T, CI, TY, 6>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
       else March<T, CI, TY, 7>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
     }
   }
@@ -988,80 +985,39 @@ __global__ __launch_bounds__(64 * (TY + 4), tb2_waves(sizeof(T), PML, TY)) void 
   const int tile_x = tile % ntx, rest = tile / ntx, k0 = (rest / nty) * kz;
   // the view is the kernel's first argument: read again where it is needed
   const ColdView<T> cold{(typename ColdView<T>::P)__builtin_amdgcn_kernarg_segment_ptr()};
-  tb2_any<T, CI, PML, TY, true>(g, cold, sm, tile_x * 60, (rest % nty) * TY, 60, TY, k0, min(k0 + kz, g.nz), step);
+  tb2_any<T, CI, PML, TY>(g, cold, sm, tile_x * 60, (rest % nty) * TY, 60, TY, k0, min(k0 + kz, g.nz), step);
 }
 
-// Batched two-step probes: entry q of the list is (grid, probe).
+// Batched two-step pass: as k_tb2 over a tile list that spans every grid
+// (grid, i0 | iw << 16, j0 | jh << 16, k0 | kz << 16) and a list of (grid,
+// probe) pairs; step index *d_step + offset.  Nearly every tile of a small
+// grid is in the CPML and marches at 1.7 us a plane, instruction bound.  256
+// grids of 32 to 96 cells a side with an 8-cell CPML: 1179 us a step (1473
+// with one work-queue launch per CPML group and a probe launch); 64 of them
+// 296, 8 of them 47 (80).
 template <typename T, typename CI>
-__global__ __launch_bounds__(PR_NT) void k_probes_tb2_batch(const GridView<T>* __restrict__ views,
-                                                           const int2* __restrict__ plist, int n,
-                                                           const int* __restrict__ d_step, int offset) {
-  __shared__ double red[8];
-  if ((int)blockIdx.x >= n) return;  // uniform per block
-  const int2 e = plist[blockIdx.x];
-  probe_tb2<T, CI, true, true>(views[e.x], e.y, *d_step + offset, (int)threadIdx.x, red);
-}
-
-// Batched two-step pass: tile (grid, i0 | iw << 16, j0 | jh << 16,
-// k0 | kz << 16) per block; step index *d_step + offset.  FP32: at most 80
-// VGPRs, so that two blocks share a CU.
-template <typename T, typename CI, int TY, int AX>
-__global__ __launch_bounds__(64 * (TY + 4), (sizeof(T) == 8 ? 1 : 6)) void k_tb2_batch(const GridView<T>* __restrict__ views,
-                                                                               const int4* __restrict__ tiles,
-                                                                               const int* __restrict__ d_step,
-                                                                               int offset) {
-  __shared__ TB2Smem<T, TY> sm;
-  const int4 t = tiles[xcd_tile(blockIdx.x, gridDim.x)];
-  const GridView<T>& g = views[t.x];
-  const int k0 = t.w & 0xffff;
-  tb2_tile<T, CI, true, TY, AX, false, true>(g, sm, t.y & 0xffff, t.z & 0xffff, t.y >> 16, t.z >> 16, k0,
-                                             k0 + (t.w >> 16),
-                                             *d_step + offset);
-}
-
-// Batched two-step pass as persistent launches, one per code path (AXP 5:
-// the x-slab instantiation, which also serves tiles clear of the x and y
-// slabs; AXP 7: the all-axes one, for y-slab and corner tiles, and every FP64
-// tile).  One kernel holding both paths spilled at its 80-register cap, and
-// each reload of a spill waited for all loads in flight.  A path's tile list
-// holds its tiles grid by grid (larger grids first), (grid | group << 24,
-// i0 | iw << 16, j0 | jh << 16, k0 | kz << 16), cut into 8 contiguous runs,
-// one per XCD, so that a grid's tiles share that XCD's L2.  A block takes
-// tiles from its own XCD's run through an atomic counter, then from the
-// other runs in turn, and leaves once every run is empty: each counter only
-// grows, so every block finishes.  Tiles of one pass write disjoint outputs
-// and read only the pass's input set, so no block waits for another (nor a
-// kernel for the other path's).  The counters start at 0 (k_qreset before
-// the launches).
-template <typename T, typename CI, int AXP>
-__global__ __launch_bounds__(768, (sizeof(T) == 8 ? 1 : 6)) void k_tb2_batch_q(const GridView<T>* __restrict__ views,
-                                                                             const int4* __restrict__ tiles,
-                                                                             QRuns runs, int* __restrict__ ctr,
-                                                                             const int* __restrict__ d_step,
-                                                                             int offset) {
-  __shared__ TB2Smem<T, 8> sm;
-  __shared__ int pick;
+__global__ __launch_bounds__(768, tb2_waves(sizeof(T), true, 8)) void k_tb2_batch(
+    const GridView<T>* __restrict__ views, const int4* __restrict__ tiles, const int2* __restrict__ plist, int n_probes,
+    int npb, const int* __restrict__ d_step, int offset, int prev, int run) {
   const int step = *d_step + offset;
-  const int x0 = (int)(blockIdx.x % 8);
-  for (int r = 0; r < 8; ++r) {
-    const int x = (x0 + r) % 8, base = runs.start[x], n = runs.start[x + 1] - base;
-    for (;;) {
-      __syncthreads();  // the previous tile is done with the LDS and with `pick`
-      if (threadIdx.x == 0) pick = atomicAdd(ctr + x, 1);
-      __syncthreads();
-      const int q = __builtin_amdgcn_readfirstlane(pick);  // uniform: the tile is read into scalar registers
-      if (q >= n) break;
-      const int4 t = tiles[base + q];
-      const GridView<T>& g = views[t.x & 0xffffff];
-      const int i0 = t.y & 0xffff, j0 = t.z & 0xffff, iw = t.y >> 16, jh = t.z >> 16;
-      const int k0 = t.w & 0xffff, k1 = k0 + (t.w >> 16);
-      tb2_tile<T, CI, true, 8, AXP, false, true>(g, sm, i0, j0, iw, jh, k0, k1, step);
-    }
+  __shared__ TileSmem<T, 8> sm;
+  constexpr int GRP = 768 / PR_NT;
+  __shared__ double red[12 * GRP];
+  if ((int)blockIdx.x < npb) {  // uniform per block
+    const int grp = (int)threadIdx.x / PR_NT, t = (int)threadIdx.x % PR_NT, q = (int)blockIdx.x * GRP + grp;
+    const int2 e = plist[min(q, n_probes - 1)];
+    const int p = q < n_probes ? e.y : -1;
+    probe_tb2<T, CI, true, false>(views[e.x], p, step, t, red + 12 * grp);
+    if (prev) probe_one(views[e.x], p, step - 1, t, red + 12 * grp + 8);
+    return;
   }
-}
-
-__global__ void k_qreset(int* ctr) {
-  if (threadIdx.x < 16) ctr[threadIdx.x] = 0;
+  const int4 t = tiles[xcd_runs((int)blockIdx.x - npb, (int)gridDim.x - npb, run)];
+  const int tx = __builtin_amdgcn_readfirstlane(t.x), ty = __builtin_amdgcn_readfirstlane(t.y),
+            tz = __builtin_amdgcn_readfirstlane(t.z), tw = __builtin_amdgcn_readfirstlane(t.w);
+  const GridView<T> g = uniform_view(views + tx);
+  const ColdView<T> cold{(typename ColdView<T>::P)(uintptr_t)(views + tx)};
+  const int k0 = tw & 0xffff;
+  tb2_any<T, CI, true, 8>(g, cold, sm, ty & 0xffff, tz & 0xffff, ty >> 16, tz >> 16, k0, k0 + (tw >> 16), step);
 }
 
 // ---------------------------------------------------------------------------
@@ -1503,143 +1459,27 @@ int launch_batch_probes(int prec, const void* views, const void* plist, int n, c
   return (int)hipGetLastError();
 }
 
-// Probes of both steps of a batched two-step pass (one block per (grid,
-// probe) pair).
-int batch_probes_tb2(int prec, int cls16, const void* views, const void* plist, int n_probes, const int* d_step,
-                     int offset, hipStream_t st) {
-  if (n_probes <= 0) return 0;
-  const dim3 grd((unsigned)n_probes), blk(PR_NT);
-  if (prec == 64) {
-    if (cls16)
-      hipLaunchKernelGGL((k_probes_tb2_batch<double, uint16_t>), grd, blk, 0, st, (const GridView<double>*)views,
-                         (const int2*)plist, n_probes, d_step, offset);
-    else
-      hipLaunchKernelGGL((k_probes_tb2_batch<double, uint8_t>), grd, blk, 0, st, (const GridView<double>*)views,
-                         (const int2*)plist, n_probes, d_step, offset);
-  } else {
-    if (cls16)
-      hipLaunchKernelGGL((k_probes_tb2_batch<float, uint16_t>), grd, blk, 0, st, (const GridView<float>*)views,
-                         (const int2*)plist, n_probes, d_step, offset);
-    else
-      hipLaunchKernelGGL((k_probes_tb2_batch<float, uint8_t>), grd, blk, 0, st, (const GridView<float>*)views,
-                         (const int2*)plist, n_probes, d_step, offset);
-  }
-  return (int)hipGetLastError();
-}
-
-// Group q of the pass's tile list runs the instantiation for the slabs its
-// tiles reach (FP64: the all-axes one).
 template <typename T, typename CI>
-hipError_t batch_group_t(int q, const void* views, const int4* t, int count, const int* d_step, int offset,
-                         hipStream_t st) {
-  constexpr bool D = sizeof(T) == 8;
-  const GridView<T>* v = (const GridView<T>*)views;
-  const dim3 blk(64 * 12), grd((unsigned)count);
-  if (q == 0) hipLaunchKernelGGL((k_tb2_batch<T, CI, 8, D ? 7 : 4>), grd, blk, 0, st, v, t, d_step, offset);
-  if (q == 1) hipLaunchKernelGGL((k_tb2_batch<T, CI, 8, D ? 7 : 5>), grd, blk, 0, st, v, t, d_step, offset);
-  if (q == 2) hipLaunchKernelGGL((k_tb2_batch<T, CI, 8, D ? 7 : 6>), grd, blk, 0, st, v, t, d_step, offset);
-  if (q == 3) hipLaunchKernelGGL((k_tb2_batch<T, CI, 8, 7>), grd, blk, 0, st, v, t, d_step, offset);
+hipError_t batch_pass_t(const void* views, const void* tiles, int n_tiles, const void* plist, int n_probes,
+                        const int* d_step, int offset, int prev, int run, hipStream_t st) {
+  const int npb = (n_probes + 768 / PR_NT - 1) / (768 / PR_NT);
+  hipLaunchKernelGGL((k_tb2_batch<T, CI>), dim3((unsigned)(npb + n_tiles)), dim3(768), 0, st,
+                     (const GridView<T>*)views, (const int4*)tiles, (const int2*)plist, n_probes, npb, d_step, offset,
+                     prev, run);
   return hipGetLastError();
 }
 
-template <typename T, typename CI>
-hipError_t batch_queue_t(const void* views, const int4* tiles_a, const QRuns& runs_a, int blocks_a,
-                         const int4* tiles_b, const QRuns& runs_b, int blocks_b, int* ctr, const int* d_step,
-                         int offset, hipStream_t st, hipStream_t st2, hipEvent_t ev_fork, hipEvent_t ev_join) {
-  const GridView<T>* v = (const GridView<T>*)views;
-  hipLaunchKernelGGL(k_qreset, dim3(1), dim3(64), 0, st, ctr);
-  // the all-axes path (slower per cell) on the second stream, launched
-  // first: both launches fill the device, so the x-slab path's blocks start
-  // as the all-axes ones drain and fill the end of the pass
-  const bool fork = blocks_a > 0 && blocks_b > 0;
-  hipError_t e = hipSuccess;
-  if (fork) {
-    e = hipEventRecord(ev_fork, st);
-    if (e == hipSuccess) e = hipStreamWaitEvent(st2, ev_fork, 0);
-    if (e != hipSuccess) return e;
-  }
-  if (blocks_b > 0)
-    hipLaunchKernelGGL((k_tb2_batch_q<T, CI, 7>), dim3((unsigned)blocks_b), dim3(768), 0, fork ? st2 : st, v,
-                       tiles_b, runs_b, ctr + 8, d_step, offset);
-  if (blocks_a > 0)
-    hipLaunchKernelGGL((k_tb2_batch_q<T, CI, 5>), dim3((unsigned)blocks_a), dim3(768), 0, st, v, tiles_a, runs_a, ctr,
-                       d_step, offset);
-  if (fork) {
-    e = hipEventRecord(ev_join, st2);
-    if (e == hipSuccess) e = hipStreamWaitEvent(st, ev_join, 0);
-    if (e != hipSuccess) return e;
-  }
-  return hipGetLastError();
-}
-
-template <typename T, typename CI, int AXP>
-int queue_blocks_t() {
-  int dev = 0, cus = 0, per = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_tb2_batch_q<T, CI, AXP>, 768, 0) != hipSuccess) return 0;
-  return cus * std::max(per, 1);
-}
-
-int batch_queue_blocks(int prec, int cls16, int axp) {
-  if (prec == 64) {
-    if (axp == 5) return cls16 ? queue_blocks_t<double, uint16_t, 5>() : queue_blocks_t<double, uint8_t, 5>();
-    return cls16 ? queue_blocks_t<double, uint16_t, 7>() : queue_blocks_t<double, uint8_t, 7>();
-  }
-  if (axp == 5) return cls16 ? queue_blocks_t<float, uint16_t, 5>() : queue_blocks_t<float, uint8_t, 5>();
-  return cls16 ? queue_blocks_t<float, uint16_t, 7>() : queue_blocks_t<float, uint8_t, 7>();
-}
-
-int launch_batch_pass_queue(int prec, int cls16, const void* views, const void* tiles_a, const QRuns* runs_a,
-                            int blocks_a, const void* tiles_b, const QRuns* runs_b, int blocks_b, int* ctr,
-                            const void* plist, int n_probes, const int* d_step, int offset, void* stream,
-                            void* stream2, void* ev_fork, void* ev_join) {
-  hipStream_t st = (hipStream_t)stream, st2 = (hipStream_t)stream2;
-  hipEvent_t ef = (hipEvent_t)ev_fork, ej = (hipEvent_t)ev_join;
-  const int4 *ta = (const int4*)tiles_a, *tb = (const int4*)tiles_b;
+int launch_batch_pass(int prec, int cls16, const void* views, const void* tiles, int n_tiles, const void* plist,
+                      int n_probes, const int* d_step, int offset, int prev, int run, void* stream) {
+  hipStream_t st = (hipStream_t)stream;
   hipError_t e;
   if (prec == 64)
-    e = cls16 ? batch_queue_t<double, uint16_t>(views, ta, *runs_a, blocks_a, tb, *runs_b, blocks_b, ctr, d_step,
-                                                offset, st, st2, ef, ej)
-              : batch_queue_t<double, uint8_t>(views, ta, *runs_a, blocks_a, tb, *runs_b, blocks_b, ctr, d_step,
-                                               offset, st, st2, ef, ej);
+    e = cls16 ? batch_pass_t<double, uint16_t>(views, tiles, n_tiles, plist, n_probes, d_step, offset, prev, run, st)
+              : batch_pass_t<double, uint8_t>(views, tiles, n_tiles, plist, n_probes, d_step, offset, prev, run, st);
   else
-    e = cls16 ? batch_queue_t<float, uint16_t>(views, ta, *runs_a, blocks_a, tb, *runs_b, blocks_b, ctr, d_step,
-                                               offset, st, st2, ef, ej)
-              : batch_queue_t<float, uint8_t>(views, ta, *runs_a, blocks_a, tb, *runs_b, blocks_b, ctr, d_step,
-                                              offset, st, st2, ef, ej);
-  if (e != hipSuccess) return (int)e;
-  return batch_probes_tb2(prec, cls16, views, plist, n_probes, d_step, offset, st);
-}
-
-int launch_batch_pass_tb2(int prec, int cls16, const void* views, const void* tiles, const int* counts,
-                          const void* plist, int n_probes, const int* d_step, int offset, void* stream,
-                          void* stream2, void* ev_fork, void* ev_join) {
-  hipStream_t st = (hipStream_t)stream, st2 = (hipStream_t)stream2;
-  hipError_t e = hipSuccess;
-  // group 1 on the second stream beside the others, when both are there
-  const bool fork = st2 && counts[1] > 0 && counts[0] + counts[2] + counts[3] > 0;
-  if (fork) {
-    e = hipEventRecord((hipEvent_t)ev_fork, st);
-    if (e == hipSuccess) e = hipStreamWaitEvent(st2, (hipEvent_t)ev_fork, 0);
-  }
-  const int4* t = (const int4*)tiles;
-  for (int q = 0; q < 4 && e == hipSuccess; t += counts[q], ++q) {
-    if (counts[q] <= 0) continue;
-    hipStream_t s = fork && q == 1 ? st2 : st;
-    if (prec == 64)
-      e = cls16 ? batch_group_t<double, uint16_t>(q, views, t, counts[q], d_step, offset, s)
-                : batch_group_t<double, uint8_t>(q, views, t, counts[q], d_step, offset, s);
-    else
-      e = cls16 ? batch_group_t<float, uint16_t>(q, views, t, counts[q], d_step, offset, s)
-                : batch_group_t<float, uint8_t>(q, views, t, counts[q], d_step, offset, s);
-  }
-  if (fork && e == hipSuccess) {
-    e = hipEventRecord((hipEvent_t)ev_join, st2);
-    if (e == hipSuccess) e = hipStreamWaitEvent(st, (hipEvent_t)ev_join, 0);
-  }
-  if (e != hipSuccess) return (int)e;
-  return batch_probes_tb2(prec, cls16, views, plist, n_probes, d_step, offset, st);
+    e = cls16 ? batch_pass_t<float, uint16_t>(views, tiles, n_tiles, plist, n_probes, d_step, offset, prev, run, st)
+              : batch_pass_t<float, uint8_t>(views, tiles, n_tiles, plist, n_probes, d_step, offset, prev, run, st);
+  return (int)e;
 }
 
 __global__ void k_set(int* p, int v) {

@@ -38,9 +38,8 @@ __device__ __forceinline__ void psi_load(const GridView<T>& g, int kind, const i
   for (int u = 0; u < 3; ++u) {
     ps[u][0] = ps[u][1] = T(0);
     if (l[u] >= 0) {
-      const unsigned q = psi_index(u, l[u], x, y, k, g.nx, g.ny, g.npml) + (unsigned)(2 * kind) * g.pel[u];
-      ps[u][0] = ldg(g.pib[u], q);
-      ps[u][1] = ldg(g.pib[u], q + g.pel[u]);
+      const unsigned q = psi_index(u, l[u], x, y, k, g.nx, g.ny, g.npml) + (unsigned)kind * g.pel[u];
+      ld_pair(g.pib[u], q * 2u * (unsigned)sizeof(T), ps[u]);
     }
   }
 }
@@ -49,9 +48,8 @@ __device__ __forceinline__ void psi_store(const GridView<T>& g, int kind, const 
                                           const T ps[3][2]) {
   for (int u = 0; u < 3; ++u) {
     if (l[u] >= 0) {
-      const unsigned q = psi_index(u, l[u], x, y, k, g.nx, g.ny, g.npml) + (unsigned)(2 * kind) * g.pel[u];
-      stg(g.pob[u], q, ps[u][0]);
-      stg(g.pob[u], q + g.pel[u], ps[u][1]);
+      const unsigned q = psi_index(u, l[u], x, y, k, g.nx, g.ny, g.npml) + (unsigned)kind * g.pel[u];
+      st_pair(g.pob[u], q * 2u * (unsigned)sizeof(T), ps[u]);
     }
   }
 }
@@ -74,30 +72,30 @@ struct ProfG {
 };
 
 // H^{n+1/2} of one node from E^n at the node (ex, ey, ez), at x+1 (ey_i,
-// ez_i), y+1 (ex_j, ez_j) and k+1 (ex_k, ey_k); ps is the node's H-type CPML
-// state, advanced in place.
+// ez_i), y+1 (ex_j, ez_j) and k+1 (ex_k, ey_k); p0, p1, p2 are the node's
+// H-type CPML pairs along x, y and z, advanced in place.
 template <typename T, bool PML, typename PF>
 __device__ __forceinline__ void h_core_pf(const PF& pf, const int l[3], const T* cf, T ex, T ey, T ez, T ex_j,
-                                          T ex_k, T ey_i, T ey_k, T ez_i, T ez_j, const T hold[3], T ps[3][2],
-                                          T hnew[3]) {
+                                          T ex_k, T ey_i, T ey_k, T ez_i, T ez_j, const T hold[3], T* p0,
+                                          T* p1, T* p2, T hnew[3]) {
   T a_hx = ey_k - ey, b_hx = ez_j - ez;  // Hx: dEy/dz - dEz/dy
   T a_hy = ez_i - ez, b_hy = ex_k - ex;  // Hy: dEz/dx - dEx/dz
   T a_hz = ex_j - ex, b_hz = ey_i - ey;  // Hz: dEx/dy - dEy/dx
   if (PML) {
     if (l[0] >= 0) {  // Hy (dEz/dx), Hz (dEy/dx)
       const Prof3<T> q = pf.template at<0>(P_BH, l[0]);
-      a_hy = pml_step(a_hy, ps[0][0], q.b, q.c, q.k);
-      b_hz = pml_step(b_hz, ps[0][1], q.b, q.c, q.k);
+      a_hy = pml_step(a_hy, p0[0], q.b, q.c, q.k);
+      b_hz = pml_step(b_hz, p0[1], q.b, q.c, q.k);
     }
     if (l[1] >= 0) {  // Hz (dEx/dy), Hx (dEz/dy)
       const Prof3<T> q = pf.template at<1>(P_BH, l[1]);
-      a_hz = pml_step(a_hz, ps[1][0], q.b, q.c, q.k);
-      b_hx = pml_step(b_hx, ps[1][1], q.b, q.c, q.k);
+      a_hz = pml_step(a_hz, p1[0], q.b, q.c, q.k);
+      b_hx = pml_step(b_hx, p1[1], q.b, q.c, q.k);
     }
     if (l[2] >= 0) {  // Hx (dEy/dz), Hy (dEx/dz)
       const Prof3<T> q = pf.template at<2>(P_BH, l[2]);
-      a_hx = pml_step(a_hx, ps[2][0], q.b, q.c, q.k);
-      b_hy = pml_step(b_hy, ps[2][1], q.b, q.c, q.k);
+      a_hx = pml_step(a_hx, p2[0], q.b, q.c, q.k);
+      b_hy = pml_step(b_hy, p2[1], q.b, q.c, q.k);
     }
   }
   hnew[0] = h_new(hold[0], cf[K_DBX], a_hx, b_hx);
@@ -106,29 +104,30 @@ __device__ __forceinline__ void h_core_pf(const PF& pf, const int l[3], const T*
 }
 
 // E^{n+1} of one node from H^{n+1/2} at the node (hx, hy, hz), at x-1 (hy_i,
-// hz_i), y-1 (hx_j, hz_j) and k-1 (hx_k, hy_k), before any source; ps is the
-// node's E-type CPML state, advanced in place.
+// hz_i), y-1 (hx_j, hz_j) and k-1 (hx_k, hy_k), before any source; p0,
+// p1, p2 are the node's E-type CPML pairs, advanced in place.
 template <typename T, bool PML, typename PF>
 __device__ __forceinline__ void e_core_pf(const PF& pf, const int l[3], const T* cf, T hx, T hy, T hz, T hx_j, T hx_k,
-                                          T hy_i, T hy_k, T hz_i, T hz_j, const T eold[3], T ps[3][2], T enew[3]) {
+                                          T hy_i, T hy_k, T hz_i, T hz_j, const T eold[3], T* p0, T* p1, T* p2,
+                                          T enew[3]) {
   T a_ex = hz - hz_j, b_ex = hy - hy_k;  // Ex: dHz/dy - dHy/dz
   T a_ey = hx - hx_k, b_ey = hz - hz_i;  // Ey: dHx/dz - dHz/dx
   T a_ez = hy - hy_i, b_ez = hx - hx_j;  // Ez: dHy/dx - dHx/dy
   if (PML) {
     if (l[0] >= 0) {  // Ey (dHz/dx), Ez (dHy/dx)
       const Prof3<T> q = pf.template at<0>(P_BE, l[0]);
-      b_ey = pml_step(b_ey, ps[0][0], q.b, q.c, q.k);
-      a_ez = pml_step(a_ez, ps[0][1], q.b, q.c, q.k);
+      b_ey = pml_step(b_ey, p0[0], q.b, q.c, q.k);
+      a_ez = pml_step(a_ez, p0[1], q.b, q.c, q.k);
     }
     if (l[1] >= 0) {  // Ez (dHx/dy), Ex (dHz/dy)
       const Prof3<T> q = pf.template at<1>(P_BE, l[1]);
-      b_ez = pml_step(b_ez, ps[1][0], q.b, q.c, q.k);
-      a_ex = pml_step(a_ex, ps[1][1], q.b, q.c, q.k);
+      b_ez = pml_step(b_ez, p1[0], q.b, q.c, q.k);
+      a_ex = pml_step(a_ex, p1[1], q.b, q.c, q.k);
     }
     if (l[2] >= 0) {  // Ex (dHy/dz), Ey (dHx/dz)
       const Prof3<T> q = pf.template at<2>(P_BE, l[2]);
-      b_ex = pml_step(b_ex, ps[2][0], q.b, q.c, q.k);
-      a_ey = pml_step(a_ey, ps[2][1], q.b, q.c, q.k);
+      b_ex = pml_step(b_ex, p2[0], q.b, q.c, q.k);
+      a_ey = pml_step(a_ey, p2[1], q.b, q.c, q.k);
     }
   }
   enew[0] = e_new(eold[0], cf[K_CAX], cf[K_CBX], a_ex, b_ex);
@@ -157,13 +156,15 @@ template <typename T, bool PML>
 __device__ __forceinline__ void h_core(const GridView<T>& g, const int l[3], const T* cf, T ex, T ey, T ez,
                                        T ex_j, T ex_k, T ey_i, T ey_k, T ez_i, T ez_j, const T hold[3],
                                        T ps[3][2], T hnew[3]) {
-  h_core_pf<T, PML>(ProfG<T>{g}, l, cf, ex, ey, ez, ex_j, ex_k, ey_i, ey_k, ez_i, ez_j, hold, ps, hnew);
+  h_core_pf<T, PML>(ProfG<T>{g}, l, cf, ex, ey, ez, ex_j, ex_k, ey_i, ey_k, ez_i, ez_j, hold, ps[0], ps[1], ps[2],
+                    hnew);
 }
 template <typename T, bool PML>
 __device__ __forceinline__ void e_core(const GridView<T>& g, const int l[3], unsigned n, const T* cf, T hx, T hy,
                                        T hz, T hx_j, T hx_k, T hy_i, T hy_k, T hz_i, T hz_j, const T eold[3],
                                        int step, T ps[3][2], T enew[3], int slo, int shi) {
-  e_core_pf<T, PML>(ProfG<T>{g}, l, cf, hx, hy, hz, hx_j, hx_k, hy_i, hy_k, hz_i, hz_j, eold, ps, enew);
+  e_core_pf<T, PML>(ProfG<T>{g}, l, cf, hx, hy, hz, hx_j, hx_k, hy_i, hy_k, hz_i, hz_j, eold, ps[0], ps[1], ps[2],
+                    enew);
   e_sources(&g, slo, shi, n, step, enew);
 }
 

@@ -60,6 +60,30 @@ __device__ __forceinline__ void stg(T* base, unsigned idx, T v) {
   *(GT*)((__attribute__((address_space(1))) char*)base + idx * (unsigned)sizeof(T)) = v;
 }
 
+// The same by a byte offset, and for a pair of values in one access.
+template <typename T>
+__device__ __forceinline__ T ldb(const T* base, unsigned off) {
+  typedef __attribute__((address_space(1))) const T GT;
+  return *(GT*)((const __attribute__((address_space(1))) char*)base + off);
+}
+template <typename T>
+__device__ __forceinline__ void stb(T* base, unsigned off, T v) {
+  typedef __attribute__((address_space(1))) T GT;
+  *(GT*)((__attribute__((address_space(1))) char*)base + off) = v;
+}
+template <typename T>
+__device__ __forceinline__ void ld_pair(const T* base, unsigned off, T v[2]) {
+  typedef T V2 __attribute__((ext_vector_type(2)));
+  const V2 q = ldb((const V2*)base, off);
+  v[0] = q.x;
+  v[1] = q.y;
+}
+template <typename T>
+__device__ __forceinline__ void st_pair(T* base, unsigned off, const T v[2]) {
+  typedef T V2 __attribute__((ext_vector_type(2)));
+  stb((V2*)base, off, V2{v[0], v[1]});
+}
+
 // H update of one node from raw E differences.
 //   Hx += db_x ((Ey[k+1] - Ey) - (Ez[j+1] - Ez))
 //   Hy += db_y ((Ez[i+1] - Ez) - (Ex[k+1] - Ex))
