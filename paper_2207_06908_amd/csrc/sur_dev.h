@@ -12,8 +12,9 @@ enum Epi {
   EPI_DW = 4,          // o32 = acc for columns < n_valid
 };
 
-// C[M x N] = A[M x K] B[N x K]^T (both operands K-contiguous bfloat16),
-// FP32 accumulation on the matrix cores, then the epilogue.  M and N are
+// C[M x N] = A[M x K] B[N x K]^T (bfloat16; A K-contiguous, B a weight copy
+// in fragment order or, for EPI_DW, K-contiguous with pitch ldb), FP32
+// accumulation on the matrix cores, then the epilogue.  M and N are
 // multiples of 16, K a multiple of 32, leading dimensions multiples of 8.
 struct GemmArgs {
   const uint16_t* A;
@@ -34,7 +35,7 @@ struct GemmArgs {
 
 struct AdamLayer {
   int off, n, k, kp;  // flat offset of W (bias follows), shape, padded K
-  long long w16, wt;  // element offsets of the bfloat16 copies W [n x kp], W^T [kp x n]
+  long long w16, wt;  // element offsets of the bfloat16 copies W [n x kp], W^T [kp x n] (fragment order)
 };
 
 struct AdamArgs {
@@ -49,13 +50,11 @@ struct AdamArgs {
 };
 
 // Fused inference (k_mlp_infer): all layers of `nets` consecutive nets over
-// M gathered rows, activations kept on chip; hidden widths <= MLP_KMAX, the
-// output width <= MLP_NOUT (its FP32 rows are staged in the same LDS).  Net q's bfloat16 weight copies start at bf + q bf_stride,
-// its FP32 parameters at p + q p_stride; its outputs go to
-// out[q ld_net + row ldo + col] for rows < m_valid.
-// Block shape of k_mlp_infer: MLP_BM rows, MLP_NW waves, MLP_CF column
-// fragments per wave.
-constexpr int MLP_BM = 128, MLP_NW = 16, MLP_CF = 2;
+// M rows of kin inputs, activations kept on chip; hidden widths <= MLP_KMAX,
+// the output width <= MLP_NOUT (its FP32 rows are staged in the same LDS).
+// Net q's bfloat16 weight copies start at bf + q bf_stride, its FP32
+// parameters at p + q p_stride; its outputs go to out[q ld_net], dense rows
+// (ld_net a multiple of 4).
 constexpr int MLP_KMAX = 512, MLP_LDA = MLP_KMAX + 8, MLP_NOUT = MLP_LDA / 2;
 struct MlpLayer {
   long long w16;   // element offset of W [n x kp] in a net's bfloat16 copies
@@ -63,11 +62,11 @@ struct MlpLayer {
   int kp, n;
 };
 struct MlpArgs {
-  const uint16_t* X16;  // [M x 32]
+  const float* x;  // [M x kin]
   const uint16_t* bf;
   const float* p;
   long long bf_stride, p_stride;
-  int M, L, m_valid, ldo;
+  int M, L, kin;
   float* out;
   long long ld_net;
   MlpLayer lay[8];

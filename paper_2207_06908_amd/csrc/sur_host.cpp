@@ -292,19 +292,18 @@ static bool fused_ok(const sur_ctx* c) {
   return c->L <= 8;
 }
 
-// All layers of nets [net0, net0 + nets) over the M gathered rows of X16, in
-// one launch; outputs to y[q ld_net + row W + col] for rows < m_valid.
-static int forward_fused(sur_ctx* c, int net0, int nets, int M, float* y, long long ld_net, int m_valid) {
+// All layers of nets [net0, net0 + nets) over the m rows at x, in one launch;
+// outputs to y[q ld_net + row W + col].
+static int forward_fused(sur_ctx* c, int net0, int nets, const float* x, int m, float* y, long long ld_net) {
   MlpArgs a{};
-  a.X16 = c->at<uint16_t>(c->o_X16);
+  a.x = x;
+  a.kin = c->w[0];
   a.bf = c->bf(net0);
   a.p = c->p(net0);
   a.bf_stride = (long long)(c->net_stride / 2);
   a.p_stride = (long long)(c->net_stride / 4);
-  a.M = M;
+  a.M = m;
   a.L = c->L;
-  a.m_valid = m_valid;
-  a.ldo = c->w.back();
   a.out = y;
   a.ld_net = ld_net;
   for (int l = 0; l < c->L; ++l) {
@@ -381,12 +380,15 @@ int sur_forward(sur_ctx* c, int net, const float* x_dev, int n, float* y_dev) {
   const int W = c->w.back(), k0 = c->w[0];
   for (int c0 = 0; c0 < n; c0 += c->R) {
     const int m = std::min(c->R, n - c0), M = (m + 63) / 64 * 64;
-    int e = launch_gather(x_dev + (size_t)c0 * k0, nullptr, nullptr, m, M, k0, W, c->at<uint16_t>(c->o_X16),
-                          nullptr, nullptr, c->stream);
+    const float* x = x_dev + (size_t)c0 * k0;
+    float* y = y_dev + (size_t)c0 * W;
+    if (fused_ok(c)) {
+      if ((r = forward_fused(c, net, 1, x, m, y, 0))) return r;
+      continue;
+    }
+    int e = launch_gather(x, nullptr, nullptr, m, M, k0, W, c->at<uint16_t>(c->o_X16), nullptr, nullptr, c->stream);
     if (e) return hip_fail(c, e, "gather");
-    r = fused_ok(c) ? forward_fused(c, net, 1, M, y_dev + (size_t)c0 * W, 0, m)
-                    : forward(c, net, M, false, y_dev + (size_t)c0 * W, W, m);
-    if (r) return r;
+    if ((r = forward(c, net, M, false, y, W, m))) return r;
   }
   return SUR_OK;
 }
@@ -404,16 +406,17 @@ int sur_infer_route(sur_ctx* c, const float* x_dev, int n, float threshold, floa
   int r;
   for (int c0 = 0; c0 < n; c0 += c->R) {
     const int m = std::min(c->R, n - c0), M = (m + 63) / 64 * 64;
-    int e = launch_gather(x_dev + (size_t)c0 * k0, nullptr, nullptr, m, M, k0, W, c->at<uint16_t>(c->o_X16),
-                          nullptr, nullptr, c->stream);
-    if (e) return hip_fail(c, e, "gather");
+    const float* x = x_dev + (size_t)c0 * k0;
+    int e;
     if (fused_ok(c)) {
-      if ((r = forward_fused(c, 0, c->nets, M, ys, (long long)c->R * W, m))) return r;
+      if ((r = forward_fused(c, 0, c->nets, x, m, ys, (long long)c->R * W))) return r;
     } else {
+      e = launch_gather(x, nullptr, nullptr, m, M, k0, W, c->at<uint16_t>(c->o_X16), nullptr, nullptr, c->stream);
+      if (e) return hip_fail(c, e, "gather");
       for (int q = 0; q < c->nets; ++q)
         if ((r = forward(c, q, M, false, ys + (size_t)q * c->R * W, W, m))) return r;
     }
-    if ((e = launch_route(ys, c->nets, c->R * W, m, W, x_dev + (size_t)c0 * k0, k0, c->xbound,
+    if ((e = launch_route(ys, c->nets, c->R * W, m, W, x, k0, c->xbound,
                           y_mean_dev + (size_t)c0 * W, spread_dev + c0, c->stream)))
       return hip_fail(c, e, "route");
   }

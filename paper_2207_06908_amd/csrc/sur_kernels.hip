@@ -9,6 +9,13 @@
 // W^T copies.  So every product reads 16-byte vectors along K and no kernel
 // transposes through LDS.
 //
+// The copies W and W^T are in fragment order (frag_off): the 16 rows x 32 of
+// K that one instruction takes are 1 KB in a row, in lane order, so a wave's
+// load of a fragment is one contiguous KB.  (Row by row, a fragment takes
+// half of each of 16 cache lines, and with 16 waves streaming weights the
+// other halves were gone from the 32 KB L1 when the next step wanted them:
+// twice the traffic from L2.)
+//
 // Fragment layout of the 16x16x32 instruction (64 lanes): lane l supplies
 // A[row l%16][k = 8(l/16) .. 8(l/16)+7] and B^T[col l%16][same k], and holds
 // D[rows 4(l/16) .. 4(l/16)+3][col l%16].
@@ -28,21 +35,27 @@ namespace mi355sur {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-// FP32 -> bfloat16, round to nearest, ties to even (inputs are finite).
-__device__ __forceinline__ uint32_t f2bf(float f) {
-  const uint32_t u = __float_as_uint(f);
-  return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
+// FP32 -> bfloat16, round to nearest, ties to even (one instruction).
+__device__ __forceinline__ uint32_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
 __device__ __forceinline__ bf16x8 ld_frag(const uint16_t* p) {
   const uint4 q = *(const uint4*)p;
   return __builtin_bit_cast(bf16x8, q);
 }
 
-constexpr float kInvSqrt2Pi = 0.39894228040143268f;
+// Element offset of (row, k) in a fragment-ordered operand of K columns.
+__device__ __forceinline__ long long frag_off(int row, int k, int K) {
+  return ((long long)(row >> 4) * (K >> 5) + (k >> 5)) * 512 + ((row & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
+}
 
-// Prefetch distance (K steps) of the weight fragments in k_mlp_infer.
-constexpr int MLP_PD = 3;
+// Two at once, the first value in the low half.
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+__device__ __forceinline__ uint32_t f2bf2(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+
+constexpr float kInvSqrt2Pi = 0.39894228040143268f;
 
 // The standard normal distribution function Phi(z), and exp(-z^2 / 2), for
 // the exact GELU z Phi(z) and its derivative Phi(z) + z phi(z).  Phi comes
@@ -130,8 +143,10 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
   }
   const int r16 = lane & 15, kq = (lane >> 4) * 8;
   const uint16_t* pa = g.A + (size_t)(mw + r16) * g.lda + kq;
-  const uint16_t* pb = g.B + (size_t)(nw + r16) * g.ldb + kq;
-  const size_t sa = (size_t)16 * g.lda, sb = (size_t)16 * g.ldb;
+  // B is a weight copy in fragment order, but for the weight gradient
+  constexpr bool FO = EPI != EPI_DW;
+  const uint16_t* pb = FO ? g.B + (size_t)(nw >> 4) * 16 * g.K + lane * 8 : g.B + (size_t)(nw + r16) * g.ldb + kq;
+  const size_t sa = (size_t)16 * g.lda, sb = (size_t)16 * (FO ? g.K : g.ldb);
   f32x4 c[F][F];
 #pragma unroll
   for (int i = 0; i < F; ++i)
@@ -148,7 +163,7 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
 #pragma unroll
       for (int i = 0; i < F; ++i) {
         fa[s][i] = vm[i] ? ld_frag(pa + i * sa + k0 + 32 * s) : zero;
-        fb[s][i] = vn[i] ? ld_frag(pb + i * sb + k0 + 32 * s) : zero;
+        fb[s][i] = vn[i] ? ld_frag(pb + i * sb + (FO ? 16 : 1) * (k0 + 32 * s)) : zero;
       }
 #pragma unroll
     for (int s = 0; s < U; ++s)
@@ -234,10 +249,13 @@ __global__ __launch_bounds__(256, 3) void k_gemm_lds(GemmArgs g) {
   // this thread's 16-byte pieces of a K tile: rows cr + 32 i, k offset ck
   const int cr = tid >> 3, ck = (tid & 7) * 8;
   const uint16_t* ga = g.A + (size_t)(m0 + cr) * g.lda + ck;
-  const uint16_t* gb = g.B + (size_t)(n0 + cr) * g.ldb + ck;
-  const size_t a32 = (size_t)32 * g.lda, b32 = (size_t)32 * g.ldb;
+  // ... and of B, in fragment order: fragment (w >> 1) + 2 i, half w & 1 of
+  // the K tile, this lane's piece
+  const int br = 16 * (w >> 1) + (lane & 15), bk = 32 * (w & 1) + 8 * (lane >> 4);
+  const uint16_t* gb = g.B + frag_off(n0 + br, bk, g.K);
+  const size_t a32 = (size_t)32 * g.lda, b32 = (size_t)32 * g.K;
   uint16_t* const la = sa + cr * GL_LD + ck;
-  uint16_t* const lb = sb + cr * GL_LD + ck;
+  uint16_t* const lb = sb + br * GL_LD + bk;
   // (named values, not arrays: an array would be kept in scratch memory
   // across the asm statement below)
   uint4 a0, a1, a2, a3, b0, b1, b2, b3;
@@ -246,10 +264,10 @@ __global__ __launch_bounds__(256, 3) void k_gemm_lds(GemmArgs g) {
   a1 = *(const uint4*)(ga + a32 + (k0));         \
   a2 = *(const uint4*)(ga + 2 * a32 + (k0));     \
   a3 = *(const uint4*)(ga + 3 * a32 + (k0));     \
-  b0 = *(const uint4*)(gb + (k0));               \
-  b1 = *(const uint4*)(gb + b32 + (k0));         \
-  b2 = *(const uint4*)(gb + 2 * b32 + (k0));     \
-  b3 = *(const uint4*)(gb + 3 * b32 + (k0));
+  b0 = *(const uint4*)(gb + 16 * (k0));               \
+  b1 = *(const uint4*)(gb + b32 + 16 * (k0));         \
+  b2 = *(const uint4*)(gb + 2 * b32 + 16 * (k0));     \
+  b3 = *(const uint4*)(gb + 3 * b32 + 16 * (k0));
 #define GL_STASH()                               \
   *(uint4*)(la) = a0;                            \
   *(uint4*)(la + 32 * GL_LD) = a1;               \
@@ -314,57 +332,63 @@ __global__ __launch_bounds__(256, 3) void k_gemm_lds(GemmArgs g) {
 // Fused inference: every layer of one net over BM rows in one block.  The
 // block's activations stay in LDS from layer to layer (bfloat16, rows padded
 // by 16 bytes so that the 16 rows of a fragment fall in different banks);
-// only the gathered inputs, the weights (a few MB per net, L2-resident) and
-// the last layer's FP32 outputs touch memory.  (Layer by layer, a 64K-row
-// activation block with 512 x 512 weights moves 128 MB through HBM per
-// layer; here it moves none.)  NW waves; the waves split the block's rows
-// into NW / (32 / CF) groups and the 32 column fragments of a 512-wide layer
-// (16 columns each) into 32 / CF groups: wave w owns the row fragments of
-// group w / (32 / CF) and the column fragments c, c + 32 / CF, ... (CF of
-// them, c = w % (32 / CF)).  Each activation fragment a wave reads from LDS
-// serves CF products, each weight fragment it reads from L2 serves RF.  The
-// weight fragments run MLP_PD K steps ahead of the products, the bias of the
-// layer is loaded before them.  The K loop has no branches: rows past M hold
-// zero inputs, a column fragment past the layer's width multiplies fragment
-// 0's weights, and neither result is ever stored.  Each accumulator takes its
-// K steps in order with the instruction k_gemm uses, and the epilogue is
-// k_gemm's, so the outputs equal the layer-by-layer products bit for bit.
-// (At most 64 accumulator registers a lane: 4 waves per SIMD, else 2.)
-template <int BM, int NW, int CF>
-__global__ __launch_bounds__(64 * NW, (BM / 16) * 32 / NW * 4 <= 64 ? 4 : 2) void k_mlp_infer(MlpArgs a) {
+// only the inputs, the weights (a few MB per net, L2-resident) and the last
+// layer's FP32 outputs touch memory.  (Layer by layer, a 64K-row activation
+// block with 512 x 512 weights moves 128 MB through HBM per layer; here it
+// moves none.)  NW waves; the waves split the block's rows into NW / (32 / CF)
+// groups and the 32 column fragments of a 512-wide layer (16 columns each)
+// into 32 / CF groups: wave w owns the row fragments of group w / (32 / CF)
+// and the column fragments c, c + 32 / CF, ... (CF of them, c = w % (32 / CF)).
+// Each activation fragment a wave reads from LDS serves CF products, each
+// weight fragment it reads from L2 serves RF.  The weight fragments run PD K
+// steps ahead of the products.
+// The K loop has no branches: rows past the last hold zero inputs, a column
+// fragment past the layer's width multiplies fragment 0's weights, and neither
+// result is ever stored.  Each accumulator takes its K steps in order with the
+// instruction k_gemm uses, and the epilogue is k_gemm's, so the outputs equal
+// the layer-by-layer products bit for bit.
+// (4 waves per SIMD: 128 registers a lane.)
+template <int BM, int NW, int CF, int PD>
+__global__ __launch_bounds__(64 * NW, 4) void k_mlp_infer(MlpArgs a) {
   constexpr int NT = 64 * NW, NWC = 32 / CF, NWR = NW / NWC, RF = BM / 16 / NWR;
   static_assert(NWC * CF == 32 && NWR * NWC == NW && RF * NWR * 16 == BM, "block shape");
   __shared__ __attribute__((aligned(16))) uint16_t act[BM * MLP_LDA];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cg = w % NWC, r0 = (w / NWC) * RF;  // column group, first row fragment
   const int net = blockIdx.y, m0 = blockIdx.x * BM;
   const uint16_t* bfn = a.bf + (size_t)net * a.bf_stride;
   const float* pn = a.p + (size_t)net * a.p_stride;
-  for (int e = tid; e < BM * 4; e += NT) {  // inputs: 32 bfloat16 per row, as four 16-byte pieces
-    const int r = e >> 2, q = e & 3;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (m0 + r < a.M) v = *(const uint4*)(a.X16 + (size_t)(m0 + r) * 32 + q * 8);
-    *(uint4*)(act + r * MLP_LDA + q * 8) = v;
+  for (int e = tid; e < BM * 16; e += NT) {  // inputs: 32 columns, two at a time
+    const int r = e >> 4, q = (e & 15) * 2;
+    const float* xr = a.x + (size_t)(m0 + r) * a.kin;
+    const bool in = m0 + r < a.M;
+    const float v0 = in && q < a.kin ? xr[q] : 0.0f, v1 = in && q + 1 < a.kin ? xr[q + 1] : 0.0f;
+    *(uint32_t*)(act + r * MLP_LDA + q) = f2bf2(v0, v1);
   }
   __syncthreads();
   const int r16 = lane & 15, kq = (lane >> 4) * 8, rq = (lane >> 4) * 4;
   const uint16_t* pa = act + (16 * r0 + r16) * MLP_LDA + kq;
+  const unsigned lo = 16u * lane;  // this lane's piece of a weight fragment
 #pragma unroll 1
   for (int l = 0; l < a.L; ++l) {
     const MlpLayer ly = a.lay[l];
     const int nf = ly.n >> 4;
-    // a fragment past the width reads fragment 0's rows and bias (its
-    // products are never stored)
-    bool vn[CF];
+    // a fragment past the width reads fragment 0's rows (its products are
+    // never stored); uniform pointers, advanced a K step at each load
     const uint16_t* pb[CF];
-    float bn[CF];
 #pragma unroll
     for (int j = 0; j < CF; ++j) {
-      vn[j] = cg + NWC * j < nf;
-      const int f = vn[j] ? cg + NWC * j : 0;
-      pb[j] = bfn + ly.w16 + (size_t)(f * 16 + r16) * ly.kp + kq;
-      bn[j] = pn[ly.bias + f * 16 + r16];
+      const int f = cg + NWC * j < nf ? cg + NWC * j : 0;
+      pb[j] = bfn + ly.w16 + (size_t)f * 16 * ly.kp;
     }
+    auto ld_w = [&](bf16x8* b) {
+#pragma unroll
+      for (int j = 0; j < CF; ++j) {
+        asm volatile("" : "+s"(pb[j]));
+        b[j] = ld_frag((const uint16_t*)((const char*)pb[j] + lo));
+        pb[j] += 512;
+      }
+    };
     f32x4 c[RF][CF];
 #pragma unroll
     for (int i = 0; i < RF; ++i)
@@ -387,21 +411,17 @@ __global__ __launch_bounds__(64 * NW, (BM / 16) * 32 / NW * 4 <= 64 ? 4 : 2) voi
     // step would wait for its own loads.
     if (ly.kp == MLP_KMAX) {
       // the 16 steps of a 512-wide layer unrolled: step s reads the register
-      // set s % MLP_PD, so the prefetched values are never copied (a copy
-      // would wait for the load)
+      // set s % PD, so the prefetched values are never copied (a copy would
+      // wait for the load)
       constexpr int NS = MLP_KMAX / 32;
-      bf16x8 b[MLP_PD][CF];
+      bf16x8 b[PD][CF];
 #pragma unroll
-      for (int q = 0; q < MLP_PD; ++q)
-#pragma unroll
-        for (int j = 0; j < CF; ++j) b[q][j] = ld_frag(pb[j] + 32 * q);
+      for (int q = 0; q < PD; ++q) ld_w(b[q]);
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         asm volatile("" ::: "memory");
-        kstep(32 * s, b[s % MLP_PD]);
-        if (s + MLP_PD < NS)
-#pragma unroll
-          for (int j = 0; j < CF; ++j) b[s % MLP_PD][j] = ld_frag(pb[j] + 32 * (s + MLP_PD));
+        kstep(32 * s, b[s % PD]);
+        if (s + PD < NS) ld_w(b[s % PD]);
       }
     } else {
       // other widths (the first layer, small nets): one step at a time
@@ -409,33 +429,36 @@ __global__ __launch_bounds__(64 * NW, (BM / 16) * 32 / NW * 4 <= 64 ? 4 : 2) voi
       for (int k0 = 0; k0 < ly.kp; k0 += 32) {
         asm volatile("" ::: "memory");
         bf16x8 b[CF];
-#pragma unroll
-        for (int j = 0; j < CF; ++j) b[j] = ld_frag(pb[j] + k0);
+        ld_w(b);
         kstep(k0, b);
       }
     }
+    float bn[CF];
+#pragma unroll
+    for (int j = 0; j < CF; ++j) bn[j] = pn[ly.bias + (cg + NWC * j < nf ? cg + NWC * j : 0) * 16 + r16];
     __syncthreads();  // every wave has read this layer's input
     if (l + 1 < a.L) {  // hidden layer: bias, exact GELU, bfloat16 into LDS
 #pragma unroll
       for (int j = 0; j < CF; ++j) {
-        if (!vn[j]) continue;
-        const int n = (cg + NWC * j) * 16 + r16;
+        if (cg + NWC * j >= nf) continue;
+        uint16_t* const col = act + (16 * r0 + rq) * MLP_LDA + (cg + NWC * j) * 16 + r16;
 #pragma unroll
         for (int i = 0; i < RF; ++i) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float z = c[i][j][r] + bn[j];
+          for (int r = 0; r < 4; r += 2) {
             float gz;
-            const float ph = norm_cdf(z, gz);
-            act[(16 * (r0 + i) + rq + r) * MLP_LDA + n] = (uint16_t)f2bf(z * ph);
+            const float z0 = c[i][j][r] + bn[j], z1 = c[i][j][r + 1] + bn[j];
+            const uint32_t q = f2bf2(z0 * norm_cdf(z0, gz), z1 * norm_cdf(z1, gz));
+            col[(16 * i + r) * MLP_LDA] = (uint16_t)q;
+            col[(16 * i + r + 1) * MLP_LDA] = (uint16_t)(q >> 16);
           }
         }
       }
-    } else {  // output layer: bias, FP32 staged in LDS, then rows < m_valid out as whole rows
+    } else {  // output layer: bias, FP32 staged in LDS, then rows < M out as whole rows
       float* of = (float*)act;
 #pragma unroll
       for (int j = 0; j < CF; ++j) {
-        if (!vn[j]) continue;
+        if (cg + NWC * j >= nf) continue;
         const int n = (cg + NWC * j) * 16 + r16;
 #pragma unroll
         for (int i = 0; i < RF; ++i)
@@ -443,10 +466,13 @@ __global__ __launch_bounds__(64 * NW, (BM / 16) * 32 / NW * 4 <= 64 ? 4 : 2) voi
           for (int r = 0; r < 4; ++r) of[(16 * (r0 + i) + rq + r) * ly.n + n] = c[i][j][r] + bn[j];
       }
       __syncthreads();
-      const int rows = min(BM, a.m_valid - m0);
-      for (int e = tid; e < rows * ly.n; e += NT) {
-        const int m = e / ly.n, n = e - m * ly.n;
-        a.out[(size_t)net * a.ld_net + (size_t)(m0 + m) * a.ldo + n] = of[e];
+      // the block's rows are contiguous (of is dense, as the output is)
+      const int cnt = min(BM, a.M - m0) * (ly.n >> 2);
+      float4* out = (float4*)(a.out + (size_t)net * a.ld_net + (size_t)m0 * ly.n);
+      if (((uintptr_t)a.out & 15) == 0) {
+        for (int e = tid; e < cnt; e += NT) out[e] = ((const float4*)of)[e];
+      } else {
+        for (int e = tid; e < 4 * cnt; e += NT) ((float*)out)[e] = of[e];
       }
     }
     __syncthreads();  // the next layer reads what this one wrote
@@ -542,7 +568,8 @@ __global__ __launch_bounds__(256) void k_colsum(const float* __restrict__ dz, in
 }
 
 // Adam on the flat FP32 parameters of one net (update != 0), then refresh of
-// the bfloat16 copies W [n x kp] and W^T [kp x n] used by the products.
+// the bfloat16 copies W [n x kp] and W^T [kp x n] used by the products, in
+// fragment order.
 __global__ __launch_bounds__(256) void k_adam(AdamArgs a) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= a.P) return;
@@ -563,8 +590,8 @@ __global__ __launch_bounds__(256) void k_adam(AdamArgs a) {
   if (i < L.n * L.k) {
     const int row = i / L.k, col = i - row * L.k;
     const uint16_t b = (uint16_t)f2bf(p);
-    a.bf[L.w16 + (long long)row * L.kp + col] = b;
-    a.bf[L.wt + (long long)col * L.n + row] = b;
+    a.bf[L.w16 + frag_off(row, col, L.kp)] = b;
+    a.bf[L.wt + frag_off(col, row, L.n)] = b;
   }
 }
 
@@ -805,9 +832,29 @@ int launch_gemm(int epi, const GemmArgs& a, void* stream) {
   return last();
 }
 
+// Block shape by the number of blocks it makes.  While 16-row blocks do not
+// outnumber the CUs, each takes one (23 us for 4 x 512 + 256 wide layers, most
+// of it the 2 MB of weights through one L1; 32 rows take 28, 128 rows 70 us).
+// Then 32-row blocks, two to a CU, up to one round of them (31 us for 8192
+// rows; 16 rows 51, 64 rows 44).  Past that 64-row blocks, two to a CU: one
+// block's GELU runs while the other's products do, which one 128-row block
+// per CU cannot (65536 rows, us: 148; 32 rows 181, 128 rows 157; with row
+// order weights and integer rounding 128 rows took 215).
+template <int BM, int NW, int CF, int PD>
+static void mlp_infer(const MlpArgs& a, int nets, hipStream_t s) {
+  k_mlp_infer<BM, NW, CF, PD><<<dim3((a.M + BM - 1) / BM, nets), 64 * NW, 0, s>>>(a);
+}
+
 int launch_mlp_infer(const MlpArgs& a, int nets, void* stream) {
   if (a.M <= 0) return 0;
-  k_mlp_infer<MLP_BM, MLP_NW, MLP_CF><<<dim3((a.M + MLP_BM - 1) / MLP_BM, nets), 64 * MLP_NW, 0, (hipStream_t)stream>>>(a);
+  const hipStream_t s = (hipStream_t)stream;
+  const long long n16 = (long long)((a.M + 15) / 16) * nets, n32 = (long long)((a.M + 31) / 32) * nets;
+  if (n16 <= 256)
+    mlp_infer<16, 16, 2, 6>(a, nets, s);
+  else if (n32 <= 512)
+    mlp_infer<32, 8, 4, 3>(a, nets, s);
+  else
+    mlp_infer<64, 8, 4, 2>(a, nets, s);
   return last();
 }
 
