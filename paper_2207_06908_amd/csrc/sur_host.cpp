@@ -4,8 +4,9 @@
 // Adam, activation and gradient buffers, and sequences the kernels of
 // sur_kernels.hip: forward (one product per layer with the bias/GELU
 // epilogue; inference of every net in one fused launch where the widths
-// allow), loss, backward (weight-gradient product, bias column sums and the
-// input-gradient product with the GELU-derivative epilogue), Adam.
+// allow), loss, backward (input-gradient product with the GELU-derivative
+// epilogue; one launch with the forward pass where the widths and the batch
+// allow), then weight and bias gradients with Adam in one launch.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -45,9 +46,9 @@ struct sur_ctx {
   char* ws = nullptr;
   size_t ws_bytes = 0, need = 0;
   size_t o_net = 0, net_stride = 0, o_bf = 0;  // o_bf: offset of the copies inside a net block
-  size_t o_X16 = 0, o_XT = 0, o_T = 0, o_y = 0, o_part = 0, o_ys = 0;
+  size_t o_X16 = 0, o_XT = 0, o_y = 0, o_part = 0, o_ys = 0;
   size_t o_a16[kMaxLayers] = {}, o_aT[kMaxLayers] = {}, o_gz[kMaxLayers] = {};
-  size_t o_g16[2] = {}, o_gT[2] = {}, o_dz[2] = {};
+  size_t o_g16[2] = {}, o_gT = 0, o_dz = 0;
   std::vector<long long> adam_t;
   std::vector<char> ready;
   float xbound = INFINITY;   // routing bound on the inputs (sur_set_input_bound)
@@ -112,7 +113,6 @@ int sur_create(const int* widths, int n_widths, int n_nets, int max_rows, void* 
   c->o_net = take(c->net_stride * c->nets);
   c->o_X16 = take(R * 32 * 2);
   c->o_XT = take(R * 32 * 2);
-  c->o_T = take(R * W * 4);
   for (int l = 0; l + 1 < c->L; ++l) {
     const size_t n = c->lay[l].n;
     c->o_a16[l] = take(R * n * 2);
@@ -120,11 +120,9 @@ int sur_create(const int* widths, int n_widths, int n_nets, int max_rows, void* 
     c->o_gz[l] = take(R * n * 4);
   }
   c->o_y = take(R * W * 4);
-  for (int q = 0; q < 2; ++q) {
-    c->o_g16[q] = take(R * c->wmax * 2);
-    c->o_gT[q] = take(R * c->wmax * 2);
-    c->o_dz[q] = take(R * c->wmax * 4);
-  }
+  for (int q = 0; q < 2; ++q) c->o_g16[q] = take(R * c->wmax * 2);
+  c->o_gT = take(R * W * 2);
+  c->o_dz = take(R * W * 4);
   c->o_part = take((size_t)loss_parts(c->R, (int)W) * 4);
   c->o_ys = take((size_t)c->nets * R * W * 4);
   c->need = o;
@@ -148,30 +146,6 @@ int sur_bind_workspace(sur_ctx* c, void* dev, size_t bytes) {
 
 long long sur_num_params(const sur_ctx* c) { return c ? c->P : 0; }
 
-static AdamArgs adam_args(const sur_ctx* c, int net, int update, float lr) {
-  AdamArgs a{};
-  a.p = c->p(net);
-  a.m = c->m(net);
-  a.v = c->v(net);
-  a.g = c->g(net);
-  a.bf = c->bf(net);
-  a.P = (int)c->P;
-  a.nl = c->L;
-  a.update = update;
-  a.lr = lr;
-  a.b1 = 0.9f;
-  a.b2 = 0.999f;
-  a.eps = 1e-8f;
-  const long long t = c->adam_t[net];
-  a.c1 = (float)(1.0 - std::pow(0.9, (double)t));
-  a.c2 = (float)(1.0 - std::pow(0.999, (double)t));
-  for (int l = 0; l < c->L; ++l) {
-    const Layer& y = c->lay[l];
-    a.L[l] = AdamLayer{(int)y.off_w, y.n, y.k, y.kp, y.w16, y.wt};
-  }
-  return a;
-}
-
 static int check_net(sur_ctx* c, int net, bool need_ready) {
   if (!c) return SUR_EINVAL;
   if (net < 0 || net >= c->nets) return fail(c, SUR_EINVAL, "net index out of range");
@@ -187,7 +161,16 @@ static int upload_params(sur_ctx* c, int net, const float* host) {
   if (e == hipSuccess) e = hipMemsetAsync(c->m(net), 0, (size_t)c->P * 4 * 3, c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->bf(net), 0, (size_t)c->nbf * 2, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "parameter upload");
-  int r = launch_adam(adam_args(c, net, 0, 0.0f), c->stream);
+  CopyArgs a{};
+  a.p = c->p(net);
+  a.bf = c->bf(net);
+  a.P = (int)c->P;
+  a.nl = c->L;
+  for (int l = 0; l < c->L; ++l) {
+    const Layer& y = c->lay[l];
+    a.L[l] = CopyLayer{(int)y.off_w, y.n, y.k, y.kp, y.w16, y.wt};
+  }
+  const int r = launch_copies(a, c->stream);
   if (r) return hip_fail(c, r, "copy refresh");
   e = hipStreamSynchronize(c->stream);  // the host buffer may go away after return
   if (e != hipSuccess) return hip_fail(c, e, "parameter upload");
@@ -254,7 +237,6 @@ static int forward(sur_ctx* c, int net, int M, bool train, float* y, int ldy, in
     a.A = in;
     a.lda = ly.kp;
     a.B = bfb + ly.w16;
-    a.ldb = ly.kp;
     a.M = M;
     a.N = ly.n;
     a.K = ly.kp;
@@ -265,9 +247,7 @@ static int forward(sur_ctx* c, int net, int M, bool train, float* y, int ldy, in
       a.o16 = c->at<uint16_t>(c->o_a16[l]);
       a.ld16 = ly.n;
       a.oT = c->at<uint16_t>(c->o_aT[l]);
-      a.ldT = M;
       a.o32 = c->at<float>(c->o_gz[l]);
-      a.ld32 = ly.n;
       in = a.o16;
     } else {
       epi = EPI_LINEAR;
@@ -314,62 +294,102 @@ static int forward_fused(sur_ctx* c, int net0, int nets, const float* x, int m, 
   return e ? hip_fail(c, e, "fused inference") : SUR_OK;
 }
 
+// dZ of layer l: transposed (over the layer's row-major activations, which
+// only the forward product of the next layer reads) and FP32 (over its GELU
+// derivatives).
+static uint16_t* grad_t(const sur_ctx* c, int l) { return c->at<uint16_t>(l + 1 < c->L ? c->o_a16[l] : c->o_gT); }
+static float* grad_32(const sur_ctx* c, int l) { return c->at<float>(l + 1 < c->L ? c->o_gz[l] : c->o_dz); }
+
+// Whether one launch takes the step up to dZ of every layer: widths that fit
+// its LDS buffers, and at most MLP_TROWS rows.
+static bool fused_train_ok(const sur_ctx* c, int M) {
+  return fused_ok(c) && c->w.back() <= MLP_TOUT && M <= MLP_TROWS;
+}
+
 int sur_train_step(sur_ctx* c, int net, const float* x_dev, const float* t_dev, const int* rows_dev, int batch,
                    float lr, int update, float* loss_dev) {
   int r = check_net(c, net, true);
   if (r) return r;
   if (!x_dev || !t_dev || batch < 1 || batch > c->R) return fail(c, SUR_EINVAL, "bad batch");
   if (!(lr >= 0.0f) || !std::isfinite(lr)) return fail(c, SUR_EINVAL, "bad learning rate");
-  const int M = (batch + 63) / 64 * 64, W = c->w.back();
-  int e = launch_gather(x_dev, t_dev, rows_dev, batch, M, c->w[0], W, c->at<uint16_t>(c->o_X16),
-                        c->at<uint16_t>(c->o_XT), c->at<float>(c->o_T), c->stream);
-  if (e) return hip_fail(c, e, "gather");
-  if ((r = forward(c, net, M, true, c->at<float>(c->o_y), W, M))) return r;
-  e = launch_loss(c->at<float>(c->o_y), c->at<float>(c->o_T), M, batch, W, c->at<uint16_t>(c->o_g16[0]),
-                  c->at<uint16_t>(c->o_gT[0]), c->at<float>(c->o_dz[0]), c->at<float>(c->o_part), loss_dev,
-                  c->stream);
-  if (e) return hip_fail(c, e, "loss");
-  int cur = 0;
-  for (int l = c->L - 1; l >= 0; --l) {
-    const Layer& ly = c->lay[l];
-    GemmArgs a{};  // dW_l = dZ_l^T A_{l-1}
-    a.A = c->at<uint16_t>(c->o_gT[cur]);
-    a.lda = M;
-    a.B = l == 0 ? c->at<uint16_t>(c->o_XT) : c->at<uint16_t>(c->o_aT[l - 1]);
-    a.ldb = M;
-    a.M = ly.n;
-    a.N = ly.kp;
-    a.K = M;
-    a.o32 = c->g(net) + ly.off_w;
-    a.ld32 = ly.k;
-    a.n_valid = ly.k;
-    if ((e = launch_gemm(EPI_DW, a, c->stream))) return hip_fail(c, e, "weight gradient");
-    if ((e = launch_colsum(c->at<float>(c->o_dz[cur]), M, ly.n, c->g(net) + ly.off_b, c->stream)))
-      return hip_fail(c, e, "bias gradient");
-    if (l == 0) break;
-    GemmArgs b{};  // dZ_{l-1} = (dZ_l W_l) * gelu'(Z_{l-1})
-    b.A = c->at<uint16_t>(c->o_g16[cur]);
-    b.lda = ly.n;
-    b.B = c->bf(net) + ly.wt;
-    b.ldb = ly.n;
-    b.M = M;
-    b.N = ly.kp;
-    b.K = ly.n;
-    b.aux = c->at<float>(c->o_gz[l - 1]);
-    b.ldaux = ly.kp;
-    b.o16 = c->at<uint16_t>(c->o_g16[1 - cur]);
-    b.ld16 = ly.kp;
-    b.oT = c->at<uint16_t>(c->o_gT[1 - cur]);
-    b.ldT = M;
-    b.o32 = c->at<float>(c->o_dz[1 - cur]);
-    b.ld32 = ly.kp;
-    if ((e = launch_gemm(EPI_BWD, b, c->stream))) return hip_fail(c, e, "input gradient");
-    cur ^= 1;
+  const int M = (batch + 63) / 64 * 64, W = c->w.back(), L = c->L;
+  const double denom = (double)batch * W;
+  const float scale = (float)(2.0 / denom);
+  uint16_t* const XT = c->at<uint16_t>(c->o_XT);
+  float* const part = c->at<float>(c->o_part);
+  int e;
+  if (fused_train_ok(c, M)) {
+    TrainArgs a{};
+    a.x = x_dev;
+    a.t = t_dev;
+    a.rows = rows_dev;
+    a.bf = c->bf(net);
+    a.p = c->p(net);
+    a.M = M;
+    a.m_valid = batch;
+    a.kin = c->w[0];
+    a.L = L;
+    a.scale = scale;
+    a.XT = XT;
+    a.part = part;
+    for (int l = 0; l < L; ++l) {
+      const Layer& y = c->lay[l];
+      a.lay[l] = TrainLayer{y.w16, y.wt, (int)y.off_b, y.kp, y.n, l + 1 < L ? c->at<uint16_t>(c->o_aT[l]) : nullptr,
+                            grad_t(c, l), grad_32(c, l)};
+    }
+    if ((e = launch_mlp_train(a, c->stream))) return hip_fail(c, e, "forward and backward");
+  } else {
+    e = launch_gather(x_dev, rows_dev, batch, M, c->w[0], c->at<uint16_t>(c->o_X16), XT, c->stream);
+    if (e) return hip_fail(c, e, "gather");
+    if ((r = forward(c, net, M, true, c->at<float>(c->o_y), W, M))) return r;
+    int cur = 0;
+    e = launch_loss(c->at<float>(c->o_y), t_dev, rows_dev, M, batch, W, scale, c->at<uint16_t>(c->o_g16[cur]),
+                    grad_t(c, L - 1), grad_32(c, L - 1), part, c->stream);
+    if (e) return hip_fail(c, e, "loss");
+    for (int l = L - 1; l > 0; --l) {  // dZ_{l-1} = (dZ_l W_l) * gelu'(Z_{l-1})
+      const Layer& ly = c->lay[l];
+      GemmArgs b{};
+      b.A = c->at<uint16_t>(c->o_g16[cur]);
+      b.lda = ly.n;
+      b.B = c->bf(net) + ly.wt;
+      b.M = M;
+      b.N = ly.kp;
+      b.K = ly.n;
+      b.o16 = c->at<uint16_t>(c->o_g16[1 - cur]);
+      b.ld16 = ly.kp;
+      b.oT = grad_t(c, l - 1);
+      b.o32 = grad_32(c, l - 1);
+      if ((e = launch_gemm(EPI_BWD, b, c->stream))) return hip_fail(c, e, "input gradient");
+      cur ^= 1;
+    }
   }
-  if (update) {
-    c->adam_t[net] += 1;
-    if ((e = launch_adam(adam_args(c, net, 1, lr), c->stream))) return hip_fail(c, e, "adam");
+  if (update) c->adam_t[net] += 1;
+  DwArgs d{};
+  d.p = c->p(net);
+  d.m = c->m(net);
+  d.v = c->v(net);
+  d.g = c->g(net);
+  d.bf = c->bf(net);
+  d.M = M;
+  d.nl = L;
+  d.update = update ? 1 : 0;
+  d.lr = lr;
+  d.b1 = 0.9f;
+  d.b2 = 0.999f;
+  d.eps = 1e-8f;
+  const double t = (double)c->adam_t[net];
+  d.c1 = (float)(1.0 - std::pow(0.9, t));
+  d.c2 = (float)(1.0 - std::pow(0.999, t));
+  d.part = part;
+  d.n_part = loss_parts(M, W);
+  d.inv = (float)(1.0 / denom);
+  d.loss = loss_dev;
+  for (int l = 0; l < L; ++l) {
+    const Layer& y = c->lay[l];
+    d.L[l] = DwLayer{l ? c->at<uint16_t>(c->o_aT[l - 1]) : XT, grad_t(c, l), grad_32(c, l), (int)y.off_w, y.n, y.k,
+                     y.kp, y.w16, y.wt, 0, 0};
   }
+  if ((e = launch_dw_adam(d, c->stream))) return hip_fail(c, e, "weight gradients");
   return SUR_OK;
 }
 
@@ -386,7 +406,7 @@ int sur_forward(sur_ctx* c, int net, const float* x_dev, int n, float* y_dev) {
       if ((r = forward_fused(c, net, 1, x, m, y, 0))) return r;
       continue;
     }
-    int e = launch_gather(x, nullptr, nullptr, m, M, k0, W, c->at<uint16_t>(c->o_X16), nullptr, nullptr, c->stream);
+    int e = launch_gather(x, nullptr, m, M, k0, c->at<uint16_t>(c->o_X16), nullptr, c->stream);
     if (e) return hip_fail(c, e, "gather");
     if ((r = forward(c, net, M, false, y, W, m))) return r;
   }
@@ -411,7 +431,7 @@ int sur_infer_route(sur_ctx* c, const float* x_dev, int n, float threshold, floa
     if (fused_ok(c)) {
       if ((r = forward_fused(c, 0, c->nets, x, m, ys, (long long)c->R * W))) return r;
     } else {
-      e = launch_gather(x, nullptr, nullptr, m, M, k0, W, c->at<uint16_t>(c->o_X16), nullptr, nullptr, c->stream);
+      e = launch_gather(x, nullptr, m, M, k0, c->at<uint16_t>(c->o_X16), nullptr, c->stream);
       if (e) return hip_fail(c, e, "gather");
       for (int q = 0; q < c->nets; ++q)
         if ((r = forward(c, q, M, false, ys + (size_t)q * c->R * W, W, m))) return r;

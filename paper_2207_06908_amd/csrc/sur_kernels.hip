@@ -1,20 +1,21 @@
 // sur_kernels.hip -- kernels of the surrogate network on gfx950.
 //
-// Products are C = A B^T with both operands bfloat16 and K-contiguous, on
-// the CDNA4 matrix cores (v_mfma_f32_16x16x32_bf16, FP32 accumulation).  The
-// producers of every operand write it in the layout its consumer wants: the
-// forward epilogue writes each activation both row-major (input of the next
-// layer) and transposed (input of the weight-gradient product), the backward
-// epilogue does the same for the output-side gradient, and Adam keeps W and
-// W^T copies.  So every product reads 16-byte vectors along K and no kernel
-// transposes through LDS.
+// Products are C = A B^T with both operands bfloat16, on the CDNA4 matrix
+// cores (v_mfma_f32_16x16x32_bf16, FP32 accumulation).  The producers of every
+// operand write it in the layout its consumer wants: the forward epilogue
+// writes each activation transposed (input of the weight-gradient product),
+// the backward epilogue does the same for the output-side gradient, and Adam
+// keeps W and W^T copies.  So every product reads 16-byte vectors along K and
+// no kernel transposes through LDS.
 //
-// The copies W and W^T are in fragment order (frag_off): the 16 rows x 32 of
-// K that one instruction takes are 1 KB in a row, in lane order, so a wave's
-// load of a fragment is one contiguous KB.  (Row by row, a fragment takes
+// The copies and the transposes are in fragment order (frag_off): the 16 rows
+// x 32 of K that one instruction takes are 1 KB in a row, in lane order, so a
+// wave's load of a fragment is one contiguous KB.  (Row by row, a fragment takes
 // half of each of 16 cache lines, and with 16 waves streaming weights the
 // other halves were gone from the 32 KB L1 when the next step wanted them:
-// twice the traffic from L2.)
+// twice the traffic from L2.)  The K steps of a row fragment lie next to each
+// other: with the rows of a step next to each other instead, the fused
+// inference of 65,536 rows takes 181 us, not 148.
 //
 // Fragment layout of the 16x16x32 instruction (64 lanes): lane l supplies
 // A[row l%16][k = 8(l/16) .. 8(l/16)+7] and B^T[col l%16][same k], and holds
@@ -34,6 +35,7 @@ namespace mi355sur {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
 // FP32 -> bfloat16, round to nearest, ties to even (one instruction).
 __device__ __forceinline__ uint32_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
@@ -41,6 +43,21 @@ __device__ __forceinline__ uint32_t f2bf(float f) { return __builtin_bit_cast(ui
 __device__ __forceinline__ bf16x8 ld_frag(const uint16_t* p) {
   const uint4 q = *(const uint4*)p;
   return __builtin_bit_cast(bf16x8, q);
+}
+
+// A lane's piece, at byte offset lo, of what lies at a uniform address.  The
+// address stays in scalar registers and the offset in one vector register
+// (the asm statements keep the compiler from adding them up outside a loop).
+typedef __attribute__((address_space(1))) char* gptr;
+template <typename T>
+__device__ __forceinline__ T ld_uni(gptr p, unsigned lo) {
+  asm volatile("" : "+s"(p), "+v"(lo));
+  return *(const __attribute__((address_space(1))) T*)(p + lo);
+}
+template <typename T>
+__device__ __forceinline__ void st_uni(gptr p, unsigned lo, T v) {
+  asm volatile("" : "+s"(p), "+v"(lo));
+  *(__attribute__((address_space(1))) T*)(p + lo) = v;
 }
 
 // Element offset of (row, k) in a fragment-ordered operand of K columns.
@@ -53,6 +70,13 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 __device__ __forceinline__ uint32_t f2bf2(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+
+// Offset of the four values (m .. m + 3, n) that a lane holds of a result
+// fragment, in an FP32 block of N columns kept in fragment order: 16 x 16
+// patches, a lane's four values side by side (m a multiple of 4).
+__device__ __forceinline__ long long acc_off(int m, int n, int N) {
+  return ((long long)(m >> 4) * (N >> 4) + (n >> 4)) * 256 + (((m & 15) >> 2) * 16 + (n & 15)) * 4;
 }
 
 constexpr float kInvSqrt2Pi = 0.39894228040143268f;
@@ -94,7 +118,10 @@ __device__ __forceinline__ void gemm_store(const GemmArgs& g, const f32x4 (&c)[F
     for (int j = 0; j < FN; ++j) {
       if (!vn[j]) continue;
       const int m0 = mw + 16 * i + rq, n = nw + 16 * j + r16;
+      constexpr bool T = EPI == EPI_GELU_TRAIN || EPI == EPI_BWD;
       uint32_t t16[4];
+      f32x4 f32;
+      if (EPI == EPI_BWD) f32 = *(const f32x4*)(g.o32 + acc_off(m0, n, g.N));
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int m = m0 + r;
@@ -104,21 +131,19 @@ __device__ __forceinline__ void gemm_store(const GemmArgs& g, const f32x4 (&c)[F
           float gz;
           const float ph = norm_cdf(z, gz);
           t16[r] = f2bf(z * ph);
-          g.o16[(size_t)m * g.ld16 + n] = (uint16_t)t16[r];
-          if (EPI == EPI_GELU_TRAIN) g.o32[(size_t)m * g.ld32 + n] = ph + z * (gz * kInvSqrt2Pi);
+          f32[r] = ph + z * (gz * kInvSqrt2Pi);
         } else if (EPI == EPI_LINEAR) {
           if (m < g.m_valid) g.o32[(size_t)m * g.ld32 + n] = v + g.bias[n];
-        } else if (EPI == EPI_BWD) {
-          const float dz = v * g.aux[(size_t)m * g.ldaux + n];
-          t16[r] = f2bf(dz);
-          g.o16[(size_t)m * g.ld16 + n] = (uint16_t)t16[r];
-          g.o32[(size_t)m * g.ld32 + n] = dz;
-        } else {  // EPI_DW
-          if (n < g.n_valid) g.o32[(size_t)m * g.ld32 + n] = v;
+        } else {  // EPI_BWD
+          f32[r] = v * f32[r];
+          t16[r] = f2bf(f32[r]);
         }
+        if (EPI != EPI_LINEAR) g.o16[(size_t)m * g.ld16 + n] = (uint16_t)t16[r];
       }
-      if (EPI == EPI_GELU_TRAIN || EPI == EPI_BWD)
-        *(uint2*)(g.oT + (size_t)n * g.ldT + m0) = make_uint2(t16[0] | (t16[1] << 16), t16[2] | (t16[3] << 16));
+      if (T) {
+        *(uint2*)(g.oT + frag_off(n, m0, g.M)) = make_uint2(t16[0] | (t16[1] << 16), t16[2] | (t16[3] << 16));
+        *(f32x4*)(g.o32 + acc_off(m0, n, g.N)) = f32;
+      }
     }
   }
 }
@@ -143,10 +168,8 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
   }
   const int r16 = lane & 15, kq = (lane >> 4) * 8;
   const uint16_t* pa = g.A + (size_t)(mw + r16) * g.lda + kq;
-  // B is a weight copy in fragment order, but for the weight gradient
-  constexpr bool FO = EPI != EPI_DW;
-  const uint16_t* pb = FO ? g.B + (size_t)(nw >> 4) * 16 * g.K + lane * 8 : g.B + (size_t)(nw + r16) * g.ldb + kq;
-  const size_t sa = (size_t)16 * g.lda, sb = (size_t)16 * (FO ? g.K : g.ldb);
+  const uint16_t* pb = g.B + (size_t)nw * g.K + lane * 8;
+  const size_t sa = (size_t)16 * g.lda, sb = (size_t)16 * g.K;
   f32x4 c[F][F];
 #pragma unroll
   for (int i = 0; i < F; ++i)
@@ -163,7 +186,7 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
 #pragma unroll
       for (int i = 0; i < F; ++i) {
         fa[s][i] = vm[i] ? ld_frag(pa + i * sa + k0 + 32 * s) : zero;
-        fb[s][i] = vn[i] ? ld_frag(pb + i * sb + (FO ? 16 : 1) * (k0 + 32 * s)) : zero;
+        fb[s][i] = vn[i] ? ld_frag(pb + i * sb + 16 * (k0 + 32 * s)) : zero;
       }
 #pragma unroll
     for (int s = 0; s < U; ++s)
@@ -375,18 +398,17 @@ __global__ __launch_bounds__(64 * NW, 4) void k_mlp_infer(MlpArgs a) {
     const int nf = ly.n >> 4;
     // a fragment past the width reads fragment 0's rows (its products are
     // never stored); uniform pointers, advanced a K step at each load
-    const uint16_t* pb[CF];
+    gptr pb[CF];
 #pragma unroll
     for (int j = 0; j < CF; ++j) {
       const int f = cg + NWC * j < nf ? cg + NWC * j : 0;
-      pb[j] = bfn + ly.w16 + (size_t)f * 16 * ly.kp;
+      pb[j] = (gptr)(bfn + ly.w16 + (size_t)f * 16 * ly.kp);
     }
     auto ld_w = [&](bf16x8* b) {
 #pragma unroll
       for (int j = 0; j < CF; ++j) {
-        asm volatile("" : "+s"(pb[j]));
-        b[j] = ld_frag((const uint16_t*)((const char*)pb[j] + lo));
-        pb[j] += 512;
+        b[j] = ld_uni<bf16x8>(pb[j], lo);
+        pb[j] += 1024;
       }
     };
     f32x4 c[RF][CF];
@@ -480,9 +502,9 @@ __global__ __launch_bounds__(64 * NW, 4) void k_mlp_infer(MlpArgs a) {
 }
 
 // Batch assembly: inputs to bfloat16, zero-padded to 32 columns and to M rows
-// (row-major and transposed), targets to a dense FP32 block.
-__global__ void k_gather(const float* __restrict__ x, const float* __restrict__ t, const int* __restrict__ rows,
-                         int m_valid, int M, int kin, int W, uint16_t* X16, uint16_t* XT, float* T) {
+// (row-major and, for training, transposed in fragment order).
+__global__ void k_gather(const float* __restrict__ x, const int* __restrict__ rows, int m_valid, int M, int kin,
+                         uint16_t* X16, uint16_t* XT) {
   const int stride = gridDim.x * blockDim.x;
   for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < M * 32; e += stride) {
     const int m = e >> 5, c = e & 31;
@@ -493,43 +515,36 @@ __global__ void k_gather(const float* __restrict__ x, const float* __restrict__ 
     }
     const uint16_t b = (uint16_t)f2bf(v);
     X16[e] = b;
-    if (XT) XT[(size_t)c * M + m] = b;
-  }
-  if (!T) return;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < M * W; e += stride) {
-    const int m = e / W, c = e - m * W;
-    float v = 0.0f;
-    if (m < m_valid) {
-      const long long r = rows ? rows[m] : m;
-      v = t[r * W + c];
-    }
-    T[e] = v;
+    if (XT) XT[frag_off(c, m, M)] = b;
   }
 }
 
 // Mean squared error and its gradient dY = 2 (y - t) / (m_valid W), written
-// as FP32, bfloat16 and transposed bfloat16.  Each block covers 64 columns x
-// 16 rows and leaves the sum of its squared errors in part[].
-__global__ __launch_bounds__(256) void k_loss(const float* __restrict__ y, const float* __restrict__ t, int M,
-                                              int m_valid, int W, float scale, uint16_t* g16, uint16_t* gT,
-                                              float* dz, float* part) {
+// as bfloat16 (row-major and transposed in fragment order) and FP32 in
+// fragment order.  Each block covers 64 columns x 16 rows and leaves the sum
+// of its squared errors in part[].
+__global__ __launch_bounds__(256) void k_loss(const float* __restrict__ y, const float* __restrict__ t,
+                                              const int* __restrict__ rows, int M, int m_valid, int W, float scale,
+                                              uint16_t* g16, uint16_t* gT, float* dz, float* part) {
   __shared__ float red[256];
   const int n = blockIdx.x * 64 + (threadIdx.x & 63);
   const int m0 = blockIdx.y * 16 + (threadIdx.x >> 6) * 4;
   float s = 0.0f;
   uint32_t q[4];
+  f32x4 gv;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int m = m0 + r;
     const size_t e = (size_t)m * W + n;
-    const float d = m < m_valid ? y[e] - t[e] : 0.0f;
+    float d = 0.0f;
+    if (m < m_valid) d = y[e] - t[(long long)(rows ? rows[m] : m) * W + n];
     s += d * d;
-    const float gv = scale * d;
-    dz[e] = gv;
-    q[r] = f2bf(gv);
+    gv[r] = scale * d;
+    q[r] = f2bf(gv[r]);
     g16[e] = (uint16_t)q[r];
   }
-  *(uint2*)(gT + (size_t)n * M + m0) = make_uint2(q[0] | (q[1] << 16), q[2] | (q[3] << 16));
+  *(f32x4*)(dz + acc_off(m0, n, W)) = gv;
+  *(uint2*)(gT + frag_off(n, m0, M)) = make_uint2(q[0] | (q[1] << 16), q[2] | (q[3] << 16));
   red[threadIdx.x] = s;
   __syncthreads();
   for (int h = 128; h > 0; h >>= 1) {
@@ -539,57 +554,365 @@ __global__ __launch_bounds__(256) void k_loss(const float* __restrict__ y, const
   if (threadIdx.x == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = red[0];
 }
 
-__global__ __launch_bounds__(256) void k_loss_final(const float* part, int n, float inv, float* loss) {
-  __shared__ float red[256];
-  float s = 0.0f;
-  for (int i = threadIdx.x; i < n; i += 256) s += part[i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-    __syncthreads();
+// Forward, loss and backward of one net over 16 rows of the batch per block:
+// the rows are independent until the weight gradient, so a step needs no
+// launch per layer.  16 waves; wave w owns the 16-column fragments 2w and
+// 2w + 1 of every layer.  The row-major activations and gradients stay in LDS
+// (two buffers, a barrier per layer); their transposes, the GELU derivatives
+// and dZ, which replaces the derivatives in place, go to memory in fragment
+// order, every store contiguous across the wave.
+//
+// What bounds it is the weights through the CU's L1: each block reads W and
+// W^T once (3.6 MB for 4 x 512 + 256 wide layers, 27 us at 64 bytes a clock),
+// so they stream without a break: fragments run PD K steps ahead, and the
+// last steps of a layer load the first of the next.  Each pass costs about 2
+// us more than its share of the stream, for the epilogue and the barrier.
+// Measured with k_dw_adam, us a step: batches of 64 59, 256 61 (23 launches:
+// 220), 1024 66, 4096 104 (one launch per layer: 81, 87, 100, 164).
+// Each accumulator takes its K steps in order with the instruction k_gemm
+// uses and the epilogues are k_gemm's and k_loss's: the same bits.
+template <int PD>
+__global__ __launch_bounds__(1024) void k_mlp_train(TrainArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t act[2][16 * MLP_LDA];
+  __shared__ float red[1024];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, kq = (lane >> 4) * 8, rq = (lane >> 4) * 4;
+  const int m0 = blockIdx.x * 16, M = a.M, L = a.L, T = 2 * L - 1;
+  const unsigned lo = 16u * lane;  // this lane's piece of a fragment or of a result's patch
+  // ... of a transposed result: column r16 of 16, rows (m0 % 32) + rq .. + 3 of 32
+  const unsigned lt = 16u * (r16 + 16 * (((m0 & 31) + rq) >> 3)) + 2u * (rq & 7);
+
+  // Weights of pass t (0 .. L-1: forward through layer t; L .. 2L-2: backward
+  // through layer 2L-1-t): K steps and the wave's fragments 2w and 2w + 1.  A
+  // wave past the layer's width reads fragments 0 and 1.
+  struct Stream {
+    gptr p0, p1;  // the next step to load
+    int ns;
+  };
+  auto weights = [&](int t) {
+    const bool fwd = t < L;
+    const TrainLayer& ly = a.lay[fwd ? t : 2 * L - 1 - t];
+    const int K = fwd ? ly.kp : ly.n, N = fwd ? ly.n : ly.kp, f = 2 * w < (N >> 4) ? 2 * w : 0;
+    const gptr p = (gptr)(a.bf + (fwd ? ly.w16 : ly.wt) + (size_t)f * 16 * K);
+    return Stream{p, p + 32 * K, K >> 5};
+  };
+  bf16x8 b[PD][2];
+  // the next step into b[q], while there is one (the last stays in place)
+  auto ld_w = [&](int q, Stream& s, int step) {
+    b[q][0] = ld_uni<bf16x8>(s.p0, lo);
+    b[q][1] = ld_uni<bf16x8>(s.p1, lo);
+    const int d = step + 1 < s.ns ? 1024 : 0;
+    s.p0 += d;
+    s.p1 += d;
+  };
+  Stream ws = weights(0);
+#pragma unroll
+  for (int q = 0; q < PD; ++q) ld_w(q, ws, q);
+
+  if (tid < 256) {  // inputs: 16 rows x 32 columns, two at a time
+    const int r = tid >> 4, c = (tid & 15) * 2, m = m0 + r;
+    float v0 = 0.0f, v1 = 0.0f;
+    if (m < a.m_valid) {
+      const float* xr = a.x + (long long)(a.rows ? a.rows[m] : m) * a.kin;
+      if (c < a.kin) v0 = xr[c];
+      if (c + 1 < a.kin) v1 = xr[c + 1];
+    }
+    const uint32_t q = f2bf2(v0, v1);
+    *(uint32_t*)(act[0] + r * MLP_LDA + c) = q;
+    a.XT[frag_off(c, m, M)] = (uint16_t)q;
+    a.XT[frag_off(c + 1, m, M)] = (uint16_t)(q >> 16);
   }
-  if (threadIdx.x == 0) *loss = red[0] * inv;
-}
-
-// Column sums of an M x N FP32 block (bias gradients): 64 columns x 4 row
-// slices per block, slices added in a fixed order.
-__global__ __launch_bounds__(256) void k_colsum(const float* __restrict__ dz, int M, int N, float* out) {
-  __shared__ float red[4][64];
-  const int c = threadIdx.x & 63, s = threadIdx.x >> 6;
-  const int n = blockIdx.x * 64 + c;
-  const int rows = (M + 3) / 4, r0 = s * rows, r1 = min(M, r0 + rows);
-  float acc = 0.0f;
-  if (n < N)
-    for (int m = r0; m < r1; ++m) acc += dz[(size_t)m * N + n];
-  red[s][c] = acc;
   __syncthreads();
-  if (s == 0 && n < N) out[n] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
+
+  // One pass: N columns, this wave's two fragments of them.  KIND 0: hidden
+  // layer forward, 1: output layer and loss, 2: backward.  tr: where the
+  // result goes transposed; o32: GELU derivatives (0: written, 2: read and
+  // replaced by dZ) or dZ (1).
+  auto pass = [&](auto kind, int t, int N, const float* bias, uint16_t* tr, float* o32) {
+    constexpr int KIND = decltype(kind)::value;
+    const uint16_t* cur = act[t & 1] + r16 * MLP_LDA + kq;
+    uint16_t* const nxt = act[(t & 1) ^ 1] + rq * MLP_LDA + 32 * w + r16;
+    Stream wn = weights(t + 1 < T ? t + 1 : t);
+    if (2 * w < (N >> 4)) {
+      const gptr pz = (gptr)(o32 + (size_t)((m0 >> 4) * (N >> 4) + 2 * w) * 256);
+      const gptr pt = (gptr)(tr + (size_t)(2 * w * (M >> 5) + (m0 >> 5)) * 512);
+      // the epilogue's operands ahead of the products
+      float bn[2];
+      f32x4 ep[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (KIND == 2)
+          ep[j] = ld_uni<f32x4>(pz + 1024 * j, lo);
+        else
+          bn[j] = bias[32 * w + 16 * j + r16];
+      }
+      f32x4 c[2] = {f32x4{0, 0, 0, 0}, f32x4{0, 0, 0, 0}};
+      auto kstep = [&](int q, int step) {
+        const bf16x8 fa = *(const bf16x8*)(cur + 32 * step);
+        c[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, b[q][0], c[0], 0, 0, 0);
+        c[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, b[q][1], c[1], 0, 0, 0);
+      };
+      int s0 = 0;
+#pragma unroll 1
+      for (; s0 + PD < ws.ns; s0 += PD) {
+#pragma unroll
+        for (int q = 0; q < PD; ++q) {
+          kstep(q, s0 + q);
+          ld_w(q, ws, s0 + PD + q);
+          asm volatile("" ::: "memory");
+        }
+      }
+      if (KIND == 1) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = m0 + rq + r;
+          const float* tp = a.t + (long long)(a.rows ? a.rows[min(m, a.m_valid - 1)] : min(m, a.m_valid - 1)) * N +
+                            32 * w + r16;
+          ep[0][r] = tp[0];
+          ep[1][r] = tp[16];
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < PD; ++q) {  // the last steps; the next pass's first fragments
+        if (s0 + q < ws.ns) kstep(q, s0 + q);
+        ld_w(q, wn, q);
+        asm volatile("" ::: "memory");
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        __builtin_amdgcn_sched_barrier(0);
+        f32x4 o;
+        float h[4], se = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if (KIND == 0) {
+            const float z = c[j][r] + bn[j];
+            float g;
+            const float ph = norm_cdf(z, g);
+            h[r] = z * ph;
+            o[r] = ph + z * (g * kInvSqrt2Pi);
+          } else if (KIND == 1) {
+            const float d = m0 + rq + r < a.m_valid ? (c[j][r] + bn[j]) - ep[j][r] : 0.0f;
+            se += d * d;
+            o[r] = h[r] = a.scale * d;
+          } else {
+            o[r] = h[r] = c[j][r] * ep[j][r];
+          }
+        }
+        if (KIND == 1) red[(w >> 1) * 256 + (rq >> 2) * 64 + ((32 * w + 16 * j) & 63) + r16] = se;
+        const uint32_t h01 = f2bf2(h[0], h[1]), h23 = f2bf2(h[2], h[3]);
+        nxt[16 * j] = (uint16_t)h01;
+        nxt[16 * j + MLP_LDA] = (uint16_t)(h01 >> 16);
+        nxt[16 * j + 2 * MLP_LDA] = (uint16_t)h23;
+        nxt[16 * j + 3 * MLP_LDA] = (uint16_t)(h23 >> 16);
+        st_uni(pt + j * 32 * M, lt, u32x2{h01, h23});
+        st_uni(pz + 1024 * j, lo, o);
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < PD; ++q) ld_w(q, wn, q);
+    }
+    ws = wn;
+    __syncthreads();  // the next pass reads what this one wrote
+  };
+#pragma unroll 1
+  for (int l = 0; l + 1 < L; ++l) {
+    const TrainLayer& ly = a.lay[l];
+    pass(std::integral_constant<int, 0>(), l, ly.n, a.p + ly.bias, ly.aT, ly.gz);
+  }
+  {
+    const TrainLayer& ly = a.lay[L - 1];
+    pass(std::integral_constant<int, 1>(), L - 1, ly.n, a.p + ly.bias, ly.gT, ly.gz);
+    if (w < (ly.n >> 6)) {  // k_loss's tree over 64 columns x 16 rows
+      const float* q = red + w * 256 + lane;
+      float s = (q[0] + q[128]) + (q[64] + q[192]);
+      for (int h = 32; h > 0; h >>= 1) s += __shfl_down(s, h, 64);
+      if (lane == 0) a.part[blockIdx.x * (ly.n >> 6) + w] = s;
+    }
+  }
+#pragma unroll 1
+  for (int l = L - 1; l > 0; --l) {
+    const TrainLayer& ly = a.lay[l - 1];  // (of the columns this pass makes)
+    pass(std::integral_constant<int, 2>(), 2 * L - 1 - l, ly.n, nullptr, ly.gT, ly.gz);
+  }
 }
 
-// Adam on the flat FP32 parameters of one net (update != 0), then refresh of
-// the bfloat16 copies W [n x kp] and W^T [kp x n] used by the products, in
-// fragment order.
-__global__ __launch_bounds__(256) void k_adam(AdamArgs a) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= a.P) return;
-  float p = a.p[e];
-  if (a.update) {
-    const float g = a.g[e];
-    const float m = a.b1 * a.m[e] + (1.0f - a.b1) * g;
-    const float v = a.b2 * a.v[e] + (1.0f - a.b2) * (g * g);
-    a.m[e] = m;
-    a.v[e] = v;
-    p = p - a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
-    a.p[e] = p;
+__device__ __forceinline__ float adam1(const DwArgs& a, float g, float p, float& m, float& v) {
+  m = a.b1 * m + (1.0f - a.b1) * g;
+  v = a.b2 * v + (1.0f - a.b2) * (g * g);
+  return p - a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
+}
+
+// Everything of a training step after dZ of every layer is known, in one
+// launch: weight gradients dW = dZ^T A with Adam and the refresh of the
+// bfloat16 copies in the epilogue (blocks 0 .. n_tile - 1, one 32 x 16 tile of
+// some layer's W^T per wave), bias gradients with theirs (n_col blocks of 64
+// columns x 4 row slices, added in a fixed order), and the loss.  The tile's
+// parameters and moments are loaded before the products; a lane holds four
+// adjacent columns of W, so all of it moves in 16-byte pieces.  Bound by the
+// parameters and moments: 32 bytes a weight, 30 MB for 0.93 M weights.
+template <int KF, int NF, int U>
+__global__ __launch_bounds__(256) void k_dw_adam(DwArgs a) {
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), M = a.M;
+  if ((int)blockIdx.x >= a.n_tile + a.n_col) {  // the loss, from the blocks' parts
+    __shared__ float red[256];
+    float s = 0.0f;
+    for (int i = tid; i < a.n_part; i += 256) s += a.part[i];
+    red[tid] = s;
+    __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+      if (tid < h) red[tid] += red[tid + h];
+      __syncthreads();
+    }
+    if (tid == 0) *a.loss = red[0] * a.inv;
+    return;
   }
   int l = 0;
+  if ((int)blockIdx.x >= a.n_tile) {  // bias gradients
+    __shared__ float sl[4][64];
+    const int blk = (int)blockIdx.x - a.n_tile;
+    while (l + 1 < a.nl && blk >= a.L[l + 1].c0) ++l;
+    const DwLayer& y = a.L[l];
+    const int n = (blk - y.c0) * 64 + lane, q = M / 64;  // row blocks of a slice
+    float acc = 0.0f;
+#pragma unroll 4
+    for (int b = w * q; b < (w + 1) * q; ++b) {
+      const float* d = y.dz + acc_off(16 * b, n, y.n);
+      f32x4 v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = *(const f32x4*)(d + 64 * i);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc += v[i][r];
+    }
+    sl[w][lane] = acc;
+    __syncthreads();
+    if (w == 0) {
+      const int e = y.off + y.n * y.k + n;
+      const float g = ((sl[0][lane] + sl[1][lane]) + sl[2][lane]) + sl[3][lane];
+      a.g[e] = g;
+      if (a.update) {
+        float m = a.m[e], v = a.v[e];
+        a.p[e] = adam1(a, g, a.p[e], m, v);
+        a.m[e] = m;
+        a.v[e] = v;
+      }
+    }
+    return;
+  }
+  const int wt = (int)blockIdx.x * 4 + w;
+  if (wt >= a.n_wave) return;
+  while (l + 1 < a.nl && wt >= a.L[l + 1].t0) ++l;
+  const DwLayer& y = a.L[l];
+  const int q = wt - y.t0, nk = y.kp / (16 * KF), k0 = 16 * KF * (q % nk), n0 = 16 * NF * (q / nk);
+  const int r16 = lane & 15, rq = (lane >> 4) * 4;
+  const bool vec = (y.k & 3) == 0;  // (offsets of the layers are multiples of 64)
+  // a lane's elements of fragment (i, j): columns k0 + 16 i + rq .. + 3 of row n0 + 16 j + r16
+  f32x4 p[KF][NF], m[KF][NF], v[KF][NF];
+  auto elem = [&](int i, int j) { return y.off + (n0 + 16 * j + r16) * y.k + k0 + 16 * i + rq; };
+  auto get = [&](const float* src, int i, int j) {
+    f32x4 x = f32x4{0, 0, 0, 0};
+    const int e = elem(i, j);
+    if (vec) {
+      if (k0 + 16 * i + rq < y.k) x = *(const f32x4*)(src + e);
+      return x;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (k0 + 16 * i + rq + r < y.k) x[r] = src[e + r];
+    return x;
+  };
+  auto put = [&](float* dst, int i, int j, f32x4 x) {
+    const int e = elem(i, j);
+    if (vec) {
+      if (k0 + 16 * i + rq < y.k) *(f32x4*)(dst + e) = x;
+      return;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (k0 + 16 * i + rq + r < y.k) dst[e + r] = x[r];
+  };
+  if (a.update)
+#pragma unroll
+    for (int i = 0; i < KF; ++i)
+#pragma unroll
+      for (int j = 0; j < NF; ++j) {
+        p[i][j] = get(a.p, i, j);
+        m[i][j] = get(a.m, i, j);
+        v[i][j] = get(a.v, i, j);
+      }
+  const size_t fs = (size_t)16 * M;  // a row fragment of the transposes
+  const uint16_t* pa = y.aT + (k0 >> 4) * fs + lane * 8;
+  const uint16_t* pb = y.gT + (n0 >> 4) * fs + lane * 8;
+  f32x4 c[KF][NF];
+#pragma unroll
+  for (int i = 0; i < KF; ++i)
+#pragma unroll
+    for (int j = 0; j < NF; ++j) c[i][j] = f32x4{0, 0, 0, 0};
+  auto steps = [&](int s, auto u_tag) {
+    constexpr int V = decltype(u_tag)::value;
+    bf16x8 fa[V][KF], fb[V][NF];
+#pragma unroll
+    for (int u = 0; u < V; ++u)
+#pragma unroll
+      for (int i = 0; i < KF; ++i) fa[u][i] = ld_frag(pa + i * fs + 512 * (s + u));
+#pragma unroll
+    for (int u = 0; u < V; ++u)
+#pragma unroll
+      for (int j = 0; j < NF; ++j) fb[u][j] = ld_frag(pb + j * fs + 512 * (s + u));
+#pragma unroll
+    for (int u = 0; u < V; ++u)
+#pragma unroll
+      for (int i = 0; i < KF; ++i)
+#pragma unroll
+        for (int j = 0; j < NF; ++j)
+          c[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[u][i], fb[u][j], c[i][j], 0, 0, 0);
+  };
+  const int S = M >> 5;
+  int s = 0;
+  for (; s + U <= S; s += U) steps(s, std::integral_constant<int, U>());
+  for (; s < S; s += 2) steps(s, std::integral_constant<int, 2>());
+#pragma unroll
+  for (int i = 0; i < KF; ++i)
+#pragma unroll
+    for (int j = 0; j < NF; ++j) {
+      put(a.g, i, j, c[i][j]);
+      if (!a.update) continue;
+      f32x4 x;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float mr = m[i][j][r], vr = v[i][j][r];
+        x[r] = adam1(a, c[i][j][r], p[i][j][r], mr, vr);
+        m[i][j][r] = mr;
+        v[i][j][r] = vr;
+      }
+      put(a.m, i, j, m[i][j]);
+      put(a.v, i, j, v[i][j]);
+      put(a.p, i, j, x);
+      const int n = n0 + 16 * j + r16, k = k0 + 16 * i + rq;
+      uint16_t h[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) h[r] = k + r < y.k ? (uint16_t)f2bf(x[r]) : (uint16_t)0;  // padding stays zero
+      *(uint2*)(a.bf + y.w16 + frag_off(n, k, y.kp)) =
+          make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
+#pragma unroll
+      for (int r = 0; r < 4; ++r) a.bf[y.wt + frag_off(k + r, n, y.n)] = h[r];
+    }
+}
+
+// The bfloat16 copies W [n x kp] and W^T [kp x n], in fragment order, of newly
+// set parameters (k_dw_adam keeps them from then on; the padding is zero).
+__global__ __launch_bounds__(256) void k_copies(CopyArgs a) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= a.P) return;
+  int l = 0;
   while (l + 1 < a.nl && e >= a.L[l + 1].off) ++l;
-  const AdamLayer& L = a.L[l];
+  const CopyLayer& L = a.L[l];
   const int i = e - L.off;
   if (i < L.n * L.k) {
     const int row = i / L.k, col = i - row * L.k;
-    const uint16_t b = (uint16_t)f2bf(p);
+    const uint16_t b = (uint16_t)f2bf(a.p[e]);
     a.bf[L.w16 + frag_off(row, col, L.kp)] = b;
     a.bf[L.wt + frag_off(col, row, L.n)] = b;
   }
@@ -804,8 +1127,7 @@ void launch_gemm_f(int epi, const GemmArgs& a, hipStream_t s) {
     case EPI_GELU_TRAIN: k_gemm<EPI_GELU_TRAIN, F><<<grid, block, 0, s>>>(a); break;
     case EPI_GELU_INFER: k_gemm<EPI_GELU_INFER, F><<<grid, block, 0, s>>>(a); break;
     case EPI_LINEAR: k_gemm<EPI_LINEAR, F><<<grid, block, 0, s>>>(a); break;
-    case EPI_BWD: k_gemm<EPI_BWD, F><<<grid, block, 0, s>>>(a); break;
-    default: k_gemm<EPI_DW, F><<<grid, block, 0, s>>>(a); break;
+    default: k_gemm<EPI_BWD, F><<<grid, block, 0, s>>>(a); break;
   }
 }
 
@@ -858,32 +1180,46 @@ int launch_mlp_infer(const MlpArgs& a, int nets, void* stream) {
   return last();
 }
 
-int launch_gather(const float* x, const float* t, const int* rows, int m_valid, int M, int kin, int W,
-                  uint16_t* X16, uint16_t* XT, float* T, void* stream) {
-  const long long work = (long long)M * (T ? (W > 32 ? W : 32) : 32);
+int launch_gather(const float* x, const int* rows, int m_valid, int M, int kin, uint16_t* X16, uint16_t* XT,
+                  void* stream) {
+  const long long work = (long long)M * 32;
   const int blocks = (int)((work + 255) / 256 < 4096 ? (work + 255) / 256 : 4096);
-  k_gather<<<blocks, 256, 0, (hipStream_t)stream>>>(x, t, rows, m_valid, M, kin, W, X16, XT, T);
+  k_gather<<<blocks, 256, 0, (hipStream_t)stream>>>(x, rows, m_valid, M, kin, X16, XT);
   return last();
 }
 
 int loss_parts(int M, int W) { return (W / 64) * (M / 16); }
 
-int launch_loss(const float* y, const float* t, int M, int m_valid, int W, uint16_t* g16, uint16_t* gT, float* dz,
-                float* part, float* loss_dev, void* stream) {
-  hipStream_t s = (hipStream_t)stream;
-  const double denom = (double)m_valid * W;
-  k_loss<<<dim3(W / 64, M / 16), 256, 0, s>>>(y, t, M, m_valid, W, (float)(2.0 / denom), g16, gT, dz, part);
-  if (loss_dev) k_loss_final<<<1, 256, 0, s>>>(part, loss_parts(M, W), (float)(1.0 / denom), loss_dev);
+int launch_loss(const float* y, const float* t, const int* rows, int M, int m_valid, int W, float scale, uint16_t* g16,
+                uint16_t* gT, float* dz, float* part, void* stream) {
+  k_loss<<<dim3(W / 64, M / 16), 256, 0, (hipStream_t)stream>>>(y, t, rows, M, m_valid, W, scale, g16, gT, dz, part);
   return last();
 }
 
-int launch_colsum(const float* dz, int M, int N, float* out, void* stream) {
-  k_colsum<<<(N + 63) / 64, 256, 0, (hipStream_t)stream>>>(dz, M, N, out);
+int launch_mlp_train(const TrainArgs& a, void* stream) {
+  k_mlp_train<4><<<a.M / 16, 1024, 0, (hipStream_t)stream>>>(a);
   return last();
 }
 
-int launch_adam(const AdamArgs& a, void* stream) {
-  k_adam<<<(a.P + 255) / 256, 256, 0, (hipStream_t)stream>>>(a);
+// Tiles of 32 x 16 a wave, 8 K steps' loads in flight: 12 us for batches of
+// 256 (32 x 32 17, 16 x 16 12), 53 for 4096 (85 and 61; 32 x 16 with 4 steps 56).
+constexpr int DW_KF = 2, DW_NF = 1, DW_U = 8;
+
+int launch_dw_adam(DwArgs a, void* stream) {
+  a.n_wave = a.n_col = 0;
+  for (int l = 0; l < a.nl; ++l) {
+    a.L[l].t0 = a.n_wave;
+    a.L[l].c0 = a.n_col;
+    a.n_wave += (a.L[l].n / (16 * DW_NF)) * (a.L[l].kp / (16 * DW_KF));
+    a.n_col += a.L[l].n / 64;
+  }
+  a.n_tile = (a.n_wave + 3) / 4;
+  k_dw_adam<DW_KF, DW_NF, DW_U><<<a.n_tile + a.n_col + (a.loss ? 1 : 0), 256, 0, (hipStream_t)stream>>>(a);
+  return last();
+}
+
+int launch_copies(const CopyArgs& a, void* stream) {
+  k_copies<<<(a.P + 255) / 256, 256, 0, (hipStream_t)stream>>>(a);
   return last();
 }
 

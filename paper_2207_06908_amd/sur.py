@@ -131,7 +131,7 @@ class Ensemble:
         return out
 
     def set_kernel(self, fused):
-        """1: fused inference (default); 0: one product launch per layer."""
+        """1: fused inference and training step (default); 0: one product launch per layer."""
         self._chk(lib().sur_set_kernel(self._h, int(fused)))
 
     def set_input_bound(self, bound):
