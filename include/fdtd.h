@@ -111,10 +111,11 @@ int fdtd_set_materials(fdtd_ctx* c, const uint8_t* cell_mat, const fdtd_material
  * Each pole adds a polarisation current per E component,
  *   tau_p dJ_p/dt + J_p = eps0 d_eps_p dE/dt,
  * taken at n + 1/2 with the trapezoidal rule, like sigma E; J_p lives in the
- * workspace (3 n_poles extra arrays of nx*ny*nz values).  Such a grid runs
+ * workspace (3 n_poles extra arrays of nx*ny*nz values; 6 n_poles where the
+ * two-step pass can run: FP32, at most 256 coefficient classes, 2 npml <= 128
+ * and at least 4096 nodes).  Such a grid runs the two-step pass, elsewhere
  * the split pass, or the fused pass when fdtd_set_kernel asks for it (8-row
- * tiles whatever tile_y asks; a two-step request takes the split pass), and
- * cannot join a batch.
+ * tiles whatever tile_y asks), and cannot join a batch.
  * Needs the semi-implicit loss form.  Errors: EINVAL, ENONFINITE, ESTATE. */
 int fdtd_set_debye(fdtd_ctx* c, int n_poles, const double* tau, const double* d_eps);
 

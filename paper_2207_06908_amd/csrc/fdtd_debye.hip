@@ -1,4 +1,9 @@
-// fdtd_debye.hip -- fused one-step pass of grids with Debye media (gfx950).
+// fdtd_debye.hip -- two-step pass and fused one-step pass of grids with Debye
+// media (gfx950).
+//
+// The two-step pass is the tile of fdtd_march.h with its pole currents on: one
+// launch per two steps, probes included.  FP32 grids with up to 256 classes
+// take it; the currents have two sets, like the fields.
 //
 // The fused tile of fdtd_tile.h with its Debye switch on: the owner of each
 // E node also advances that node's pole currents, in place (they are
@@ -10,9 +15,85 @@
 #include <hip/hip_runtime.h>
 
 #include "fdtd_dev.h"
+#include "fdtd_march.h"
 #include "fdtd_tile.h"
 
 namespace mi355fdtd {
+
+// A two-step pass of a grid with Debye media: as k_tb2 over 60 x 8 tiles.  12
+// waves of one block on a CU: the currents between the two steps take 74 KB
+// of LDS (four poles) beside the tile's 46 and the factors' 25.  A plane of a
+// soil tile in the CPML takes about 4 us against 1.7 without currents: 24
+// more values in and out of memory and 48 of LDS per point, and addresses
+// that no longer fit the scalar registers.  Measured with four poles below
+// the surface, us a step (H and E passes with a probe launch): 512 x 512 x
+// 384 1,547 (2,573), a 100 x 100 x 80 array 25 (30).
+template <bool PML, int NP>
+__global__ __launch_bounds__(768, 3) void k_tb2_debye(GridView<float> g, MarchDebye<float> db, int step, int kz,
+                                                      int ntx, int nty, int npb, int prev, int run) {
+  typedef float T;
+  typedef uint8_t CI;
+  step = gstep(g, step);
+  __shared__ MarchSmem<T, 8> sm;
+  __shared__ MarchDebyeSmem<T, 8, NP> ds;
+  constexpr int GRP = 768 / PR_NT;
+  __shared__ double red[12 * GRP];
+  if ((int)blockIdx.x < npb) {  // uniform per block
+    const int grp = (int)threadIdx.x / PR_NT, t = (int)threadIdx.x % PR_NT, q = (int)blockIdx.x * GRP + grp;
+    const int p = q < g.n_probe ? q : -1;
+    probe_tb2<T, CI, PML>(g, p, step, t, red + 12 * grp, &db);
+    if (prev) probe_one(g, p, step - 1, t, red + 12 * grp + 8);
+    return;
+  }
+  const int tile = xcd_runs((int)blockIdx.x - npb, (int)gridDim.x - npb, run);
+  const int tile_x = tile % ntx, rest = tile / ntx, k0 = (rest / nty) * kz, k1 = min(k0 + kz, g.nz);
+  const int i0 = tile_x * 60, j0 = (rest % nty) * 8;
+  const ColdView<T> cold{(typename ColdView<T>::P)__builtin_amdgcn_kernarg_segment_ptr()};
+  static_assert(sizeof(GridView<T>) % alignof(MarchDebye<T>) == 0, "db follows the view in the kernel's arguments");
+  const DebyeArgs<T> dargs{(typename DebyeArgs<T>::P)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() +
+                                                      sizeof(GridView<T>))};
+  if constexpr (!PML) {
+    March<T, CI, 8, 0, NP>(g, cold, sm, i0, j0, 60, 8, k0, k1, step, &ds, dargs);
+  } else {
+    const int n = g.npml;
+    const bool cx = i0 - 2 >= n && i0 + 62 <= g.nx - n, cy = j0 - 2 >= n && j0 + 10 <= g.ny - n,
+               cz = k0 - 2 >= n && k1 < g.nz - n;
+    if (cx && cy && cz) March<T, CI, 8, 0, NP>(g, cold, sm, i0, j0, 60, 8, k0, k1, step, &ds, dargs);
+    else if (cx && cy) March<T, CI, 8, 4, NP>(g, cold, sm, i0, j0, 60, 8, k0, k1, step, &ds, dargs);
+    else March<T, CI, 8, 7, NP>(g, cold, sm, i0, j0, 60, 8, k0, k1, step, &ds, dargs);
+  }
+}
+
+template <bool PML>
+void tb2_debye(const GridView<float>& g, const MarchDebye<float>& db, int step, int kz, int run, int prev,
+               hipStream_t st) {
+  const int ntx = (g.nx + 59) / 60, nty = (g.ny + 7) / 8, ntz = (g.nz + kz - 1) / kz, npb = (g.n_probe + 2) / 3;
+  const dim3 grid((unsigned)(ntx * nty * ntz + npb)), block(768);
+  if (db.npole <= 2)
+    hipLaunchKernelGGL((k_tb2_debye<PML, 2>), grid, block, 0, st, g, db, step, kz, ntx, nty, npb, prev, run);
+  else
+    hipLaunchKernelGGL((k_tb2_debye<PML, 4>), grid, block, 0, st, g, db, step, kz, ntx, nty, npb, prev, run);
+}
+
+int launch_tb2_debye(const void* view, const void* dview, const void* jout, size_t pitch, int step, int kz, int run,
+                     int prev, void* stream) {
+  const GridView<float>& g = *(const GridView<float>*)view;
+  const DebyeView<float>& d = *(const DebyeView<float>*)dview;
+  if (g.ncls > 256 || kz < 1) return (int)hipErrorInvalidValue;
+  MarchDebye<float> db{};
+  db.jin = d.j[0];
+  db.jout = (const float*)jout - d.j[0];
+  db.pitch = pitch;
+  db.dtab = d.dtab;
+  db.dflag = d.dflag;
+  for (int p = 0; p < D_MAXPOLE; ++p) db.kp[p] = d.kp[p];
+  db.npole = d.npole;
+  if (g.npml > 0)
+    tb2_debye<true>(g, db, step, kz, run, prev, (hipStream_t)stream);
+  else
+    tb2_debye<false>(g, db, step, kz, run, prev, (hipStream_t)stream);
+  return (int)hipGetLastError();
+}
 
 // Prefetch distance of the Debye tiles (planes).
 constexpr int DPF = 2;

@@ -157,6 +157,10 @@ int launch_step_debye(int prec, const void* view, const void* dview, int cls16, 
 // Debye poles (fdtd_debye.hip): over the 4-group tile list `tiles` / counts
 // (as for launch_lists_step, 8-row tiles; groups 1-3 on
 // `stream2`) or, with tiles == nullptr, over 64 x 8 tiles of tile_z planes.
+// One two-step pass in Debye media (FP32, 1-byte classes): currents from the
+// view's set to the one at jout, arrays `pitch` values apart.
+int launch_tb2_debye(const void* view, const void* dview, const void* jout, size_t pitch, int step, int kz, int run,
+                     int prev, void* stream);
 int launch_fused_debye(int prec, const void* view, const void* dview, int cls16, int step, int tile_z,
                        const void* tiles, const int* counts, void* stream, void* stream2);
 

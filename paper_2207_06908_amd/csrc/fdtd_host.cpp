@@ -74,6 +74,7 @@ struct fdtd_ctx {
   std::vector<uint8_t> dflag;         // [ncls]
   long long debye_nodes = 0;          // nodes whose class has a pole term
   size_t off_j = 0, off_dtab = 0, off_dflag = 0;
+  int jsets = 0, jcur = 0;            // sets of pole currents, the one that holds the current step's
   DebyeView<float> d32 = {};
   DebyeView<double> d64 = {};
   std::vector<WireRec> wires;
@@ -742,6 +743,10 @@ int group_sources(fdtd_ctx* c) {
   }
   return FDTD_OK;
 }
+// The two-step tiles keep the z CPML table (P_NROW rows of 2 npml values)
+// in LDS, room for 2 npml <= 128 values (FP32) or 64 (FP64).
+static bool tb2_cpml_fits(int npml, int precision) { return 2 * npml <= (precision == 64 ? 64 : 128); }
+
 
 void layout(fdtd_ctx* c) {
   const size_t ts = tsize(c);
@@ -762,7 +767,13 @@ void layout(fdtd_ctx* c) {
   }
   for (int s = 0; s < 2; ++s)
     for (int u = 0; u < 3; ++u) c->off_psi[s][u] = take(4 * c->psi_elems[u] * ts);
-  c->off_j = take((size_t)3 * c->npole * N * ts);     // Debye currents, zeroed with the fields
+  // Debye currents, zeroed with the fields; two sets where the two-step pass
+  // can run (FP32, 1-byte classes, a CPML table that fits its tiles) and the
+  // grid is more than one or two of its tiles (17 x 16 x 16 nodes: 7.4 us a
+  // step in two-step passes, 9.6 in split ones; below that a step is the
+  // latency of its launches)
+  c->jsets = c->npole && c->P.precision == 32 && !c->cls16 && tb2_cpml_fits(np, 32) && c->ncell >= 4096 ? 2 : 1;
+  c->off_j = take((size_t)c->jsets * 3 * c->npole * N * ts);
   c->off_cls = take(N * (c->cls16 ? 2 : 1));
   c->off_ctab = take((size_t)c->ncls * K_STRIDE * ts);
   c->off_dtab = take(c->npole ? (size_t)c->ncls * D_STRIDE * ts : 0);
@@ -1300,10 +1311,6 @@ std::vector<Seg> segments(int n, int np, int w, int align, int w_out) {
   return s;
 }
 
-// The two-step tiles keep the z CPML table (P_NROW rows of 2 npml values)
-// in LDS, room for 2 npml <= 128 values (FP32) or 64 (FP64).
-bool tb2_cpml_fits(int npml, int precision) { return 2 * npml <= (precision == 64 ? 64 : 128); }
-
 
 // Tile list of the fused pass for a grid with a CPML (see fdtd_ctx::tl and
 // launch_lists_step).
@@ -1410,7 +1417,7 @@ struct Tb2Shape {
 };
 Tb2Shape tb2_shape(const fdtd_ctx* c) {
   Tb2Shape s;
-  s.ty = c->tile_y ? c->tile_y : c->P.precision == 32 && c->ncell >= (40ll << 20) ? 12 : 8;
+  s.ty = c->npole ? 8 : c->tile_y ? c->tile_y : c->P.precision == 32 && c->ncell >= (40ll << 20) ? 12 : 8;
   const int ntx = (c->N[0] + 59) / 60, nty = (c->N[1] + s.ty - 1) / s.ty, nz = c->N[2];
   s.kz = c->tile_z;
   if (s.kz == 0) {
@@ -1487,6 +1494,9 @@ int launch_pass(fdtd_ctx* c, hipStream_t st, int variant, bool lists, int lty, i
   }
   DebyeView<float> d32 = c->d32;
   DebyeView<double> d64v = c->d64;
+  const size_t jset = (size_t)3 * c->npole * (size_t)c->ncell;
+  if (c->jcur)
+    for (int q = 0; q < 3 * D_MAXPOLE; ++q) d32.j[q] += jset;
   const void* dview = d64 ? (const void*)&d64v : (const void*)&d32;
   if (lists) {
     hipError_t he = hipEventRecord(c->ev_fork, st);
@@ -1512,6 +1522,12 @@ int launch_pass(fdtd_ctx* c, hipStream_t st, int variant, bool lists, int lty, i
       if (he == hipSuccess) he = hipStreamWaitEvent(st, c->ev_join, 0);
       if (he != hipSuccess) return hip_fail(c, he, "stream join");
     }
+  } else if (c->npole && variant == FDTD_KERNEL_TB2) {
+    const Tb2Shape sh = tb2_shape(c);
+    e = launch_tb2_debye(view, dview, c->d32.j[0] + (c->jcur ? 0 : jset), (size_t)c->ncell, step, sh.kz, sh.run,
+                         c->probe_due ? 1 : 0, (void*)st);
+    c->probe_due = !c->probes.empty();
+    if (!e) c->jcur ^= 1;
   } else if (c->npole) {
     e = variant == FDTD_KERNEL_SPLIT
             ? launch_step_debye(c->P.precision, view, dview, c->cls16, step, (void*)st)
@@ -1551,7 +1567,7 @@ int capture_graph(fdtd_ctx* c, int variant, bool lists, int lty) {
     hipError_t he = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking);
     if (he != hipSuccess) return hip_fail(c, he, "capture stream");
   }
-  const int cur0 = c->cur, G = c->graph_steps, adv = variant == FDTD_KERNEL_TB2 ? 2 : 1;
+  const int cur0 = c->cur, jcur0 = c->jcur, G = c->graph_steps, adv = variant == FDTD_KERNEL_TB2 ? 2 : 1;
   const int* dstep = (const int*)(c->ws + c->off_dstep);
   hipError_t he = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal);
   if (he != hipSuccess) return hip_fail(c, he, "begin capture");
@@ -1563,6 +1579,7 @@ int capture_graph(fdtd_ctx* c, int variant, bool lists, int lty) {
   if (rc == FDTD_OK) rc = record_due(c, c->cap_stream, G, dstep);
   c->probe_due = false;
   c->cur = cur0;
+  c->jcur = jcur0;
   hipGraph_t gr = nullptr;
   he = hipStreamEndCapture(c->cap_stream, &gr);
   if (rc) {
@@ -1594,15 +1611,19 @@ int fdtd_step(fdtd_ctx* c, int n) {
   int chosen = c->variant != FDTD_KERNEL_AUTO ? c->variant : FDTD_KERNEL_TB2;
   if (chosen == FDTD_KERNEL_TB2 && !tb2_ok) chosen = FDTD_KERNEL_FUSED;
   if (c->npole && !c->owr.empty()) return fail(c, FDTD_EINVAL, "oblique wires in a grid with Debye media");
-  // Debye media: the split pass, or the fused pass when asked for (the pole
-  // currents would have to live across the two-step pass's stages).  The
-  // fused pass with pole currents ran 1% faster than the split pass on
-  // 512 x 512 x 384 cells and slower on every smaller grid measured (its
-  // CPML slab groups dominate there).
-  if (c->npole) chosen = c->variant == FDTD_KERNEL_FUSED ? FDTD_KERNEL_FUSED : FDTD_KERNEL_SPLIT;
+  // Debye media: the two-step pass where it can run, else the split pass, or
+  // the fused pass when asked for.  us per step, two-step / split / fused,
+  // four poles on half of the nodes: 17 x 16 x 16 7.4 / 9.6 / 34, 60^3 with a
+  // CPML 12 / 15 / 95, 128^3 54 / 56 / 167, 200 x 200 x 160 149 / 174 / 352,
+  // 384 x 384 x 288 681 / 1,096 / 1,270, 512 x 512 x 384 1,547 / 2,573.
+  if (c->npole && (c->variant == FDTD_KERNEL_SPLIT || (chosen != FDTD_KERNEL_FUSED && c->jsets < 2) ||
+                   (chosen == FDTD_KERNEL_FUSED && c->variant != FDTD_KERNEL_FUSED)))
+    chosen = FDTD_KERNEL_SPLIT;
   c->probe_due = false;
   const int G = c->graph_steps;
-  const long long key = ((long long)chosen * 16 + c->tile_y) * 65536 + c->tile_z;
+  // (one-step passes flip the field sets but not the currents': a graph
+  // belongs to one pairing of the two)
+  const long long key = (((long long)chosen * 16 + c->tile_y) * 65536 + c->tile_z) * 2 + (c->cur ^ c->jcur);
   if (G > 0 && key != c->graph_key) {
     drop_graphs(c);
     c->graph_key = key;
@@ -1613,7 +1634,7 @@ int fdtd_step(fdtd_ctx* c, int n) {
     // idle (us per step, split / fused: 48^3 8.6 / 38, 256 x 256 x 192 with
     // a CPML 226 / 304, 384 x 384 x 288 681 / 714, 512 x 512 x 384 1,708 /
     // 1,412; without one 96^3 16 / 40, 256^3 237 / 190)
-    const int odd = c->ncell < (listable ? 64ll << 20 : 8ll << 20) ? FDTD_KERNEL_SPLIT : FDTD_KERNEL_FUSED;
+    const int odd = c->npole || c->ncell < (listable ? 64ll << 20 : 8ll << 20) ? FDTD_KERNEL_SPLIT : FDTD_KERNEL_FUSED;
     const int variant = (chosen == FDTD_KERNEL_TB2 && n - t < 2) ? odd : chosen;
     const int adv = variant == FDTD_KERNEL_TB2 ? 2 : 1;
     // grids with a CPML run the fused pass over tile lists (8 rows in Debye
