@@ -417,27 +417,62 @@ int build_classes(fdtd_ctx* c) {
     return id;
   };
   c->cls_id.assign((size_t)c->ncell, 0);
+  // Media come in layers and blocks.  A node's class follows from the cells of
+  // two planes and two rows: where those equal the ones before (both of them),
+  // the plane or row of ids is a copy of the last one; elsewhere the key slides
+  // along the row, four new cells a node.  (Every node on its own took 0.9 of
+  // the 2.7 ms of a whole 300-step run of a 48^3 box, this 0.02.)
   Coefs v;
-  for (int k = 0; k < c->N[2]; ++k)
-    for (int j = 0; j < c->N[1]; ++j) {
-      uint64_t last = ~0ull;
+  const int nx = c->N[0], ny = c->N[1], nz = c->N[2];
+  const size_t sx = (size_t)nx, sp = sx * (size_t)ny;
+  const uint8_t* cm = c->cell_mat.empty() ? nullptr : c->cell_mat.data();
+  auto same = [&](size_t a, size_t b, size_t n) { return !cm || std::memcmp(cm + a, cm + b, n) == 0; };
+  std::vector<uint8_t> out(sx, 0xFF), zero(sx, 0);  // rows outside the grid, rows of a grid without materials
+  bool pl0 = false, pl1 = false;                    // plane k - 1 equals k - 2, k equals k - 1
+  for (int k = 0; k < nz; ++k) {
+    pl0 = pl1;
+    pl1 = k > 0 && same((size_t)k * sp, (size_t)(k - 1) * sp, sp);
+    uint16_t* const ids = c->cls_id.data() + (size_t)k * sp;
+    if (k >= 2 && pl0 && pl1) {
+      std::memcpy(ids, ids - sp, sp * sizeof(uint16_t));
+      continue;
+    }
+    bool r0 = false, r1 = false;  // rows j - 1 equal rows j - 2, rows j equal rows j - 1 (planes k and k - 1)
+    for (int j = 0; j < ny; ++j) {
+      const size_t row = (size_t)k * sp + (size_t)j * sx;
+      r0 = r1;
+      r1 = j > 0 && same(row, row - sx, sx) && (k == 0 || same(row - sp, row - sp - sx, sx));
+      uint16_t* const id = ids + (size_t)j * sx;
+      if (j >= 2 && r0 && r1) {
+        std::memcpy(id, id - sx, sx * sizeof(uint16_t));
+        continue;
+      }
+      // the four rows of cells around the row of nodes, dj + 2 dk
+      const uint8_t* r[4];
+      for (int q = 0; q < 4; ++q) {
+        const int jj = j - 1 + (q & 1), kk = k - 1 + (q >> 1);
+        r[q] = jj < 0 || kk < 0 ? out.data() : cm ? cm + (size_t)kk * sp + (size_t)jj * sx : zero.data();
+      }
+      uint64_t key = ~0ull, last = ~0ull;
       int last_id = -1;
-      for (int i = 0; i < c->N[0]; ++i) {
-        const uint64_t key = node_key(c, i, j, k);
-        if (key != last) {
+      for (int i = 0; i < nx; ++i) {
+        key = (key >> 8 & 0x00FF00FF00FF00FFull) | (uint64_t)r[0][i] << 8 | (uint64_t)r[1][i] << 24 |
+              (uint64_t)r[2][i] << 40 | (uint64_t)r[3][i] << 56;
+        if (key != last || last_id < 0) {
           auto it = by_key.find(key);
           if (it == by_key.end()) {
             int rc = node_coefs(c, key, nullptr, v);
             if (rc) return rc;
             it = by_key.emplace(key, intern(v)).first;
+            if ((int)by_tuple.size() > 65535) return fail(c, FDTD_ECLASS, "more than 65535 classes");
           }
           last = key;
           last_id = it->second;
         }
-        c->cls_id[node_index(c, i, j, k)] = (uint16_t)std::min(last_id, 65535);
-        if ((int)by_tuple.size() > 65535) return fail(c, FDTD_ECLASS, "more than 65535 classes");
+        id[i] = (uint16_t)last_id;
       }
     }
+  }
   for (const auto& kv : mods) {
     const long long n = kv.first;
     const int i = (int)(n % c->N[0]);
