@@ -26,13 +26,12 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
 # once the kernels change the figure no longer applies and is reported null.
 # the kernels, and the host code that builds their tile lists and launches
 KERNEL_SOURCES = ("paper_2207_06908_amd/csrc/fdtd_kernels.hip", "paper_2207_06908_amd/csrc/fdtd_tile.h",
-                  "paper_2207_06908_amd/csrc/fdtd_debye.hip", "paper_2207_06908_amd/csrc/yee_update.h",
+                  "paper_2207_06908_amd/csrc/fdtd_debye.hip", "paper_2207_06908_amd/csrc/fdtd_march.h",
+                  "paper_2207_06908_amd/csrc/yee_update.h",
                   "paper_2207_06908_amd/csrc/fdtd_dev.h", "paper_2207_06908_amd/csrc/fdtd_host.cpp")
 MEASURED_TRAFFIC = {
     # (source hash, kernel variant, tile_y, tile_z): HBM bytes per step (all
     # launches of the step; a two-step pass counts half)
-    ("bcecac58d1d08ec9", "tb2", 8, 20): 4.452e9,
-    ("bcecac58d1d08ec9", "tb2", 8, 16): 4.471e9,
 }
 
 
@@ -168,14 +167,15 @@ def bench_batch(warmup: int = 100, graph_steps: int = 100, tune: bool = True):
 def bench_debye(steps: int = 400, warmup: int = 20):
     """The 512 x 512 x 384 scene with the paper's measured four-pole Debye
     soil in both layers.  The autotuner picks, for this grid, between the
-    split pass with polarisation currents and the fused pass over CPML tile
-    groups (and its chunk height); the picked pass gives the value and the
-    roofline, and both passes are timed and reported beside it."""
+    two-step pass with polarisation currents, the split pass and the fused
+    pass over CPML tile groups (and its chunk height); the picked pass gives
+    the value and the roofline, and all three are timed and reported beside
+    it."""
     import torch
     from paper_2207_06908_amd import autotune, fdtd
     from paper_2207_06908_amd import scenarios as S
     tune_steps = len(autotune.DEBYE_CANDIDATES) * (4 + 24)
-    sc = S.config2_debye(n_steps=tune_steps + 2 * (warmup + steps) + 8)
+    sc = S.config2_debye(n_steps=tune_steps + 3 * (warmup + steps) + 8)
     g = fdtd.Grid.from_params(sc.params(), precision=32)
     S.apply(sc, g)
     g.bind()
@@ -197,12 +197,14 @@ def bench_debye(steps: int = 400, warmup: int = 20):
         g.timing(False)
         return e0.elapsed_time(e1) / steps, kms / max(kn, 1)
 
-    runs = {"split": timed(fdtd.KERNEL_SPLIT, 0, 0), "fused": timed(fdtd.KERNEL_FUSED, 8, fused_tz)}
-    picked = "fused" if choice["variant"] == fdtd.KERNEL_FUSED else "split"
+    runs = {"tb2": timed(fdtd.KERNEL_TB2, 0, 0), "split": timed(fdtd.KERNEL_SPLIT, 0, 0),
+            "fused": timed(fdtd.KERNEL_FUSED, 8, fused_tz)}
+    picked = {fdtd.KERNEL_TB2: "tb2", fdtd.KERNEL_FUSED: "fused"}.get(choice["variant"], "split")
     ms, kms = runs[picked]
     bytes_step = g.algorithmic_bytes_per_step()
     achieved = bytes_step / (kms / 1e3) / 1e9
-    kernels = {"split": "k_h_split + k_e_split_debye (two launches per step)",
+    kernels = {"tb2": "k_tb2_debye (one launch per two steps)",
+               "split": "k_h_split + k_e_split_debye (two launches per step)",
                "fused": f"k_fused_list_debye (one launch per step and CPML tile group, {fused_tz}-plane chunks)"}
     out = {"workload": "512x512x384 Yee FDTD as above, both soil layers four-pole Debye soil "
                        "(eps_inf 16.381, sigma0 2.684 mS/m), ADE currents",
@@ -332,7 +334,7 @@ def bench_array(steps: int = 20000, warmup: int = 2000):
     full = sc.meta["full_steps"]
     out = {"workload": "apparent-resistivity array, 100x100x80 cells, dx 0.05 m, three 4-pole Debye layers, "
                        "8 thin wires, Heidler source; steps 2000-22000 of the 400 us run",
-           "kernel": "k_h_split + k_e_split_debye + k_probes per step, replayed from 100-step HIP graphs",
+           "kernel": "k_tb2_debye (one launch per two steps, probes included), replayed from 100-step HIP graphs",
            "steps": steps, "value": round(sc.cells * steps / (ms / 1e3) / 1e6, 1), "unit": "Mcell-updates/s",
            "ms_per_step": round(ms / steps, 6), "full_run_steps": full,
            "full_run_s": round(full * ms / steps / 1e3, 1)}

@@ -113,9 +113,10 @@ int fdtd_set_materials(fdtd_ctx* c, const uint8_t* cell_mat, const fdtd_material
  * taken at n + 1/2 with the trapezoidal rule, like sigma E; J_p lives in the
  * workspace (3 n_poles extra arrays of nx*ny*nz values; 6 n_poles where the
  * two-step pass can run: FP32, at most 256 coefficient classes, 2 npml <= 128
- * and at least 4096 nodes).  Such a grid runs the two-step pass, elsewhere
- * the split pass, or the fused pass when fdtd_set_kernel asks for it (8-row
- * tiles whatever tile_y asks), and cannot join a batch.
+ * and at least 4096 nodes).  Such a grid runs the two-step pass where that is
+ * the faster one (or asked for), elsewhere the split pass, or the fused pass
+ * when fdtd_set_kernel asks for it (8-row tiles whatever tile_y asks), and
+ * cannot join a batch.
  * Needs the semi-implicit loss form.  Errors: EINVAL, ENONFINITE, ESTATE. */
 int fdtd_set_debye(fdtd_ctx* c, int n_poles, const double* tau, const double* d_eps);
 
@@ -229,6 +230,8 @@ size_t fdtd_workspace_bytes(fdtd_ctx* c);
 
 /* Bind caller-owned device memory of at least fdtd_workspace_bytes bytes,
  * 256-byte aligned.  Uploads the tables and zeroes the fields on the stream.
+ * (A Debye grid with a second set of pole currents also binds without room
+ * for it, 3 n_poles arrays less, and then runs the split pass.)
  * Errors: ENOMEM, ESTATE, EDEVICE. */
 int fdtd_bind_workspace(fdtd_ctx* c, void* dev_ptr, size_t bytes);
 

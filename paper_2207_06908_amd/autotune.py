@@ -23,15 +23,17 @@ from . import fdtd
 GRID_CANDIDATES: List[Tuple[int, int, int]] = (
     [(fdtd.KERNEL_SPLIT, 0, 0)]
     + [(fdtd.KERNEL_FUSED, ty, tz) for ty in (4, 8) for tz in (16, 24, 32, 48, 64)]
+    + [(fdtd.KERNEL_TB2, 0, 0)]  # the library's own shape for the grid's size
     + [(fdtd.KERNEL_TB2, 8, tz) for tz in (16, 18, 20, 22, 24, 28, 32, 40)]
     + [(fdtd.KERNEL_TB2, 4, tz) for tz in (16, 20, 28)]
     + [(fdtd.KERNEL_TB2, 12, tz) for tz in (16, 20, 24)]
 )
-# Grids with Debye media take the split pass or the fused pass (8-row tiles;
-# TZ-plane chunks of the CPML tile groups).  Their cache key needs its own
+# Grids with Debye media take the two-step pass (where it can run, else the
+# split pass), the split pass or the fused pass (8-row tiles).  Their cache key needs its own
 # suffix (grid_key does not see the poles).
 DEBYE_CANDIDATES: List[Tuple[int, int, int]] = (
-    [(fdtd.KERNEL_SPLIT, 0, 0)] + [(fdtd.KERNEL_FUSED, 8, tz) for tz in (16, 24, 32, 48, 64)])
+    [(fdtd.KERNEL_SPLIT, 0, 0), (fdtd.KERNEL_TB2, 0, 0)]
+    + [(fdtd.KERNEL_FUSED, 8, tz) for tz in (16, 24, 32, 48, 64)])
 # (TX, TY, TZ, persistent): one-step batch tiles, then two-step 60 x 8
 # tiles (one launch per pass; the last field, kept in cached choices, no
 # longer changes it).

@@ -783,7 +783,8 @@ int group_sources(fdtd_ctx* c) {
 static bool tb2_cpml_fits(int npml, int precision) { return 2 * npml <= (precision == 64 ? 64 : 128); }
 
 
-void layout(fdtd_ctx* c) {
+// jsets: at most this many sets of pole currents.
+void layout(fdtd_ctx* c, int jsets = 2) {
   const size_t ts = tsize(c);
   const size_t N = (size_t)c->ncell;
   const int np = c->P.npml;
@@ -807,7 +808,8 @@ void layout(fdtd_ctx* c) {
   // grid is more than one or two of its tiles (17 x 16 x 16 nodes: 7.4 us a
   // step in two-step passes, 9.6 in split ones; below that a step is the
   // latency of its launches)
-  c->jsets = c->npole && c->P.precision == 32 && !c->cls16 && tb2_cpml_fits(np, 32) && c->ncell >= 4096 ? 2 : 1;
+  const bool two = c->npole && c->P.precision == 32 && !c->cls16 && tb2_cpml_fits(np, 32) && c->ncell >= 4096;
+  c->jsets = two ? jsets : 1;
   c->off_j = take((size_t)c->jsets * 3 * c->npole * N * ts);
   c->off_cls = take(N * (c->cls16 ? 2 : 1));
   c->off_ctab = take((size_t)c->ncls * K_STRIDE * ts);
@@ -1304,7 +1306,7 @@ int fdtd_bind_workspace(fdtd_ctx* c, void* dev, size_t bytes) {
   int rc = freeze(c);
   if (rc) return rc;
   if (c->ws) return fail(c, FDTD_ESTATE, "workspace already bound");
-  if (!dev || bytes < c->ws_bytes) return fail(c, FDTD_ENOMEM, "workspace too small");
+  if (!dev || bytes < fdtd_fit_workspace(c, bytes)) return fail(c, FDTD_ENOMEM, "workspace too small");
   if (((uintptr_t)dev & 255) != 0) return fail(c, FDTD_ENOMEM, "workspace not 256-byte aligned");
   c->ws = (char*)dev;
   rc = c->P.precision == 64 ? upload<double>(c) : upload<float>(c);
@@ -1447,27 +1449,35 @@ int ensure_tiles(fdtd_ctx* c, int ty, int kz) {
 //    x slabs do not meet the same CUs in every round (203 x 157 x 131, 4
 //    tiles a row: 12 in a row 59, 5 and 7 50 us; 512 x 512 x 384: 27 764, 9
 //    782, 36 797, 1 824 us).
+//  - In Debye media a tile's time depends on where it lies: with one round of
+//    blocks the soil tiles in the CPML set it, 3.8 us a plane, with several
+//    it averages, 2.3 us a plane and round and 1.5 for the ragged end
+//    (130 x 130 x 100, planes per chunk 4 / 8 / 12 / 16 / 25: 52 / 47 / 44 /
+//    48 / 55 us a step).
 struct Tb2Shape {
   int ty, kz, run;
+  double us;  // Debye media: time of a pass as modelled above
 };
 Tb2Shape tb2_shape(const fdtd_ctx* c) {
   Tb2Shape s;
   s.ty = c->npole ? 8 : c->tile_y ? c->tile_y : c->P.precision == 32 && c->ncell >= (40ll << 20) ? 12 : 8;
   const int ntx = (c->N[0] + 59) / 60, nty = (c->N[1] + s.ty - 1) / s.ty, nz = c->N[2];
+  const long long probes = (long long)c->probes.size() / 3 + 1;  // blocks that record probes
   s.kz = c->tile_z;
-  if (s.kz == 0) {
-    const long long probes = (long long)c->probes.size() / 3 + 1;  // blocks that record probes
-    double best = 0;
-    for (int kz = 2; kz <= (s.ty == 12 ? 20 : 40); ++kz) {
-      const int chunks = (nz + kz - 1) / kz, d = (nz + chunks - 1) / chunks;
-      const long long nb = (long long)ntx * nty * chunks + probes;
-      const double cost = (nb <= 256 ? 1.0 : (double)nb / 256.0 + 0.5) * (d + 4);
-      if (s.kz == 0 || cost < best) {
-        best = cost;
-        s.kz = d;
-      }
+  s.us = 0;
+  const int lo = s.kz ? s.kz : 2, hi = s.kz ? s.kz : s.ty == 12 ? 20 : 40;
+  double best = 0;
+  for (int kz = lo; kz <= hi; ++kz) {
+    const int chunks = (nz + kz - 1) / kz, d = c->tile_z ? kz : (nz + chunks - 1) / chunks;
+    const long long nb = (long long)ntx * nty * chunks + probes;
+    const double r = (double)nb / 256.0;
+    const double cost = (c->npole ? (r <= 1.0 ? 3.8 : 2.3 * r + 1.5) : r <= 1.0 ? 1.0 : r + 0.5) * (d + 4);
+    if (kz == lo || cost < best) {
+      best = cost;
+      s.kz = d;
     }
   }
+  s.us = best;
   s.run = (3 * ntx) | 1;
   return s;
 }
@@ -1633,6 +1643,15 @@ int capture_graph(fdtd_ctx* c, int variant, bool lists, int lty) {
 
 }  // namespace
 
+size_t fdtd_fit_workspace(fdtd_ctx* c, size_t bytes) {
+  layout(c, 2);
+  if (bytes < c->ws_bytes && c->jsets == 2) {
+    layout(c, 1);
+    if (bytes < c->ws_bytes) layout(c, 2);
+  }
+  return c->ws_bytes;
+}
+
 extern "C" {
 
 int fdtd_step(fdtd_ctx* c, int n) {
@@ -1646,14 +1665,20 @@ int fdtd_step(fdtd_ctx* c, int n) {
   int chosen = c->variant != FDTD_KERNEL_AUTO ? c->variant : FDTD_KERNEL_TB2;
   if (chosen == FDTD_KERNEL_TB2 && !tb2_ok) chosen = FDTD_KERNEL_FUSED;
   if (c->npole && !c->owr.empty()) return fail(c, FDTD_EINVAL, "oblique wires in a grid with Debye media");
-  // Debye media: the two-step pass where it can run, else the split pass, or
-  // the fused pass when asked for.  us per step, two-step / split / fused,
-  // four poles on half of the nodes: 17 x 16 x 16 7.4 / 9.6 / 34, 60^3 with a
-  // CPML 12 / 15 / 95, 128^3 54 / 56 / 167, 200 x 200 x 160 149 / 174 / 352,
-  // 384 x 384 x 288 681 / 1,096 / 1,270, 512 x 512 x 384 1,547 / 2,573.
-  if (c->npole && (c->variant == FDTD_KERNEL_SPLIT || (chosen != FDTD_KERNEL_FUSED && c->jsets < 2) ||
-                   (chosen == FDTD_KERNEL_FUSED && c->variant != FDTD_KERNEL_FUSED)))
-    chosen = FDTD_KERNEL_SPLIT;
+  // Debye media: the two-step pass where it can run and is the faster one,
+  // else the split pass, or the fused pass when asked for.  While a grid's
+  // fields stay in the caches the split pass takes about 9 us a step and 21 a
+  // million nodes; past 3 million it takes 27 and more.  us per step, four
+  // poles below the surface, two-step / split: 48^3 11.6 / 12.3, 64 x 200 x 56
+  // (its second tile of a row is nearly empty) 30 / 25, 300 x 60 x 60 25 / 32,
+  // 130 x 130 x 100 44 / 46, 150 x 150 x 120 61 / 62, 200 x 180 x 150 112 /
+  // 145, 256 x 256 x 192 214 / 346, 512 x 512 x 384 1,547 / 2,573.
+  if (c->npole) {
+    const double cells = (double)c->ncell * 1e-6;
+    const bool two = chosen == FDTD_KERNEL_TB2 && c->jsets == 2 &&
+                     (c->variant == FDTD_KERNEL_TB2 || cells > 3.0 || tb2_shape(c).us < 2.0 * (9.0 + 21.0 * cells));
+    chosen = c->variant == FDTD_KERNEL_FUSED ? FDTD_KERNEL_FUSED : two ? FDTD_KERNEL_TB2 : FDTD_KERNEL_SPLIT;
+  }
   c->probe_due = false;
   const int G = c->graph_steps;
   // (one-step passes flip the field sets but not the currents': a graph

@@ -48,3 +48,40 @@ def test_two_step_debye_equals_the_split_pass(dims, npml, poles, tile_z):
     for plan in plans:
         for a, b in zip(ref, run(plan)):
             assert np.array_equal(a, b), plan
+
+
+def test_debye_without_room_for_a_second_set():
+    """A workspace too small for the second set of currents still binds, and the split pass gives the same bits; a
+    smaller one does not."""
+    import ctypes as C
+    import torch
+    from paper_2207_06908_amd import fdtd
+    de = np.full((2, 4), 3.0)
+    de[0] = 0.0
+    out = []
+    for short in (False, True, "static"):
+        sc = S.random_case(100, 75, 75, 0, seed=8, nsteps=7, n_mats=2)
+        sc.cell_mat[:] = 0
+        sc.cell_mat[:40] = 1
+        sc.debye = (TAU, de)
+        g = fdtd.Grid.from_params(sc.params(), precision=32)
+        ids = S.apply(sc, g)
+        if short:
+            n = g.workspace_bytes()
+            less = 3 * 4 * 100 * 75 * 75 * 4
+            assert n - less < 64 << 20 < n
+            if short == "static":
+                g.bind_static()
+            else:
+                buf = torch.empty(n - less, dtype=torch.uint8, device="cuda")
+                bind = fdtd.lib().fdtd_bind_workspace
+                assert bind(g._h, C.c_void_p(buf.data_ptr()), n - less - 256) == -5
+                assert bind(g._h, C.c_void_p(buf.data_ptr()), n - less) == 0
+                g._ws = buf
+        g.step(sc.n_steps)
+        out.append([g.get_field(c) for c in range(6)] + [g.probe(i) for i in ids])
+        g.close()
+    assert max(np.abs(r).max() for r in out[0]) > 0
+    for other in out[1:]:
+        for a, b in zip(out[0], other):
+            assert np.array_equal(a, b)
