@@ -922,7 +922,7 @@ int upload(fdtd_ctx* c) {
     for (int out = 0; out < 2; ++out) fill_view<T>(c, view_of<T>(c, in, out), in, out);
   const GridView<T>& g = view_of<T>(c, 0, 0);
   hipStream_t st = c->stream;
-  // zero fields, CPML state (both sets) and the zero plane
+  // zero fields and CPML state (both sets) and the pole currents
   hipError_t e = hipMemsetAsync(c->ws + c->off_f, 0, c->off_cls - c->off_f, st);
   if (e != hipSuccess) return hip_fail(c, e, "hipMemsetAsync");
   const void* cls_src = c->cls_id.data();

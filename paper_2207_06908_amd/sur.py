@@ -145,7 +145,7 @@ class Ensemble:
         ymean = torch.empty((n, self.widths[-1]), dtype=torch.float32, device=self.device)
         spread = torch.empty(n, dtype=torch.float32, device=self.device)
         ids = torch.empty(max(n, 1), dtype=torch.int32, device=self.device)
-        cnt = torch.zeros(1, dtype=torch.int32, device=self.device)
+        cnt = torch.empty(1, dtype=torch.int32, device=self.device)  # always written by the list kernel
         self._chk(lib().sur_infer_route(self._h, _ptr(x), n, float(threshold), _ptr(ymean), _ptr(spread),
                                         _ptr(ids), _ptr(cnt)))
         return ymean, spread, ids, cnt
