@@ -102,8 +102,8 @@ int sur_infer_route(sur_ctx* c, const float* x_dev, int n, float threshold, floa
  * runs every layer of every net in one fused launch per chunk, the
  * activations of a block of rows held on chip (hidden widths up to 512,
  * output width up to 260), and forward, loss and backward of a training step
- * in one (output width up to 256, up to 4096 rows); 0 runs one product launch
- * per layer and net.  Both give the same bits.  Errors: EINVAL. */
+ * in one (output width up to 256); 0 runs one product launch per layer and
+ * net.  Both give the same bits.  Errors: EINVAL. */
 int sur_set_kernel(sur_ctx* c, int fused);
 
 /* Guard for sur_infer_route: a row any of whose inputs lies outside

@@ -42,7 +42,7 @@ struct CopyArgs {
 
 // Forward, loss and backward in one launch (k_mlp_train): M rows (a multiple
 // of 64), hidden widths <= MLP_KMAX, output width <= MLP_TOUT.
-constexpr int MLP_TOUT = 256, MLP_TROWS = 4096;
+constexpr int MLP_TOUT = 256;
 struct TrainLayer {
   long long w16, wt;  // element offsets of the copies W, W^T
   int bias, kp, n;    // offset of b in the parameters, padded fan-in, fan-out

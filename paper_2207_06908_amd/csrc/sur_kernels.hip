@@ -568,7 +568,7 @@ __global__ __launch_bounds__(256) void k_loss(const float* __restrict__ y, const
 // last steps of a layer load the first of the next.  Each pass costs about 2
 // us more than its share of the stream, for the epilogue and the barrier.
 // Measured with k_dw_adam, us a step: batches of 64 59, 256 61 (23 launches:
-// 220), 1024 66, 4096 104 (one launch per layer: 81, 87, 100, 164).
+// 220), 1024 66, 4096 102 (one launch per layer: 81, 87, 100, 176).
 // Each accumulator takes its K steps in order with the instruction k_gemm
 // uses and the epilogues are k_gemm's and k_loss's: the same bits.
 template <int PD>

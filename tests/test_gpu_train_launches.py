@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("widths,batches", [
     ([5, 512, 512, 512, 512, 256], (1, 64, 65, 256, 1000)),
-    ([8, 320, 64, 192, 128], (63, 96, 4096)),
+    ([8, 320, 64, 192, 128], (63, 96, 4096, 4200)),
     ([32, 128, 64], (17, 130)),
     ([3, 64], (5, 200)),
     ([4, 64, 64, 64, 64, 64, 64, 64], (40, 129)),
@@ -25,7 +25,7 @@ def test_two_launches_match_layers(widths, batches):
         rows = torch.randperm(n + 50, generator=gen)[:n].to(torch.int32).cuda()
         got = {}
         for fused in (0, 1):
-            ens = Ensemble(widths, n_nets=2, max_rows=4096)
+            ens = Ensemble(widths, n_nets=2, max_rows=4224)
             for q in range(2):
                 ens.init_params(q, 5 + q)
             ens.set_kernel(fused)
