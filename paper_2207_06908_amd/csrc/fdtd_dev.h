@@ -213,7 +213,8 @@ int launch_set(int* d, int v, void* stream);
 // the static workspace of any device (called by fdtd_destroy).
 struct fdtd_ctx;
 int fdtd_fail_code(fdtd_ctx* c, int code, const std::string& msg);
-// Lay the (unbound) context's workspace out to fit `bytes` if it can: with two
-// sets of pole currents or, where only that fits, one.  Returns its size.
-size_t fdtd_fit_workspace(fdtd_ctx* c, size_t bytes);
+bool fdtd_is_bound(const fdtd_ctx* c);
+// The smallest workspace that the context binds: fdtd_workspace_bytes or, for
+// a Debye grid with two sets of pole currents, what one set takes.
+size_t fdtd_least_workspace(fdtd_ctx* c);
 void fdtd_static_release(const fdtd_ctx* c);

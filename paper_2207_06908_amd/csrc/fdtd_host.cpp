@@ -1306,11 +1306,15 @@ int fdtd_bind_workspace(fdtd_ctx* c, void* dev, size_t bytes) {
   int rc = freeze(c);
   if (rc) return rc;
   if (c->ws) return fail(c, FDTD_ESTATE, "workspace already bound");
-  if (!dev || bytes < fdtd_fit_workspace(c, bytes)) return fail(c, FDTD_ENOMEM, "workspace too small");
+  if (!dev || bytes < fdtd_least_workspace(c)) return fail(c, FDTD_ENOMEM, "workspace too small");
   if (((uintptr_t)dev & 255) != 0) return fail(c, FDTD_ENOMEM, "workspace not 256-byte aligned");
+  if (bytes < c->ws_bytes) layout(c, 1);
   c->ws = (char*)dev;
   rc = c->P.precision == 64 ? upload<double>(c) : upload<float>(c);
-  if (rc) c->ws = nullptr;
+  if (rc) {  // unbound again, as it was
+    c->ws = nullptr;
+    layout(c);
+  }
   return rc;
 }
 
@@ -1643,13 +1647,14 @@ int capture_graph(fdtd_ctx* c, int variant, bool lists, int lty) {
 
 }  // namespace
 
-size_t fdtd_fit_workspace(fdtd_ctx* c, size_t bytes) {
-  layout(c, 2);
-  if (bytes < c->ws_bytes && c->jsets == 2) {
-    layout(c, 1);
-    if (bytes < c->ws_bytes) layout(c, 2);
-  }
-  return c->ws_bytes;
+bool fdtd_is_bound(const fdtd_ctx* c) { return c->ws != nullptr; }
+
+size_t fdtd_least_workspace(fdtd_ctx* c) {
+  if (c->ws || c->jsets < 2) return c->ws_bytes;
+  layout(c, 1);
+  const size_t least = c->ws_bytes;
+  layout(c);
+  return least;
 }
 
 extern "C" {

@@ -40,9 +40,10 @@ extern "C" int fdtd_bind_static(fdtd_ctx* c) {
   if (!c) return FDTD_EINVAL;
   int rc = fdtd_finalize(c);
   if (rc) return rc;
-  size_t need = fdtd_workspace_bytes(c);
-  if (need == 0) return FDTD_EINVAL;
-  if (need > FDTD_STATIC_BYTES) need = fdtd_fit_workspace(c, FDTD_STATIC_BYTES);
+  // (a bound context keeps its layout, and the array if it holds it)
+  if (fdtd_is_bound(c)) return fdtd_fail_code(c, FDTD_ESTATE, "workspace already bound");
+  if (fdtd_workspace_bytes(c) == 0) return FDTD_EINVAL;
+  const size_t need = fdtd_least_workspace(c);
   if (need > FDTD_STATIC_BYTES)
     return fdtd_fail_code(c, FDTD_ENOMEM, "workspace of " + std::to_string(need) + " bytes exceeds the " +
                                               std::to_string((size_t)FDTD_STATIC_BYTES) + "-byte static array");
