@@ -265,8 +265,8 @@ int fdtd_bind_static(fdtd_ctx* c);
 int fdtd_set_kernel(fdtd_ctx* c, int variant, int tile_y, int tile_z);
 
 /* Graph replay: graph_steps (a multiple of 4; 0 = off, the default) steps
- * of launches are captured once into a HIP graph (per parity of the field
- * set they start from) and replayed for each run of that many steps, the
+ * of launches are captured once into a HIP graph (per pairing of the field
+ * set and the set of pole currents they start from) and replayed for each run of that many steps, the
  * kernels taking the step from a counter in the workspace.  For small grids,
  * whose steps are short next to the launch overhead.  Results do not depend
  * on it (bitwise).  While timing is enabled, a replay is timed whole, its

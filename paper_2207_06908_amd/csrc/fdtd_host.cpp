@@ -141,15 +141,15 @@ struct fdtd_ctx {
   bool probe_due = false;            // the probes of the last step are still to be recorded (within fdtd_step)
   long long steps_done = 0;
   int variant = FDTD_KERNEL_AUTO, tile_y = 0, tile_z = 0;
-  // graph replay (fdtd_set_graph): G steps captured once per parity of the
-  // field set they start from, replayed with the step taken from a device
-  // counter at off_dstep
+  // graph replay (fdtd_set_graph): G steps captured once per pairing of the
+  // field set and the set of pole currents they start from (graph_slot),
+  // replayed with the step taken from a device counter at off_dstep
   int graph_steps = 0;
   long long graph_key = -1;          // launch shape the graphs were captured for
   size_t off_dstep = 0;
   hipStream_t cap_stream = nullptr;
-  hipGraph_t graph[2] = {nullptr, nullptr};
-  hipGraphExec_t gexec[2] = {nullptr, nullptr};
+  hipGraph_t graph[4] = {};
+  hipGraphExec_t gexec[4] = {};
   // kernel timing: a ring of event pairs, drained when a slot is reused
   bool timing = false;
   static constexpr int kRing = 64;
@@ -1599,8 +1599,18 @@ int launch_pass(fdtd_ctx* c, hipStream_t st, int variant, bool lists, int lty, i
   return FDTD_OK;
 }
 
+// The graph of the sets that hold the current step.  (One-step passes flip
+// the field sets but not the currents'; a grid without poles has two.)
+int graph_slot(const fdtd_ctx* c) { return c->cur + 2 * c->jcur; }
+
 void drop_graphs(fdtd_ctx* c) {
-  for (int q = 0; q < 2; ++q) {
+  bool any = false;
+  for (const hipGraphExec_t x : c->gexec) any = any || x;
+  // a replay may still be running (a stream under capture cannot be waited for)
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (any && hipStreamIsCapturing(c->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone)
+    (void)hipStreamSynchronize(c->stream);
+  for (int q = 0; q < 4; ++q) {
     if (c->gexec[q]) (void)hipGraphExecDestroy(c->gexec[q]);
     if (c->graph[q]) (void)hipGraphDestroy(c->graph[q]);
     c->gexec[q] = nullptr;
@@ -1608,15 +1618,15 @@ void drop_graphs(fdtd_ctx* c) {
   }
 }
 
-// Capture graph_steps steps from the current field-set parity: step offsets
-// 0 .. G-1 from the device counter, the ping-pong sets in the order the
-// eager loop would use them (G is a multiple of 4, so the parity returns).
+// Capture graph_steps steps from the current sets: step offsets 0 .. G-1 from
+// the device counter, the ping-pong sets in the order the eager loop would
+// use them (G is a multiple of 4, so the same sets are current again).
 int capture_graph(fdtd_ctx* c, int variant, bool lists, int lty) {
   if (!c->cap_stream) {  // the legacy default stream cannot be captured
     hipError_t he = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking);
     if (he != hipSuccess) return hip_fail(c, he, "capture stream");
   }
-  const int cur0 = c->cur, jcur0 = c->jcur, G = c->graph_steps, adv = variant == FDTD_KERNEL_TB2 ? 2 : 1;
+  const int cur0 = c->cur, jcur0 = c->jcur, slot = graph_slot(c), G = c->graph_steps, adv = variant == FDTD_KERNEL_TB2 ? 2 : 1;
   const int* dstep = (const int*)(c->ws + c->off_dstep);
   hipError_t he = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal);
   if (he != hipSuccess) return hip_fail(c, he, "begin capture");
@@ -1636,8 +1646,8 @@ int capture_graph(fdtd_ctx* c, int variant, bool lists, int lty) {
     return rc;
   }
   if (he != hipSuccess) return hip_fail(c, he, "end capture");
-  c->graph[cur0] = gr;
-  he = hipGraphInstantiate(&c->gexec[cur0], gr, nullptr, nullptr, 0);
+  c->graph[slot] = gr;
+  he = hipGraphInstantiate(&c->gexec[slot], gr, nullptr, nullptr, 0);
   if (he != hipSuccess) {
     drop_graphs(c);
     return hip_fail(c, he, "graph instantiate");
@@ -1686,9 +1696,7 @@ int fdtd_step(fdtd_ctx* c, int n) {
   }
   c->probe_due = false;
   const int G = c->graph_steps;
-  // (one-step passes flip the field sets but not the currents': a graph
-  // belongs to one pairing of the two)
-  const long long key = (((long long)chosen * 16 + c->tile_y) * 65536 + c->tile_z) * 2 + (c->cur ^ c->jcur);
+  const long long key = ((long long)chosen * 16 + c->tile_y) * 65536 + c->tile_z;
   if (G > 0 && key != c->graph_key) {
     drop_graphs(c);
     c->graph_key = key;
@@ -1739,14 +1747,14 @@ int fdtd_step(fdtd_ctx* c, int n) {
     }
     int e;
     if (replay) {
-      if (!c->gexec[c->cur]) {
+      if (!c->gexec[graph_slot(c)]) {
         int rc = capture_graph(c, variant, lists, vty);
         if (rc) return rc;
       }
       e = launch_set((int*)(c->ws + c->off_dstep), (int)c->steps_done, (void*)c->stream);
       if (e) return fail(c, FDTD_EDEVICE, std::string("step counter: ") + hipGetErrorString((hipError_t)e));
       if (slot >= 0 && hipEventRecord(c->ev0[slot], c->stream) != hipSuccess) return fail(c, FDTD_EDEVICE, "event");
-      hipError_t he = hipGraphLaunch(c->gexec[c->cur], c->stream);
+      hipError_t he = hipGraphLaunch(c->gexec[graph_slot(c)], c->stream);
       if (he != hipSuccess) return hip_fail(c, he, "graph launch");
     } else {
       if (slot >= 0 && hipEventRecord(c->ev0[slot], c->stream) != hipSuccess) return fail(c, FDTD_EDEVICE, "event");
