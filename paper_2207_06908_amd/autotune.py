@@ -8,10 +8,14 @@ tile shapes (TX, TY) and TZ.  Every variant computes bitwise the same fields
 (the per-element arithmetic is shared), so tuning never changes results.
 
 The cache file is ``$FDTD_TUNE_CACHE`` if set, else
-``~/.cache/mi355fdtd/tune.json``.
+``~/.cache/mi355fdtd/tune.json``.  A measured entry names the library and the
+candidates it was measured with; another build measures again.  (An entry that
+no tuning run wrote, one without ``candidates``, stands as it is.)
 """
 from __future__ import annotations
 
+import functools
+import hashlib
 import json
 import os
 from typing import Iterable, List, Sequence, Tuple
@@ -91,6 +95,23 @@ def batch_key(dims: Sequence[Tuple[int, int, int]], npml: int, precision: int = 
     return f"{device or _device_name()}|batch|{len(dims)}|{float(f'{cells:.2g}'):.3g}|npml{npml}|fp{precision}"
 
 
+@functools.lru_cache(maxsize=None)
+def library_stamp() -> str:
+    """Digest of the built library and of the candidate lists."""
+    h = hashlib.sha1(repr((GRID_CANDIDATES, DEBYE_CANDIDATES, BATCH_CANDIDATES)).encode())
+    with open(fdtd.LIB_PATH, "rb") as f:
+        h.update(f.read())
+    return h.hexdigest()[:16]
+
+
+def cached_choice(key: str, path: str = None):
+    """The cached choice of a key, None if there is none or another build's."""
+    v = load_cache(path).get(key)
+    if isinstance(v, dict) and "candidates" in v and v.get("library") != library_stamp():
+        return None
+    return v
+
+
 def _time_grid(g: "fdtd.Grid", cand, warmup: int, steps: int) -> float:
     g.set_kernel(*cand)
     g.step(warmup)
@@ -107,9 +128,9 @@ def tune_grid(make_grid, key: str, candidates: Iterable = None, warmup: int = 4,
     """make_grid(max_steps) -> a set-up fdtd.Grid, or a Grid with room for
     tuning_steps() more steps.  Returns the cached or newly measured best
     {variant, tile_y, tile_z, ms_per_step}."""
-    cache = load_cache(path)
-    if key in cache and not force:
-        return cache[key]
+    cached = None if force else cached_choice(key, path)
+    if cached is not None:
+        return cached
     cands = list(candidates or GRID_CANDIDATES)
     g = make_grid if isinstance(make_grid, fdtd.Grid) else make_grid(len(cands) * (warmup + steps) + 4)
     results = []
@@ -120,7 +141,7 @@ def tune_grid(make_grid, key: str, candidates: Iterable = None, warmup: int = 4,
             log(f"tune {key}: variant {cand[0]} TY {cand[1]} TZ {cand[2]}: {ms:.4f} ms/step")
     ms, best = min(results)
     value = {"variant": best[0], "tile_y": best[1], "tile_z": best[2], "ms_per_step": ms,
-             "candidates": len(cands)}
+             "candidates": len(cands), "library": library_stamp()}
     store(key, value, path)
     return value
 
@@ -140,9 +161,9 @@ def tune_batch(make_batch, key: str, candidates: Iterable = None, warmup: int = 
     """make_batch(max_steps) -> an fdtd.Batch, or a Batch with room for
     tuning_steps() more steps.  Returns the best {tile_x, tile_y, tile_z,
     persistent, ms_per_step} (apply it with apply_batch)."""
-    cache = load_cache(path)
-    if key in cache and not force:
-        return cache[key]
+    cached = None if force else cached_choice(key, path)
+    if cached is not None:
+        return cached
     cands = list(candidates or BATCH_CANDIDATES)
     b = make_batch if isinstance(make_batch, fdtd.Batch) else make_batch(len(cands) * (warmup + steps) + 4)
     results = []
@@ -161,6 +182,6 @@ def tune_batch(make_batch, key: str, candidates: Iterable = None, warmup: int = 
             log(f"tune {key}: tile {tx}x{ty} TZ {tz} persistent {per}: {ms / max(n, 1):.4f} ms/step")
     ms, best = min(results)
     value = {"tile_x": best[0], "tile_y": best[1], "tile_z": best[2], "persistent": bool(best[3]),
-             "ms_per_step": ms, "candidates": len(cands)}
+             "ms_per_step": ms, "candidates": len(cands), "library": library_stamp()}
     store(key, value, path)
     return value
