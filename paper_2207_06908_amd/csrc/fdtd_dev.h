@@ -206,6 +206,17 @@ int launch_batch_pass(int prec, int cls16, const void* views, const void* tiles,
 int launch_add(int* d, int v, void* stream);
 // *d = v on the stream.
 int launch_set(int* d, int v, void* stream);
+// Block b of nb (dealt to the 8 XCDs round robin) takes list entry
+// xcd_runs(b, nb, run): each XCD gets runs of `run` consecutive entries,
+// interleaved with the other XCDs' runs.  Neighbouring tiles then share an L2
+// while every XCD's reads stay spread over the whole grid.  Blocks past the
+// last full round of runs keep their own index, so the map is one to one.
+__attribute__((always_inline)) constexpr int xcd_runs(int b, int nb, int run) {
+  const int nf = nb / (8 * run) * (8 * run);
+  if (b >= nf) return b;
+  const int x = b & 7, t = b >> 3, g = t / run;
+  return (g * 8 + x) * run + (t - g * run);
+}
 }  // namespace mi355fdtd
 
 // Host-side hooks between fdtd_host.cpp and fdtd_static.hip: record an

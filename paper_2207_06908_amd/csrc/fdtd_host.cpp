@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstring>
 #include <map>
+#include <queue>
 #include <string>
 #include <unordered_map>
 #include <vector>
@@ -73,6 +74,9 @@ struct fdtd_ctx {
   std::vector<double> dtab;           // [ncls][D_STRIDE]
   std::vector<uint8_t> dflag;         // [ncls]
   long long debye_nodes = 0;          // nodes whose class has a pole term
+  std::vector<uint8_t> pole_cols;     // [nz][ceil(ny / 8)][ceil(nx / 60)]: whether a two-step tile's plane holds one
+  int two_kz = 0;                     // two_step_us: planes per chunk and the time
+  double two_us = 0;
   size_t off_j = 0, off_dtab = 0, off_dflag = 0;
   int jsets = 0, jcur = 0;            // sets of pole currents, the one that holds the current step's
   DebyeView<float> d32 = {};
@@ -487,8 +491,23 @@ int build_classes(fdtd_ctx* c) {
   c->ncls = (int)by_tuple.size();
   c->cls16 = c->ncls > 256 ? 1 : 0;
   c->debye_nodes = 0;
-  if (c->npole)
-    for (long long n = 0; n < c->ncell; ++n) c->debye_nodes += c->dflag[c->cls_id[n]];
+  c->pole_cols.clear();
+  c->two_kz = 0;
+  if (c->npole) {
+    const int ntx = (nx + 59) / 60, nty = (ny + 7) / 8;
+    c->pole_cols.assign((size_t)nz * nty * ntx, 0);
+    const uint16_t* id = c->cls_id.data();
+    for (int k = 0; k < nz; ++k)
+      for (int j = 0; j < ny; ++j)
+        for (int t = 0; t < ntx; ++t) {
+          const int w = std::min(60, nx - 60 * t);
+          int q = 0;
+          for (int i = 0; i < w; ++i) q += c->dflag[id[i]];
+          id += w;
+          c->debye_nodes += q;
+          if (q) c->pole_cols[((size_t)k * nty + j / 8) * ntx + t] = 1;
+        }
+  }
   // a source or lumped element must not sit on a wire edge
   for (const SrcRec& s : c->srcs) {
     auto it = mods.find(node_index(c, s.p[0], s.p[1], s.p[2]));
@@ -1456,11 +1475,10 @@ int ensure_tiles(fdtd_ctx* c, int ty, int kz) {
 //  - In Debye media a tile's time depends on where it lies: with one round of
 //    blocks the soil tiles in the CPML set it, 3.8 us a plane, with several
 //    it averages, 2.3 us a plane and round and 1.5 for the ragged end
-//    (130 x 130 x 100, planes per chunk 4 / 8 / 12 / 16 / 25: 52 / 47 / 44 /
-//    48 / 55 us a step).
+//    (130 x 130 x 100, four poles, planes per chunk 4 / 8 / 12 / 16 / 25: 52 /
+//    47 / 44 / 48 / 55 us a step).
 struct Tb2Shape {
   int ty, kz, run;
-  double us;  // Debye media: time of a pass as modelled above
 };
 Tb2Shape tb2_shape(const fdtd_ctx* c) {
   Tb2Shape s;
@@ -1468,7 +1486,6 @@ Tb2Shape tb2_shape(const fdtd_ctx* c) {
   const int ntx = (c->N[0] + 59) / 60, nty = (c->N[1] + s.ty - 1) / s.ty, nz = c->N[2];
   const long long probes = (long long)c->probes.size() / 3 + 1;  // blocks that record probes
   s.kz = c->tile_z;
-  s.us = 0;
   const int lo = s.kz ? s.kz : 2, hi = s.kz ? s.kz : s.ty == 12 ? 20 : 40;
   double best = 0;
   for (int kz = lo; kz <= hi; ++kz) {
@@ -1481,9 +1498,64 @@ Tb2Shape tb2_shape(const fdtd_ctx* c) {
       s.kz = d;
     }
   }
-  s.us = best;
   s.run = (3 * ntx) | 1;
   return s;
+}
+
+// Debye media: us per step of the two-step pass and of the split pass, for
+// AUTO's choice between them.
+//
+// The two-step pass takes what its blocks take on the device: an XCD's blocks,
+// every eighth one, go in order to the first free of its 32 CUs.  A plane of
+// a tile clear of the CPML costs 0.64 us and one in it 1.42; poles add 0.4 and
+// 0.11 each, and 0.6 in the kernel of three and four.  A block that finds no
+// free CU waits for a light tile where there is one, so the time steps up
+// where nearly all tiles hold poles (100 x 100 x 80 with four: 26 us with
+// 3/4 of the planes, 42 with all).  A probe block takes 5 us, a pass 7.9 more
+// and 0.105 a MB for its fields, CPML state and currents.
+//
+// The split pass: 9 us and, a million nodes, 11.9, 7.8 for the share in the
+// CPML and 3.75 a pole for the share with poles.
+//
+// Against 1,344 grids of 4,000 to 9.9M nodes with 0 to 25 layers, one to four
+// poles in 1/40 to all of the planes, both are 6% wide (standard deviation).
+double two_step_us(fdtd_ctx* c, const Tb2Shape& sh) {
+  if (c->two_kz == sh.kz) return c->two_us;
+  const int nx = c->N[0], ny = c->N[1], nz = c->N[2], np = c->P.npml;
+  const int ntx = (nx + 59) / 60, nty = (ny + 7) / 8, nt = ntx * nty * ((nz + sh.kz - 1) / sh.kz);
+  const int npb = ((int)c->probes.size() + 2) / 3, p = c->npole;
+  const double pole = 0.4 + 0.11 * p + (p > 2 ? 0.6 : 0.0);
+  double last = 0;
+  std::priority_queue<double, std::vector<double>, std::greater<double>> cu[8];
+  for (int b = 0; b < npb + nt; ++b) {
+    double us = 5.0;
+    if (b >= npb) {
+      const int q = xcd_runs(b - npb, nt, sh.run), i0 = q % ntx * 60, col = q % (ntx * nty), j0 = col / ntx * 8;
+      const int k0 = q / (ntx * nty) * sh.kz, k1 = std::min(k0 + sh.kz, nz);
+      const bool clear = np == 0 || (i0 - 2 >= np && i0 + 62 <= nx - np && j0 - 2 >= np && j0 + 10 <= ny - np &&
+                                     k0 - 2 >= np && k1 < nz - np);
+      us = (k1 - k0 + 4) * (clear ? 0.64 : 1.42);
+      for (int k = std::max(k0 - 1, 0); k <= std::min(k1, nz - 1); ++k)
+        if (c->pole_cols[(size_t)k * nty * ntx + col]) us += pole;
+    }
+    auto& h = cu[b & 7];
+    if (h.size() == 32) {
+      us += h.top();
+      h.pop();
+    }
+    h.push(us);
+    last = std::max(last, us);
+  }
+  double psi = 0;
+  for (const size_t e : c->psi_elems) psi += (double)e;
+  const double mb = 4e-6 * (13.0 * (double)c->ncell + 6.0 * p * (double)c->debye_nodes + 8.0 * psi);
+  c->two_kz = sh.kz;
+  return c->two_us = 0.5 * (7.9 + last + 0.105 * mb);
+}
+double split_us(const fdtd_ctx* c) {
+  const double np2 = 2.0 * c->P.npml, n = (double)c->ncell;
+  const double in = (c->N[0] - np2) * (c->N[1] - np2) * (c->N[2] - np2);
+  return 9.0 + 1e-6 * (11.9 * n + 7.8 * (n - in) + 3.75 * c->npole * (double)c->debye_nodes);
 }
 
 // Record the probes of step - 1 from the current field set, where the
@@ -1681,17 +1753,20 @@ int fdtd_step(fdtd_ctx* c, int n) {
   if (chosen == FDTD_KERNEL_TB2 && !tb2_ok) chosen = FDTD_KERNEL_FUSED;
   if (c->npole && !c->owr.empty()) return fail(c, FDTD_EINVAL, "oblique wires in a grid with Debye media");
   // Debye media: the two-step pass where it can run and is the faster one,
-  // else the split pass, or the fused pass when asked for.  While a grid's
-  // fields stay in the caches the split pass takes about 9 us a step and 21 a
-  // million nodes; past 3 million it takes 27 and more.  us per step, four
-  // poles below the surface, two-step / split: 48^3 11.6 / 12.3, 64 x 200 x 56
-  // (its second tile of a row is nearly empty) 30 / 25, 300 x 60 x 60 25 / 32,
-  // 130 x 130 x 100 44 / 46, 150 x 150 x 120 61 / 62, 200 x 180 x 150 112 /
-  // 145, 256 x 256 x 192 214 / 346, 512 x 512 x 384 1,547 / 2,573.
+  // else the split pass, or the fused pass when asked for.  Past 4M nodes the
+  // split pass is never the faster by more than it varies.  Below, the
+  // two-step pass is taken where it is expected to be 5% faster or more: of
+  // the 1,344 grids, replayed from graphs, 9 are then more than 10% slower
+  // than by the split pass (19% at the most), and the mean one is 2.4% above
+  // the better of the two.
+  // us per step, two-step / split: 96^3 without a CPML, four poles in half of
+  // it 17.8 / 24.9; 100 x 100 x 80, four poles in 3/4 26.1 / 30.6, in all 42.2
+  // / 32.7, one pole in 1/4 24.5 / 21.1; 130 x 130 x 100 with two poles in
+  // half of it 36.8 / 42.7; 512 x 512 x 384 with four 1,547 / 2,573.
   if (c->npole) {
-    const double cells = (double)c->ncell * 1e-6;
     const bool two = chosen == FDTD_KERNEL_TB2 && c->jsets == 2 &&
-                     (c->variant == FDTD_KERNEL_TB2 || cells > 3.0 || tb2_shape(c).us < 2.0 * (9.0 + 21.0 * cells));
+                     (c->variant == FDTD_KERNEL_TB2 || c->ncell > 4000000 ||
+                      two_step_us(c, tb2_shape(c)) < 0.95 * split_us(c));
     chosen = c->variant == FDTD_KERNEL_FUSED ? FDTD_KERNEL_FUSED : two ? FDTD_KERNEL_TB2 : FDTD_KERNEL_SPLIT;
   }
   c->probe_due = false;

@@ -295,18 +295,6 @@ __device__ __forceinline__ void debye_point(const DebyeView<T>& d, int cid, unsi
 // Per plane: stage E(k+1) -> barrier -> H(k) -> barrier -> E(k).
 // ---------------------------------------------------------------------------
 
-// Block b of nb (dealt to the 8 XCDs round robin) takes list entry
-// xcd_runs(b, nb, run): each XCD gets runs of `run` consecutive entries,
-// interleaved with the other XCDs' runs.  Neighbouring tiles then share an L2
-// while every XCD's reads stay spread over the whole grid.  Blocks past the
-// last full round of runs keep their own index, so the map is one to one.
-__device__ __forceinline__ int xcd_runs(int b, int nb, int run) {
-  const int nf = nb / (8 * run) * (8 * run);
-  if (b >= nf) return b;
-  const int x = b & 7, t = b >> 3, g = t / run;
-  return (g * 8 + x) * run + (t - g * run);
-}
-
 // Blocks are dealt round-robin to the 8 XCDs; give each XCD a contiguous run
 // of tiles so that neighbouring tiles share that XCD's L2 for their halos.
 __device__ __forceinline__ int xcd_tile(int b, int nb) {
