@@ -31,15 +31,19 @@ __device__ __forceinline__ int gstep(const GridView<T>& g, int step) {
 }
 
 // CPML state of one node: ps[axis][q], q = 0 for the component along
-// axis+1, q = 1 for axis+2; kind 0 = E-type, 1 = H-type.
-template <typename T>
+// axis+1, q = 1 for axis+2; kind 0 = E-type, 1 = H-type.  TILE: loaded for the
+// fused one-step tiles, FP64 values one by one (us a step, by pairs / one by
+// one: a batch of 3 small grids with 32 x 16 tiles 156 / 133, 203 x 157 x 131
+// 262 / 253; the split and two-step passes are 2 to 3% faster by pairs).
+template <typename T, bool TILE = false>
 __device__ __forceinline__ void psi_load(const GridView<T>& g, int kind, const int l[3], int x, int y, int k,
                                          T ps[3][2]) {
   for (int u = 0; u < 3; ++u) {
     ps[u][0] = ps[u][1] = T(0);
     if (l[u] >= 0) {
       const unsigned q = psi_index(u, l[u], x, y, k, g.nx, g.ny, g.npml) + (unsigned)kind * g.pel[u];
-      ld_pair(g.pib[u], q * 2u * (unsigned)sizeof(T), ps[u]);
+      if constexpr (TILE && sizeof(T) == 8) ld_two(g.pib[u], q * 2u * (unsigned)sizeof(T), ps[u]);
+      else ld_pair(g.pib[u], q * 2u * (unsigned)sizeof(T), ps[u]);
     }
   }
 }
@@ -217,7 +221,7 @@ __device__ __forceinline__ SrcRange src_node(const GridView<T>& g, int x, int y,
 
 // One-step wrappers: CPML state from the input set, written (optionally for
 // H) to the output set.
-template <typename T, bool PML, int AX = 7>
+template <typename T, bool PML, int AX = 7, bool TILE = false>
 __device__ __forceinline__ void h_point(const GridView<T>& g, int x, int y, int k, const T* cf, T ex, T ey,
                                         T ez, T ex_j, T ex_k, T ey_i, T ey_k, T ez_i, T ez_j, const T hold[3],
                                         bool store_psi, T hnew[3]) {
@@ -225,13 +229,13 @@ __device__ __forceinline__ void h_point(const GridView<T>& g, int x, int y, int 
   T ps[3][2];
   if (PML) {
     slabs<T, AX>(g, x, y, k, l);
-    psi_load(g, 1, l, x, y, k, ps);
+    psi_load<T, TILE>(g, 1, l, x, y, k, ps);
   }
   h_core<T, PML>(g, l, cf, ex, ey, ez, ex_j, ex_k, ey_i, ey_k, ez_i, ez_j, hold, ps, hnew);
   if (PML && store_psi) psi_store(g, 1, l, x, y, k, ps);
 }
 
-template <typename T, bool PML, int AX = 7>
+template <typename T, bool PML, int AX = 7, bool TILE = false>
 __device__ __forceinline__ void e_point(const GridView<T>& g, int x, int y, int k, unsigned n, const T* cf,
                                         T hx, T hy, T hz, T hx_j, T hx_k, T hy_i, T hy_k, T hz_i, T hz_j,
                                         const T eold[3], int step, T enew[3], int slo, int shi) {
@@ -239,7 +243,7 @@ __device__ __forceinline__ void e_point(const GridView<T>& g, int x, int y, int 
   T ps[3][2];
   if (PML) {
     slabs<T, AX>(g, x, y, k, l);
-    psi_load(g, 0, l, x, y, k, ps);
+    psi_load<T, TILE>(g, 0, l, x, y, k, ps);
   }
   e_core<T, PML>(g, l, n, cf, hx, hy, hz, hx_j, hx_k, hy_i, hy_k, hz_i, hz_j, eold, step, ps, enew, slo, shi);
   if (PML) psi_store(g, 0, l, x, y, k, ps);
@@ -422,7 +426,7 @@ __device__ __forceinline__ void fused_tile(const GridView<T>& g, FusedSmem<T, TX
     __syncthreads();
     if (own && kb >= 0) {
       T h[3];
-      h_point<T, PML, AX>(g, i, j, kb, coef(cb), eb[0], eb[1], eb[2], se[sb][0][ty + 2][tx + 1], ecur[0],
+      h_point<T, PML, AX, true>(g, i, j, kb, coef(cb), eb[0], eb[1], eb[2], se[sb][0][ty + 2][tx + 1], ecur[0],
                       se[sb][1][ty + 1][tx + 2], ecur[1], se[sb][2][ty + 1][tx + 2], se[sb][2][ty + 2][tx + 1],
                       hb, false, h);
       hm[0] = h[0];
@@ -478,9 +482,9 @@ __device__ __forceinline__ void fused_tile(const GridView<T>& g, FusedSmem<T, TX
     // (c) H(k): own column, then the low-side halo point
     T hown[3] = {T(0), T(0), T(0)};
     if (own) {
-      h_point<T, PML, AX>(g, i, j, k, coef(cls_cur), ecur[0], ecur[1], ecur[2], se[s][0][ty + 2][tx + 1], enext[0],
-                      se[s][1][ty + 1][tx + 2], enext[1], se[s][2][ty + 1][tx + 2], se[s][2][ty + 2][tx + 1],
-                      hold, true, hown);
+      h_point<T, PML, AX, true>(g, i, j, k, coef(cls_cur), ecur[0], ecur[1], ecur[2], se[s][0][ty + 2][tx + 1],
+                      enext[0], se[s][1][ty + 1][tx + 2], enext[1], se[s][2][ty + 1][tx + 2],
+                      se[s][2][ty + 2][tx + 1], hold, true, hown);
       const unsigned n = n0 + sxy * (unsigned)k;
       stg(g.fo[3], n, hown[0]);
       stg(g.fo[4], n, hown[1]);
@@ -492,9 +496,9 @@ __device__ __forceinline__ void fused_tile(const GridView<T>& g, FusedSmem<T, TX
     if (hh) {
       T hx3[3] = {T(0), T(0), T(0)};
       if (hh_in) {
-        h_point<T, PML, AX>(g, hx_x, hx_y, k, coef(xcls_cur), se[s][0][hr][hc], se[s][1][hr][hc], se[s][2][hr][hc],
-                        se[s][0][hr + 1][hc], se[s1][0][hr][hc], se[s][1][hr][hc + 1], se[s1][1][hr][hc],
-                        se[s][2][hr][hc + 1], se[s][2][hr + 1][hc], xh_old, false, hx3);
+        h_point<T, PML, AX, true>(g, hx_x, hx_y, k, coef(xcls_cur), se[s][0][hr][hc], se[s][1][hr][hc],
+                        se[s][2][hr][hc], se[s][0][hr + 1][hc], se[s1][0][hr][hc], se[s][1][hr][hc + 1],
+                        se[s1][1][hr][hc], se[s][2][hr][hc + 1], se[s][2][hr + 1][hc], xh_old, false, hx3);
       }
       sh[0][hr][hc] = hx3[0];
       sh[1][hr][hc] = hx3[1];
@@ -505,7 +509,7 @@ __device__ __forceinline__ void fused_tile(const GridView<T>& g, FusedSmem<T, TX
     if (own) {
       const unsigned n = n0 + sxy * (unsigned)k;
       T e[3];
-      e_point<T, PML, AX>(g, i, j, k, n, coef(cls_cur), hown[0], hown[1], hown[2], sh[0][ty][tx + 1], hm[0],
+      e_point<T, PML, AX, true>(g, i, j, k, n, coef(cls_cur), hown[0], hown[1], hown[2], sh[0][ty][tx + 1], hm[0],
                       sh[1][ty + 1][tx], hm[1], sh[2][ty + 1][tx], sh[2][ty][tx + 1], ecur, step, e,
                       srcr.first(k), srcr.last(k));
       if (DB && dcur) {

@@ -78,6 +78,14 @@ __device__ __forceinline__ void ld_pair(const T* base, unsigned off, T v[2]) {
   v[0] = q.x;
   v[1] = q.y;
 }
+// ... in two accesses (the asm statement keeps them from being joined).
+template <typename T>
+__device__ __forceinline__ void ld_two(const T* base, unsigned off, T v[2]) {
+  v[0] = ldb(base, off);
+  off += (unsigned)sizeof(T);
+  asm volatile("" : "+v"(off));
+  v[1] = ldb(base, off);
+}
 template <typename T>
 __device__ __forceinline__ void st_pair(T* base, unsigned off, const T v[2]) {
   typedef T V2 __attribute__((ext_vector_type(2)));
