@@ -1781,8 +1781,11 @@ int fdtd_step(fdtd_ctx* c, int n) {
     // its own: the split pass on grids whose fused tiles leave the device
     // idle (us per step, split / fused: 48^3 8.6 / 38, 256 x 256 x 192 with
     // a CPML 226 / 304, 384 x 384 x 288 681 / 714, 512 x 512 x 384 1,708 /
-    // 1,412; without one 96^3 16 / 40, 256^3 237 / 190)
-    const int odd = c->npole || c->ncell < (listable ? 64ll << 20 : 8ll << 20) ? FDTD_KERNEL_SPLIT : FDTD_KERNEL_FUSED;
+    // 1,412; without one 96^3 16 / 40, 256^3 237 / 190; FP64 with one 400 x
+    // 400 x 320 1,562 / 1,598, 448 x 448 x 320 1,992 / 1,951, without 160^3 93
+    // / 124, 180 x 180 x 170 141 / 151, 200^3 233 / 221, 256^3 489 / 331)
+    const long long few = (listable ? 64ll : c->P.precision == 64 ? 6ll : 8ll) << 20;
+    const int odd = c->npole || c->ncell < few ? FDTD_KERNEL_SPLIT : FDTD_KERNEL_FUSED;
     const int variant = (chosen == FDTD_KERNEL_TB2 && n - t < 2) ? odd : chosen;
     const int adv = variant == FDTD_KERNEL_TB2 ? 2 : 1;
     // grids with a CPML run the fused pass over tile lists (8 rows in Debye
