@@ -67,8 +67,13 @@ __global__ __launch_bounds__(768, 3) void k_tb2_debye(GridView<float> g, MarchDe
 template <bool PML>
 void tb2_debye(const GridView<float>& g, const MarchDebye<float>& db, int step, int kz, int run, int prev,
                hipStream_t st) {
-  const int ntx = (g.nx + 59) / 60, nty = (g.ny + 7) / 8, ntz = (g.nz + kz - 1) / kz, npb = (g.n_probe + 2) / 3;
+  const bool many = g.n_probe > PR_MANY;
+  const int ntx = (g.nx + 59) / 60, nty = (g.ny + 7) / 8, ntz = (g.nz + kz - 1) / kz;
+  const int npb = many ? 0 : (g.n_probe + 2) / 3;
   const dim3 grid((unsigned)(ntx * nty * ntz + npb)), block(768);
+  if (many)
+    hipLaunchKernelGGL((k_probes_tb2<float, uint8_t, PML, true>), dim3((unsigned)g.n_probe), dim3(PR_NT), 0, st, g, db, step,
+                       prev);
   if (db.npole <= 2)
     hipLaunchKernelGGL((k_tb2_debye<PML, 2>), grid, block, 0, st, g, db, step, kz, ntx, nty, npb, prev, run);
   else

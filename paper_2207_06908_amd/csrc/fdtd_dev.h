@@ -206,6 +206,8 @@ int launch_batch_pass(int prec, int cls16, const void* views, const void* tiles,
 int launch_add(int* d, int v, void* stream);
 // *d = v on the stream.
 int launch_set(int* d, int v, void* stream);
+// A two-step pass records up to this many probes itself (k_probes_tb2).
+constexpr int PR_MANY = 2048;
 // Block b of nb (dealt to the 8 XCDs round robin) takes list entry
 // xcd_runs(b, nb, run): each XCD gets runs of `run` consecutive entries,
 // interleaved with the other XCDs' runs.  Neighbouring tiles then share an L2

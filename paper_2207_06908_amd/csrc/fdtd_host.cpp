@@ -1484,7 +1484,7 @@ Tb2Shape tb2_shape(const fdtd_ctx* c) {
   Tb2Shape s;
   s.ty = c->npole ? 8 : c->tile_y ? c->tile_y : c->P.precision == 32 && c->ncell >= (40ll << 20) ? 12 : 8;
   const int ntx = (c->N[0] + 59) / 60, nty = (c->N[1] + s.ty - 1) / s.ty, nz = c->N[2];
-  const long long probes = (long long)c->probes.size() / 3 + 1;  // blocks that record probes
+  const long long probes = c->probes.size() > PR_MANY ? 1 : (long long)c->probes.size() / 3 + 1;  // their blocks
   s.kz = c->tile_z;
   const int lo = s.kz ? s.kz : 2, hi = s.kz ? s.kz : s.ty == 12 ? 20 : 40;
   double best = 0;
@@ -1523,7 +1523,7 @@ double two_step_us(fdtd_ctx* c, const Tb2Shape& sh) {
   if (c->two_kz == sh.kz) return c->two_us;
   const int nx = c->N[0], ny = c->N[1], nz = c->N[2], np = c->P.npml;
   const int ntx = (nx + 59) / 60, nty = (ny + 7) / 8, nt = ntx * nty * ((nz + sh.kz - 1) / sh.kz);
-  const int npb = ((int)c->probes.size() + 2) / 3, p = c->npole;
+  const int npb = c->probes.size() > PR_MANY ? 0 : ((int)c->probes.size() + 2) / 3, p = c->npole;
   const double pole = 0.4 + 0.11 * p + (p > 2 ? 0.6 : 0.0);
   double last = 0;
   std::priority_queue<double, std::vector<double>, std::greater<double>> cu[8];

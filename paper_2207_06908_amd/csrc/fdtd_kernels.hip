@@ -504,6 +504,19 @@ __global__ __launch_bounds__(768, tb2_waves(sizeof(T), true, 8)) void k_tb2_batc
   tb2_any<T, CI, true, 8>(g, cold, sm, ty & 0xffff, tz & 0xffff, ty >> 16, tz >> 16, k0, k0 + (tw >> 16), step);
 }
 
+// The batch's probes apart from its pass (as k_probes_tb2).
+template <typename T, typename CI>
+__global__ __launch_bounds__(PR_NT) void k_probes_tb2_batch(const GridView<T>* __restrict__ views,
+                                                           const int2* __restrict__ plist, int n,
+                                                           const int* __restrict__ d_step, int offset, int prev) {
+  const int step = *d_step + offset;
+  __shared__ double red[8];
+  if ((int)blockIdx.x >= n) return;  // uniform per block
+  const int2 e = plist[blockIdx.x];
+  probe_tb2<T, CI, true>(views[e.x], e.y, step, (int)threadIdx.x, red);
+  if (prev) probe_one(views[e.x], e.y, step - 1, (int)threadIdx.x, red + 4);
+}
+
 // ---------------------------------------------------------------------------
 // probes of a one-step pass: one block per probe, the fixed FP64 order of
 // probe_sum
@@ -815,9 +828,13 @@ template <typename T, typename CI, bool PML, int TY>
 hipError_t launch_tb2(const GridView<T>& g, int step, int kz, int run, int prev, hipStream_t st) {
   constexpr int GRP = 64 * (TY + 4) / PR_NT;
   const int ntx = (g.nx + 59) / 60, nty = (g.ny + TY - 1) / TY, ntz = (g.nz + kz - 1) / kz;
-  const int npb = (g.n_probe + GRP - 1) / GRP;
+  const bool many = g.n_probe > PR_MANY;
+  const int npb = many ? 0 : (g.n_probe + GRP - 1) / GRP;
   const long long nb = (long long)ntx * nty * ntz + npb;
   if (nb > 0x7fffffff || (sizeof(CI) == 1 && g.ncls > 256)) return hipErrorInvalidValue;
+  if (many)
+    hipLaunchKernelGGL((k_probes_tb2<T, CI, PML, false>), dim3((unsigned)g.n_probe), dim3(PR_NT), 0, st, g, MarchDebye<T>{},
+                       step, prev);
   hipLaunchKernelGGL((k_tb2<T, CI, PML, TY>), dim3((unsigned)nb), dim3(64 * (TY + 4)), 0, st, g, step, kz, ntx, nty,
                      npb, prev, run);
   return hipGetLastError();
@@ -946,7 +963,11 @@ int launch_batch_probes(int prec, const void* views, const void* plist, int n, c
 template <typename T, typename CI>
 hipError_t batch_pass_t(const void* views, const void* tiles, int n_tiles, const void* plist, int n_probes,
                         const int* d_step, int offset, int prev, int run, hipStream_t st) {
-  const int npb = (n_probes + 768 / PR_NT - 1) / (768 / PR_NT);
+  const bool many = n_probes > PR_MANY;
+  const int npb = many ? 0 : (n_probes + 768 / PR_NT - 1) / (768 / PR_NT);
+  if (many)
+    hipLaunchKernelGGL((k_probes_tb2_batch<T, CI>), dim3((unsigned)n_probes), dim3(PR_NT), 0, st,
+                       (const GridView<T>*)views, (const int2*)plist, n_probes, d_step, offset, prev);
   hipLaunchKernelGGL((k_tb2_batch<T, CI>), dim3((unsigned)(npb + n_tiles)), dim3(768), 0, st,
                      (const GridView<T>*)views, (const int4*)tiles, (const int2*)plist, n_probes, npb, d_step, offset,
                      prev, run);

@@ -663,4 +663,20 @@ __device__ __forceinline__ void probe_one(const GridView<T>& g, int p, int step,
   if (t == 0 && p >= 0) g.pr_out[(long long)p * g.max_steps + step] = acc;
 }
 
+// Both samples of a pass with more than PR_MANY probes, one block each, in a
+// launch of its own before the pass.  (The pass's own blocks hold the LDS of a
+// tile, one to a CU, and three probes each: the faster way while they are a
+// few rounds.  96 x 96 x 80, us a step in the pass / apart: 300 probes 19 / 24,
+// 1,000 23.3 / 22.5, 3,000 34 / 24, 10,000 68 / 40, 100,000 492 / 246; a batch
+// of 64 grids with 30 probes each 311 / 311, with 300 416 / 363, with 1,000
+// 688 / 496.)
+template <typename T, typename CI, bool PML, bool DB>
+__global__ __launch_bounds__(PR_NT) void k_probes_tb2(GridView<T> g, MarchDebye<T> db, int step, int prev) {
+  step = gstep(g, step);
+  __shared__ double red[8];
+  if ((int)blockIdx.x >= g.n_probe) return;  // uniform per block
+  probe_tb2<T, CI, PML>(g, blockIdx.x, step, (int)threadIdx.x, red, DB ? &db : nullptr);
+  if (prev) probe_one(g, blockIdx.x, step - 1, (int)threadIdx.x, red + 4);
+}
+
 }  // namespace mi355fdtd
