@@ -5,8 +5,8 @@
 // sur_kernels.hip: forward (one product per layer with the bias/GELU
 // epilogue; inference of every net in one fused launch where the widths
 // allow), loss, backward (input-gradient product with the GELU-derivative
-// epilogue; one launch with the forward pass where the widths and the batch
-// allow), then weight and bias gradients with Adam in one launch.
+// epilogue; one launch with the forward pass where the widths allow), then
+// weight and bias gradients with Adam in one launch.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -397,11 +397,15 @@ int sur_forward(sur_ctx* c, int net, const float* x_dev, int n, float* y_dev) {
   if (r) return r;
   if (n < 0 || (n > 0 && (!x_dev || !y_dev))) return fail(c, SUR_EINVAL, "bad forward arguments");
   const int W = c->w.back(), k0 = c->w[0];
+  // The blocks of the fused kernel read their inputs while others write
+  // outputs: where the two share memory, a chunk's inputs are gathered first.
+  const uintptr_t xa = (uintptr_t)x_dev, ya = (uintptr_t)y_dev;
+  const bool apart = xa + (size_t)n * k0 * 4 <= ya || ya + (size_t)n * W * 4 <= xa;
   for (int c0 = 0; c0 < n; c0 += c->R) {
     const int m = std::min(c->R, n - c0), M = (m + 63) / 64 * 64;
     const float* x = x_dev + (size_t)c0 * k0;
     float* y = y_dev + (size_t)c0 * W;
-    if (fused_ok(c)) {
+    if (apart && fused_ok(c)) {
       if ((r = forward_fused(c, net, 1, x, m, y, 0))) return r;
       continue;
     }
