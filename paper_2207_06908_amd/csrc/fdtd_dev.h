@@ -140,8 +140,6 @@ struct OWireView {
 // sample.  Returns 0 or a hipError_t value.
 int launch_step(int prec, const void* view, int cls16, int variant, int step, int tile_y, int tile_z,
                 void* stream);
-// Split step (H then E, in place) of a grid with Debye poles: `dview` is a
-// DebyeView<float> or DebyeView<double>.
 // Oblique wires, before the field pass.  launch_owire_iq: the segment
 // currents of step `step` from the input E (from_e1 = 0) or from the edge
 // values of launch_owire_e1 (from_e1 = 1), then the charges; the record.
@@ -152,15 +150,17 @@ int launch_step(int prec, const void* view, int cls16, int variant, int step, in
 int launch_owire_iq(int prec, const void* view, const OWireView* ow, int step, int from_e1, void* stream);
 int launch_owire_amp(int prec, const void* view, int cls16, const OWireView* ow, int step, void* stream);
 int launch_owire_e1(int prec, const void* view, int cls16, const OWireView* ow, int step, void* stream);
+// Split step (H then E, in place) of a grid with Debye poles: `dview` is a
+// DebyeView<float> or DebyeView<double>.
 int launch_step_debye(int prec, const void* view, const void* dview, int cls16, int step, void* stream);
-// Fused one-step pass (reads one field set, writes the other) of a grid with
-// Debye poles (fdtd_debye.hip): over the 4-group tile list `tiles` / counts
-// (as for launch_lists_step, 8-row tiles; groups 1-3 on
-// `stream2`) or, with tiles == nullptr, over 64 x 8 tiles of tile_z planes.
 // One two-step pass in Debye media (FP32, 1-byte classes): currents from the
 // view's set to the one at jout, arrays `pitch` values apart.
 int launch_tb2_debye(const void* view, const void* dview, const void* jout, size_t pitch, int step, int kz, int run,
                      int prev, void* stream);
+// Fused one-step pass (reads one field set, writes the other) of a grid with
+// Debye poles (fdtd_debye.hip): over the 4-group tile list `tiles` / counts
+// (as for launch_lists_step, 8-row tiles; groups 1-3 on `stream2`) or, with
+// tiles == nullptr, over 64 x 8 tiles of tile_z planes.
 int launch_fused_debye(int prec, const void* view, const void* dview, int cls16, int step, int tile_z,
                        const void* tiles, const int* counts, void* stream, void* stream2);
 
@@ -183,7 +183,8 @@ int launch_probes(int prec, const void* view, int step, void* stream);
 // or 12) over kz planes, taken by the XCDs in runs of `run` tiles.  The
 // launch also records the probes of `step` and, with prev != 0, those of
 // `step` - 1 (the input set's); those of `step` + 1 are left to the next
-// pass's prev or to launch_probes.
+// pass's prev or to launch_probes.  (More than PR_MANY probes: by a launch of
+// their own before the pass.)
 int launch_tb2_pass(int prec, const void* view, int cls16, int step, int ty, int kz, int run, int prev, void* stream);
 
 // Batched step over a tile list.  `views` is a device array of GridView (one

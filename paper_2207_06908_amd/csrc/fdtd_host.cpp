@@ -1466,11 +1466,12 @@ int ensure_tiles(fdtd_ctx* c, int ty, int kz) {
 //    take it nb / 256 times and half a round for the ragged end.  Chunks past
 //    40 planes (20 in 12-row tiles) no longer gain: the blocks of an XCD
 //    drift apart and share fewer halo lines in its L2 (512 x 512 x 384, 12
-//    rows: 20 planes 764, 32 808, 64 860 us).
+//    rows, before the CPML values came in pairs, as below: 20 planes 764, 32
+//    808, 64 860 us; 20 take 743 now).
 //  - An XCD takes about three rows of tiles in a row (neighbours in x and y
 //    share its L2), an odd number of tiles, so that the slower tiles of the
 //    x slabs do not meet the same CUs in every round (203 x 157 x 131, 4
-//    tiles a row: 12 in a row 59, 5 and 7 50 us; 512 x 512 x 384: 27 764, 9
+//    tiles a row: 12 in a row 59, 5 and 7 50 us, 46 now; 512 x 512 x 384: 27 764, 9
 //    782, 36 797, 1 824 us).
 //  - In Debye media a tile's time depends on where it lies: with one round of
 //    blocks the soil tiles in the CPML set it, 3.8 us a plane, with several
@@ -1698,7 +1699,8 @@ int capture_graph(fdtd_ctx* c, int variant, bool lists, int lty) {
     hipError_t he = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking);
     if (he != hipSuccess) return hip_fail(c, he, "capture stream");
   }
-  const int cur0 = c->cur, jcur0 = c->jcur, slot = graph_slot(c), G = c->graph_steps, adv = variant == FDTD_KERNEL_TB2 ? 2 : 1;
+  const int cur0 = c->cur, jcur0 = c->jcur, slot = graph_slot(c);
+  const int G = c->graph_steps, adv = variant == FDTD_KERNEL_TB2 ? 2 : 1;
   const int* dstep = (const int*)(c->ws + c->off_dstep);
   hipError_t he = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal);
   if (he != hipSuccess) return hip_fail(c, he, "begin capture");

@@ -165,7 +165,9 @@ __global__ __launch_bounds__(TX * TY) void k_fused_batch(const GridView<T>* __re
 }
 
 // ---------------------------------------------------------------------------
-// temporally blocked variant: two steps per pass
+// temporally blocked variant: two steps per pass.  Most tiles are those of
+// fdtd_march.h; this is the one of FP64 grids in the CPML slabs (tb2_tile),
+// one plane of every stage at a time.
 //
 // Block = TY + 4 waves; wave v, lane u own the point x = i0 - 2 + u,
 // y = j0 - 2 + v of a 64 x (TY + 4) region around the 60 x TY output tile
@@ -448,7 +450,8 @@ constexpr int tb2_waves(int size, bool pml, int ty) { return size == 8 ? 1 : pml
 // probes (sample `step` recomputed from the input set and, with `prev`, the
 // previous pass's second sample, step - 1, which is the input set itself),
 // the others march one 60 x TY tile over kz planes.  The probes of a pass's
-// last step are left to the next pass or to k_probes after the last one.
+// last step are left to the next pass or to k_probes after the last one; more
+// than PR_MANY probes are k_probes_tb2's, npb 0.
 // `run`: tiles that an XCD takes in a row (xcd_runs).
 template <typename T, typename CI, bool PML, int TY>
 __global__ __launch_bounds__(64 * (TY + 4), tb2_waves(sizeof(T), PML, TY)) void k_tb2(GridView<T> g, int step, int kz,
@@ -779,9 +782,8 @@ hipError_t step_fused(const GridView<T>& g, int step, int tile_y, int tile_z, hi
 
 // Tile groups of a grid with a CPML, by the slabs a tile (halo included)
 // reaches: 0 neither the x nor the y slabs (z CPML code only), 1 x slabs, 2
-// y slabs, 3 both (x-y corners).  Fused tiles are 32 wide in groups 1 and 3
-// and 64 wide otherwise; two-step tiles are 60 wide.  FP64 (a diagnostic
-// precision) keeps the all-axes instantiation for every group.
+// y slabs, 3 both (x-y corners).  Tiles of the fused pass, 32 wide in groups 1
+// and 3 and 64 wide otherwise.  FP64 (a diagnostic precision) keeps the all-axes instantiation for every group.
 template <typename T, typename CI, int TY>
 hipError_t launch_lists(const GridView<T>& g, int step, const int4* tiles, const int* counts, hipStream_t st,
                         hipStream_t st2, void* ev_src) {
@@ -833,8 +835,8 @@ hipError_t launch_tb2(const GridView<T>& g, int step, int kz, int run, int prev,
   const long long nb = (long long)ntx * nty * ntz + npb;
   if (nb > 0x7fffffff || (sizeof(CI) == 1 && g.ncls > 256)) return hipErrorInvalidValue;
   if (many)
-    hipLaunchKernelGGL((k_probes_tb2<T, CI, PML, false>), dim3((unsigned)g.n_probe), dim3(PR_NT), 0, st, g, MarchDebye<T>{},
-                       step, prev);
+    hipLaunchKernelGGL((k_probes_tb2<T, CI, PML, false>), dim3((unsigned)g.n_probe), dim3(PR_NT), 0, st, g,
+                       MarchDebye<T>{}, step, prev);
   hipLaunchKernelGGL((k_tb2<T, CI, PML, TY>), dim3((unsigned)nb), dim3(64 * (TY + 4)), 0, st, g, step, kz, ntx, nty,
                      npb, prev, run);
   return hipGetLastError();

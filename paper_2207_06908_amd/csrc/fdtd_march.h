@@ -21,18 +21,20 @@ namespace mi355fdtd {
 // through LDS: E^n (x, z) for A, H^{n+1/2} (x, z) for B, E^{n+1} (x, z) for C,
 // H^{n+3/2} (x, z) for D.
 //
-// One block runs on a CU at a time (58 KB of LDS, up to 16 waves of at most
-// 128 registers), and with everything in the caches a plane costs what its
+// One block of a tile in the CPML or of 12 rows runs on a CU at a time (up to 16
+// waves of at most 128 registers; FP32 tiles of 8 rows without CPML code stay
+// below 80, and two of 12 waves share a CU; 48 KB of LDS for 8 rows, 58 for 12,
+// 124 and 155 in FP64), and with everything in the caches a plane costs what its
 // instructions cost, so the loop is built to issue few: uniform bases with
 // one 32-bit offset per plane; points and planes outside the grid are not
 // branched around (their coefficients are the table's zero row); registers
 // rotate by name over three unrolled iterations, not by copies; what is
-// needed rarely is read again where it is needed (ColdView).  A lane outside a stage's region
-// computes a value that no lane inside reads.
+// needed rarely is read again where it is needed (ColdView).  A lane outside a
+// stage's region computes a value that no lane inside reads.
 //
 // Measured (us per step, against one launch per CPML group of 8-row tiles
 // with three barriers, four LDS planes and 2.5 times the instructions):
-// 512 x 512 x 384 with a 10-cell CPML 743 (891), 203 x 157 x 131 44 (116),
+// 512 x 512 x 384 with a 10-cell CPML 743 (891), 203 x 157 x 131 46 (116),
 // 96 x 96 x 80 14.5 (82), 48^3 without one 4.3 (38, the fused pass).  In the
 // caches a plane of an 8-row tile takes 0.92 us clear of the CPML and 1.7 us
 // in it; on the largest grid 12 rows take 2 us, bound by the 5 TB/s that
