@@ -1506,41 +1506,46 @@ Tb2Shape tb2_shape(const fdtd_ctx* c) {
 // Debye media: us per step of the two-step pass and of the split pass, for
 // AUTO's choice between them.
 //
-// The two-step pass takes what its blocks take on the device: an XCD's blocks,
-// every eighth one, go in order to the first free of its 32 CUs.  A plane of
-// a tile clear of the CPML costs 0.64 us and one in it 1.42; poles add 0.4 and
-// 0.11 each, and 0.6 in the kernel of three and four.  A block that finds no
-// free CU waits for a light tile where there is one, so the time steps up
-// where nearly all tiles hold poles (100 x 100 x 80 with four: 26 us with
-// 3/4 of the planes, 42 with all).  A probe block takes 5 us, a pass 7.9 more
-// and 0.105 a MB for its fields, CPML state and currents.
+// The two-step pass takes what its blocks take on the device.  Every eighth
+// block goes to an XCD and there every fourth of those to a shader engine,
+// to the first free of its 8 CUs.  A plane of a tile clear of the CPML costs
+// 0.70 us, of one in the z slabs 1.08 and in others 1.46; poles add 0.44 and
+// 0.11 each, and 0.57 in the kernel of three and four; a tile 0.8 more, a
+// probe block 5.  A block that finds no free CU waits for a light tile where
+// there is one, so the time steps up where nearly all tiles hold poles (100 x
+// 100 x 80 with four: 26 us with 3/4 of the planes, 42 with all).  Past 210 MB
+// of fields, CPML state and currents tiles slow one another by 8% per 100 MB;
+// a pass takes 8.5 us more and 0.056 a MB.
 //
-// The split pass: 9 us and, a million nodes, 11.9, 7.8 for the share in the
-// CPML and 3.75 a pole for the share with poles.
+// The split pass takes x = 12.9 us a million nodes, 9.2 for the share in the
+// CPML and 3.7 a pole for the share with poles, 0 to 70% more from 230 to 430
+// MB, hidden at first behind the latency of its launches: 11.2 us replayed
+// from a graph, 15.5 where the host launches them.
 //
-// Against 1,344 grids of 4,000 to 9.9M nodes with 0 to 25 layers, one to four
-// poles in 1/40 to all of the planes, both are 6% wide (standard deviation).
+// Over 8,500 grids of 4,000 to 4M nodes (sides of 16 to 384, 0 to 20 layers,
+// one to four poles in one to all of the planes) either is 5% wide (standard
+// deviation).
 double two_step_us(fdtd_ctx* c, const Tb2Shape& sh) {
   if (c->two_kz == sh.kz) return c->two_us;
   const int nx = c->N[0], ny = c->N[1], nz = c->N[2], np = c->P.npml;
   const int ntx = (nx + 59) / 60, nty = (ny + 7) / 8, nt = ntx * nty * ((nz + sh.kz - 1) / sh.kz);
   const int npb = c->probes.size() > PR_MANY ? 0 : ((int)c->probes.size() + 2) / 3, p = c->npole;
-  const double pole = 0.4 + 0.11 * p + (p > 2 ? 0.6 : 0.0);
+  const double pole = 0.44 + 0.11 * p + (p > 2 ? 0.57 : 0.0);
   double last = 0;
-  std::priority_queue<double, std::vector<double>, std::greater<double>> cu[8];
+  std::priority_queue<double, std::vector<double>, std::greater<double>> cu[32];
   for (int b = 0; b < npb + nt; ++b) {
     double us = 5.0;
     if (b >= npb) {
       const int q = xcd_runs(b - npb, nt, sh.run), i0 = q % ntx * 60, col = q % (ntx * nty), j0 = col / ntx * 8;
       const int k0 = q / (ntx * nty) * sh.kz, k1 = std::min(k0 + sh.kz, nz);
-      const bool clear = np == 0 || (i0 - 2 >= np && i0 + 62 <= nx - np && j0 - 2 >= np && j0 + 10 <= ny - np &&
-                                     k0 - 2 >= np && k1 < nz - np);
-      us = (k1 - k0 + 4) * (clear ? 0.64 : 1.42);
+      const bool cxy = np == 0 || (i0 - 2 >= np && i0 + 62 <= nx - np && j0 - 2 >= np && j0 + 10 <= ny - np);
+      const bool cz = np == 0 || (k0 - 2 >= np && k1 < nz - np);
+      us = 0.8 + (k1 - k0 + 4) * (!cxy ? 1.46 : cz ? 0.70 : 1.08);
       for (int k = std::max(k0 - 1, 0); k <= std::min(k1, nz - 1); ++k)
         if (c->pole_cols[(size_t)k * nty * ntx + col]) us += pole;
     }
-    auto& h = cu[b & 7];
-    if (h.size() == 32) {
+    auto& h = cu[(b & 7) * 4 + (b >> 3 & 3)];
+    if (h.size() == 8) {
       us += h.top();
       h.pop();
     }
@@ -1551,12 +1556,14 @@ double two_step_us(fdtd_ctx* c, const Tb2Shape& sh) {
   for (const size_t e : c->psi_elems) psi += (double)e;
   const double mb = 4e-6 * (13.0 * (double)c->ncell + 6.0 * p * (double)c->debye_nodes + 8.0 * psi);
   c->two_kz = sh.kz;
-  return c->two_us = 0.5 * (7.9 + last + 0.105 * mb);
+  return c->two_us = 0.5 * (8.5 + last * (1.0 + 0.0008 * std::max(0.0, mb - 210.0)) + 0.056 * mb);
 }
 double split_us(const fdtd_ctx* c) {
-  const double np2 = 2.0 * c->P.npml, n = (double)c->ncell;
-  const double in = (c->N[0] - np2) * (c->N[1] - np2) * (c->N[2] - np2);
-  return 9.0 + 1e-6 * (11.9 * n + 7.8 * (n - in) + 3.75 * c->npole * (double)c->debye_nodes);
+  const double np2 = 2.0 * c->P.npml, n = 1e-6 * (double)c->ncell, poles = 1e-6 * c->npole * (double)c->debye_nodes;
+  const double in = 1e-6 * (c->N[0] - np2) * (c->N[1] - np2) * (c->N[2] - np2);
+  const double x = 12.9 * n + 9.2 * (n - in) + 3.7 * poles, mb = 4.0 * (6.0 * n + 3.0 * poles + 4.0 * (n - in));
+  const double launch = c->graph_steps > 0 ? 11.2 : 15.5, hidden = c->graph_steps > 0 ? 3.4 : 10.0;
+  return launch + std::hypot(x, hidden) - hidden + 0.7 * x * std::min(1.0, std::max(0.0, (mb - 230.0) / 200.0));
 }
 
 // Record the probes of step - 1 from the current field set, where the
@@ -1755,20 +1762,18 @@ int fdtd_step(fdtd_ctx* c, int n) {
   if (chosen == FDTD_KERNEL_TB2 && !tb2_ok) chosen = FDTD_KERNEL_FUSED;
   if (c->npole && !c->owr.empty()) return fail(c, FDTD_EINVAL, "oblique wires in a grid with Debye media");
   // Debye media: the two-step pass where it can run and is the faster one,
-  // else the split pass, or the fused pass when asked for.  Past 4M nodes the
-  // split pass is never the faster by more than it varies.  Below, the
-  // two-step pass is taken where it is expected to be 5% faster or more: of
-  // the 1,344 grids, replayed from graphs, 9 are then more than 10% slower
-  // than by the split pass (19% at the most), and the mean one is 2.4% above
-  // the better of the two.
+  // else the split pass, or the fused pass when asked for.  Past 6.5M nodes the
+  // split pass is hardly ever the faster.  Of 5,559 drawn grids below 4M nodes
+  // 13 (18 replayed from graphs) are more than 10% slower than by the split
+  // pass, 21% at the most; the mean one is 0.7% above the better of the two.
   // us per step, two-step / split: 96^3 without a CPML, four poles in half of
   // it 17.8 / 24.9; 100 x 100 x 80, four poles in 3/4 26.1 / 30.6, in all 42.2
-  // / 32.7, one pole in 1/4 24.5 / 21.1; 130 x 130 x 100 with two poles in
-  // half of it 36.8 / 42.7; 512 x 512 x 384 with four 1,547 / 2,573.
+  // / 32.7, one pole in 1/4 24.5 / 21.1; 130 x 130 x 100 with two poles in half
+  // of it 36.8 / 42.7; 512 x 512 x 384 with four 1,547 / 2,573.
   if (c->npole) {
     const bool two = chosen == FDTD_KERNEL_TB2 && c->jsets == 2 &&
-                     (c->variant == FDTD_KERNEL_TB2 || c->ncell > 4000000 ||
-                      two_step_us(c, tb2_shape(c)) < 0.95 * split_us(c));
+                     (c->variant == FDTD_KERNEL_TB2 || c->ncell > 6500000 ||
+                      two_step_us(c, tb2_shape(c)) < split_us(c));
     chosen = c->variant == FDTD_KERNEL_FUSED ? FDTD_KERNEL_FUSED : two ? FDTD_KERNEL_TB2 : FDTD_KERNEL_SPLIT;
   }
   c->probe_due = false;
