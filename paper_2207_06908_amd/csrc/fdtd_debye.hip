@@ -71,9 +71,7 @@ void tb2_debye(const GridView<float>& g, const MarchDebye<float>& db, int step, 
   const int ntx = (g.nx + 59) / 60, nty = (g.ny + 7) / 8, ntz = (g.nz + kz - 1) / kz;
   const int npb = many ? 0 : (g.n_probe + 2) / 3;
   const dim3 grid((unsigned)(ntx * nty * ntz + npb)), block(768);
-  if (many)
-    hipLaunchKernelGGL((k_probes_tb2<float, uint8_t, PML, true>), dim3((unsigned)g.n_probe), dim3(PR_NT), 0, st, g,
-                       db, step, prev);
+  if (many) probes_tb2<float, uint8_t, PML, true>(g, db, step, prev, st);
   if (db.npole <= 2)
     hipLaunchKernelGGL((k_tb2_debye<PML, 2>), grid, block, 0, st, g, db, step, kz, ntx, nty, npb, prev, run);
   else

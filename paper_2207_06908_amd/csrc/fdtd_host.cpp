@@ -1515,12 +1515,15 @@ Tb2Shape tb2_shape(const fdtd_ctx* c) {
 // there is one, so the time steps up where nearly all tiles hold poles (100 x
 // 100 x 80 with four: 26 us with 3/4 of the planes, 42 with all).  Past 210 MB
 // of fields, CPML state and currents tiles slow one another by 8% per 100 MB;
-// a pass takes 8.5 us more and 0.056 a MB.
+// a pass takes 8.5 us more and 0.056 a MB.  More than PR_MANY probes add 7.5 us
+// a step, 0.25 a thousand and 0.018 a thousand of their terms (k_probes_tb2).
 //
 // The split pass takes x = 12.9 us a million nodes, 9.2 for the share in the
 // CPML and 3.7 a pole for the share with poles, 0 to 70% more from 230 to 430
 // MB, hidden at first behind the latency of its launches: 11.2 us replayed
-// from a graph, 15.5 where the host launches them.
+// from a graph, 15.5 where the host launches them.  A thousand probes add 0.8.
+// (38 x 115 x 30, four poles, two-step / split: 4,000 values 20.4 / 17.6,
+// 20,000 22.3 / 26.6, 20,000 lines of 35 terms 38.9 / 30.3.)
 //
 // Over 8,500 grids of 4,000 to 4M nodes (sides of 16 to 384, 0 to 20 layers,
 // one to four poles in one to all of the planes) either is 5% wide (standard
@@ -1555,15 +1558,16 @@ double two_step_us(fdtd_ctx* c, const Tb2Shape& sh) {
   double psi = 0;
   for (const size_t e : c->psi_elems) psi += (double)e;
   const double mb = 4e-6 * (13.0 * (double)c->ncell + 6.0 * p * (double)c->debye_nodes + 8.0 * psi);
+  const double many = c->probes.size() > PR_MANY ? 7.5 + 2.5e-4 * c->probes.size() + 1.8e-5 * c->term_w.size() : 0.0;
   c->two_kz = sh.kz;
-  return c->two_us = 0.5 * (8.5 + last * (1.0 + 0.0008 * std::max(0.0, mb - 210.0)) + 0.056 * mb);
+  return c->two_us = many + 0.5 * (8.5 + last * (1.0 + 0.0008 * std::max(0.0, mb - 210.0)) + 0.056 * mb);
 }
 double split_us(const fdtd_ctx* c) {
   const double np2 = 2.0 * c->P.npml, n = 1e-6 * (double)c->ncell, poles = 1e-6 * c->npole * (double)c->debye_nodes;
   const double in = 1e-6 * (c->N[0] - np2) * (c->N[1] - np2) * (c->N[2] - np2);
   const double x = 12.9 * n + 9.2 * (n - in) + 3.7 * poles, mb = 4.0 * (6.0 * n + 3.0 * poles + 4.0 * (n - in));
   const double launch = c->graph_steps > 0 ? 11.2 : 15.5, hidden = c->graph_steps > 0 ? 3.4 : 10.0;
-  return launch + std::hypot(x, hidden) - hidden + 0.7 * x * std::min(1.0, std::max(0.0, (mb - 230.0) / 200.0));
+  return 8e-4 * c->probes.size() + launch + std::hypot(x, hidden) - hidden + 0.7 * x * std::min(1.0, std::max(0.0, (mb - 230.0) / 200.0));
 }
 
 // Record the probes of step - 1 from the current field set, where the
@@ -1602,8 +1606,8 @@ int launch_pass(fdtd_ctx* c, hipStream_t st, int variant, bool lists, int lty, i
   // Oblique wires: the currents of the pass's (first) step from its input E
   // and their source amplitudes; for a two-step pass also E^{n+1} at the
   // touched edges, the currents of the second step from it, and their
-  // amplitudes.  Over tile lists they run on the second stream, ahead of
-  // the tiles that read the amplitudes (group 4), beside the others.
+  // amplitudes.  Over tile lists they run on a third stream, ahead of the
+  // tiles that read the amplitudes (group 4), beside the others.
   auto wires = [&](hipStream_t ws) -> int {
     const int p = c->P.precision, c16 = c->cls16;
     const OWireView* w = &c->ow_view;

@@ -834,9 +834,7 @@ hipError_t launch_tb2(const GridView<T>& g, int step, int kz, int run, int prev,
   const int npb = many ? 0 : (g.n_probe + GRP - 1) / GRP;
   const long long nb = (long long)ntx * nty * ntz + npb;
   if (nb > 0x7fffffff || (sizeof(CI) == 1 && g.ncls > 256)) return hipErrorInvalidValue;
-  if (many)
-    hipLaunchKernelGGL((k_probes_tb2<T, CI, PML, false>), dim3((unsigned)g.n_probe), dim3(PR_NT), 0, st, g,
-                       MarchDebye<T>{}, step, prev);
+  if (many) probes_tb2<T, CI, PML, false>(g, MarchDebye<T>{}, step, prev, st);
   hipLaunchKernelGGL((k_tb2<T, CI, PML, TY>), dim3((unsigned)nb), dim3(64 * (TY + 4)), 0, st, g, step, kz, ntx, nty,
                      npb, prev, run);
   return hipGetLastError();

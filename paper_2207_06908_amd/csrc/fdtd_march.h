@@ -665,20 +665,72 @@ __device__ __forceinline__ void probe_one(const GridView<T>& g, int p, int step,
   if (t == 0 && p >= 0) g.pr_out[(long long)p * g.max_steps + step] = acc;
 }
 
-// Both samples of a pass with more than PR_MANY probes, one block each, in a
-// launch of its own before the pass.  (The pass's own blocks hold the LDS of a
-// tile, one to a CU, and three probes each: the faster way while they are a
-// few rounds.  96 x 96 x 80, us a step in the pass / apart: 300 probes 19 / 24,
-// 1,000 23.3 / 22.5, 3,000 34 / 24, 10,000 68 / 40, 100,000 492 / 246; a batch
-// of 64 grids with 30 probes each 311 / 311, with 300 416 / 363, with 1,000
-// 688 / 496.)
+// Both samples of a pass with more than PR_MANY probes, in a launch of its own
+// before the pass.  (The pass's own blocks hold the LDS of a tile, one to a CU,
+// and three probes each: the faster way while they are a few rounds.)  Most
+// probes of so many are single values: the first `nlane` blocks take those, a
+// lane each, 1 << lw of them a wave; the others take the rest, a wave each,
+// summed in probe_sum's order (the 0.0 of threads without a term changes no
+// bit).
 template <typename T, typename CI, bool PML, bool DB>
-__global__ __launch_bounds__(PR_NT) void k_probes_tb2(GridView<T> g, MarchDebye<T> db, int step, int prev) {
+__global__ __launch_bounds__(PR_NT) void k_probes_tb2(GridView<T> g, MarchDebye<T> db, int step, int prev, int nlane,
+                                                      int lw) {
   step = gstep(g, step);
-  __shared__ double red[8];
-  if ((int)blockIdx.x >= g.n_probe) return;  // uniform per block
-  probe_tb2<T, CI, PML>(g, blockIdx.x, step, (int)threadIdx.x, red, DB ? &db : nullptr);
-  if (prev) probe_one(g, blockIdx.x, step - 1, (int)threadIdx.x, red + 4);
+  const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  // term q, added to both samples' sums
+  auto term = [&](int q, double acc[2]) {
+    const int c = g.term_comp[q], cc = c < 3 ? c : c - 3;
+    const unsigned n = (unsigned)g.term_idx[q];
+    const double w = g.term_w[q];
+    if (prev) {
+      const T* f = c == 0 ? g.fi[0] : c == 1 ? g.fi[1] : c == 2 ? g.fi[2] : c == 3 ? g.fi[3] : c == 4 ? g.fi[4] : g.fi[5];
+      acc[1] += w * (double)ldg(f, n);
+    }
+    const int x = (int)(n % g.nx), y = (int)((n / g.nx) % g.ny), k = (int)(n / g.sxy);
+    T v3[3];
+    if (c < 3) e1_at<T, CI, PML>(g, x, y, k, step, v3, DB ? &db : nullptr);
+    else h1_at<T, CI, PML>(g, x, y, k, v3);
+    acc[0] += w * (double)(cc == 0 ? v3[0] : cc == 1 ? v3[1] : v3[2]);
+  };
+  auto record = [&](int p, const double sum[2]) {
+    double* out = g.pr_out + (long long)p * g.max_steps + step;
+    out[0] = sum[0];
+    if (prev) out[-1] = sum[1];
+  };
+  double sum[2] = {0.0, 0.0};
+  if ((int)blockIdx.x < nlane) {
+    const int p = ((int)(blockIdx.x * (PR_NT / 64) + wave) << lw) + lane;
+    if (lane >> lw || p >= g.n_probe) return;
+    const int q0 = g.pr_off[p];
+    if (g.pr_off[p + 1] - q0 != 1) return;
+    term(q0, sum);
+    record(p, sum);
+    return;
+  }
+  const int p = ((int)blockIdx.x - nlane) * (PR_NT / 64) + wave;
+  if (p >= g.n_probe) return;
+  const int q0 = g.pr_off[p], q1 = g.pr_off[p + 1];
+  if (q1 - q0 == 1) return;
+  for (int q = q0; q < q1 && q < q0 + PR_NT; q += 64) {
+    double acc[2] = {0.0, 0.0};
+    for (int r = q + lane; r < q1; r += PR_NT) term(r, acc);
+    for (int u = 0; u < 2; ++u) {
+      for (int o = 32; o > 0; o >>= 1) acc[u] += __shfl_down(acc[u], o, 64);
+      sum[u] += acc[u];
+    }
+  }
+  if (lane == 0) record(p, sum);
+}
+
+// Its launch: up to 4,096 waves of single values.
+template <typename T, typename CI, bool PML, bool DB>
+void probes_tb2(const GridView<T>& g, const MarchDebye<T>& db, int step, int prev, hipStream_t st) {
+  constexpr int W = PR_NT / 64;
+  int lw = 0;
+  while (lw < 6 && g.n_probe >> lw > 4096) ++lw;
+  const int nlane = (g.n_probe + (W << lw) - 1) / (W << lw), nwave = (g.n_probe + W - 1) / W;
+  hipLaunchKernelGGL((k_probes_tb2<T, CI, PML, DB>), dim3((unsigned)(nlane + nwave)), dim3(PR_NT), 0, st, g, db, step,
+                     prev, nlane, lw);
 }
 
 }  // namespace mi355fdtd
