@@ -201,12 +201,15 @@ int launch_batch_probes(int prec, const void* views, const void* plist, int n, c
 // i0 | iw << 16, j0 | jh << 16, k0 | kz << 16) of 60 x 8 tiles, taken by the
 // XCDs in runs of `run`.  Steps *d_step + offset and + 1.  The probes of the
 // (grid, probe) pairs of `plist` as in launch_tb2_pass.
-int launch_batch_pass(int prec, int cls16, const void* views, const void* tiles, int n_tiles, const void* plist,
-                      int n_probes, const int* d_step, int offset, int prev, int run, void* stream);
+int launch_batch_pass(int prec, int cls16, int ncls, const void* views, const void* tiles, int n_tiles,
+                      const void* plist, int n_probes, const int* d_step, int offset, int prev, int run, void* stream);
 // *d += v on the stream (advances the device step counter).
 int launch_add(int* d, int v, void* stream);
 // *d = v on the stream.
 int launch_set(int* d, int v, void* stream);
+// Classes in the LDS tables of two-step tiles of FP32 grids with 2-byte ids:
+// what a block to a CU leaves room for, and what two of 8 rows do.
+constexpr int TB2_NC1 = 2048, TB2_NC2 = 768;
 // A two-step pass records up to this many probes itself (k_probes_tb2).
 constexpr int PR_MANY = 2048;
 // Block b of nb (dealt to the 8 XCDs round robin) takes list entry

@@ -1460,7 +1460,8 @@ int ensure_tiles(fdtd_ctx* c, int ty, int kz) {
 //    ones 1.5, but their x-y corner tiles spill at the 128 registers that 16
 //    waves leave, which small grids, nearly all slabs, feel.  us per step,
 //    12 rows / 8 rows: 512 x 512 x 384 743 / 790, 384 x 384 x 288 338 / 348,
-//    304 x 305 x 230 222 / 213, 96 x 96 x 80 22 / 14.5.
+//    304 x 305 x 230 222 / 213, 96 x 96 x 80 22 / 14.5.  (Not with the classes'
+//    table in memory: two 8-row blocks of that tile share a CU.)
 //  - Planes per chunk: one block runs on a CU at a time, so up to 256 blocks
 //    take one chunk's march (its planes and about 4 of pipeline), and more
 //    take it nb / 256 times and half a round for the ragged end.  Chunks past
@@ -1483,7 +1484,8 @@ struct Tb2Shape {
 };
 Tb2Shape tb2_shape(const fdtd_ctx* c) {
   Tb2Shape s;
-  s.ty = c->npole ? 8 : c->tile_y ? c->tile_y : c->P.precision == 32 && c->ncell >= (40ll << 20) ? 12 : 8;
+  const bool tall = c->P.precision == 32 && c->ncell >= (40ll << 20) && c->ncls <= TB2_NC1;
+  s.ty = c->npole ? 8 : c->tile_y ? c->tile_y : tall ? 12 : 8;
   const int ntx = (c->N[0] + 59) / 60, nty = (c->N[1] + s.ty - 1) / s.ty, nz = c->N[2];
   const long long probes = c->probes.size() > PR_MANY ? 1 : (long long)c->probes.size() / 3 + 1;  // their blocks
   s.kz = c->tile_z;
@@ -1997,7 +1999,7 @@ const char* fdtd_last_error(const fdtd_ctx* c) { return c ? c->err.c_str() : "nu
 struct fdtd_batch {
   std::vector<fdtd_ctx*> grids;
   hipStream_t stream = nullptr;
-  int prec = 32, cls16 = 0, pml = 0;
+  int prec = 32, cls16 = 0, pml = 0, ncls = 0;  // (ncls: the most of a grid)
   int tx = 32, ty = 8, kz = 32;
   int max_steps = 0;
   std::string err;
@@ -2066,15 +2068,19 @@ void build_tiles(fdtd_batch* b) {
 // for which 256 blocks at a time take the fewest planes (4 of pipeline a
 // tile), half a round added for the ragged end.  Large batches take tb2_kz
 // itself; 8 grids at tb2_kz 32 run 58 us a step with 32-plane chunks, 47
-// with 24.
+// with 24.  With the classes' tables in memory at most 24, as shorter chunks
+// meet fewer rows of them (64 grids of 17,000 classes, 24 / 32 / 64 planes:
+// FP32 297 / 312 / 329, FP64 470 / 479 / 496).
 void build_tiles_tb2(fdtd_batch* b) {
   std::vector<int> order(b->grids.size());
   for (size_t g = 0; g < order.size(); ++g) order[g] = (int)g;
   std::stable_sort(order.begin(), order.end(),
                    [&](int a, int c) { return b->grids[a]->ncell > b->grids[c]->ncell; });
-  int depth = b->tb2_kz;
+  const bool wide = b->cls16 && (b->prec == 64 || b->ncls > TB2_NC1);
+  const int most = wide ? std::min(b->tb2_kz, 24) : b->tb2_kz;
+  int depth = most;
   double best = 0;
-  for (int kz = std::min(b->tb2_kz, 64); kz >= 8; --kz) {
+  for (int kz = std::min(most, 64); kz >= 8; --kz) {
     double planes = 0, nb = 0, dmax = 0;
     for (const fdtd_ctx* c : b->grids) {
       const int chunks = (c->N[2] + kz - 1) / kz, d = (c->N[2] + chunks - 1) / chunks;
@@ -2086,7 +2092,7 @@ void build_tiles_tb2(fdtd_batch* b) {
     const double cost = nb <= 256 ? dmax : planes / 256 + 0.5 * dmax;
     if (best == 0 || cost < best) {
       best = cost;
-      depth = kz == 64 ? b->tb2_kz : kz;
+      depth = kz == 64 ? most : kz;
     }
   }
   b->tiles2.clear();
@@ -2165,7 +2171,7 @@ int batch_launch_pass(fdtd_batch* b, hipStream_t st, int p, int off) {
   // share an L2 (256 grids: 1 tile 1,317 us a step, 3 1,259, 9 to 129 within
   // 1% of 1,244).
   const int run = 17;
-  int e = launch_batch_pass(b->prec, b->cls16, b->ws + b->off_views + p * nv * vb, b->ws + b->off_tiles2,
+  int e = launch_batch_pass(b->prec, b->cls16, b->ncls, b->ws + b->off_views + p * nv * vb, b->ws + b->off_tiles2,
                             (int)(b->tiles2.size() / 4), b->ws + b->off_plist, (int)(b->plist.size() / 2), d_step, off,
                             b->probe_due ? 1 : 0, run, (void*)st);
   if (e) return bfail(b, FDTD_EDEVICE, std::string("batch pass: ") + hipGetErrorString((hipError_t)e));
@@ -2232,6 +2238,7 @@ int fdtd_batch_pack(fdtd_ctx* const* grids, int n, void* hip_stream, fdtd_batch*
       delete b;
       return FDTD_EINVAL;  // one kernel instantiation serves the whole batch
     }
+    b->ncls = std::max(b->ncls, c->ncls);
     b->max_steps = std::min(b->max_steps, c->P.max_steps);
     b->grids.push_back(c);
     for (size_t q = 0; q < c->probes.size(); ++q) {

@@ -166,8 +166,9 @@ __global__ __launch_bounds__(TX * TY) void k_fused_batch(const GridView<T>* __re
 
 // ---------------------------------------------------------------------------
 // temporally blocked variant: two steps per pass.  Most tiles are those of
-// fdtd_march.h; this is the one of FP64 grids in the CPML slabs (tb2_tile),
-// one plane of every stage at a time.
+// fdtd_march.h; this one (tb2_tile), a plane of every stage at a time, is that
+// of FP64 grids in the CPML slabs and of grids whose classes do not fit March's
+// table in LDS.
 //
 // Block = TY + 4 waves; wave v, lane u own the point x = i0 - 2 + u,
 // y = j0 - 2 + v of a 64 x (TY + 4) region around the 60 x TY output tile
@@ -217,10 +218,10 @@ struct ProfTB2 {
   }
 };
 
-// One two-step tile in the CPML: outputs [i0, i0+iw) x [j0, j0+jh) x [k0, k1)
-// with iw <= 60, jh <= TY.  FP64 grids run their slab tiles through this one,
-// a plane of every stage at a time (tb2_any).
-template <typename T, typename CI, int TY>
+// One two-step tile: outputs [i0, i0+iw) x [j0, j0+jh) x [k0, k1) with iw <= 60,
+// jh <= TY, a plane of every stage at a time (tb2_any); AX masks the axes whose
+// CPML slabs the tile's region reaches.
+template <typename T, typename CI, int TY, int AX, bool TABV>
 __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& sm, int i0, int j0, int iw, int jh,
                                          int k0, int k1, int step) {
   constexpr int TX = 60, NT = 64 * (TY + 4);
@@ -232,7 +233,20 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
   if (LDS_TAB) {
     for (int q = tid; q < g.ncls * K_STRIDE; q += NT) sm.stab[q] = ldg(g.ctab, (unsigned)q);
   }
-  auto coef = [&](int c) -> const T* { return LDS_TAB ? sm.stab + c * K_STRIDE : g.ctab + c * K_STRIDE; };
+  // TABV: the view comes from a table of views, so that the compiler does not
+  // know its pointers for global memory's, and would use FLAT loads
+  T cf[K_STRIDE];
+  auto coef = [&](int c) -> const T* {
+    if constexpr (LDS_TAB) {
+      return sm.stab + c * K_STRIDE;
+    } else if constexpr (!TABV) {
+      return g.ctab + c * K_STRIDE;
+    } else {
+      const auto* row = (const __attribute__((address_space(1))) T*)g.ctab + c * K_STRIDE;
+      for (int q = 0; q < K_NCOEF; ++q) cf[q] = row[q];  // (what a stage does not use is not loaded)
+      return cf;
+    }
+  };
 
   const int x = i0 - 2 + u, y = j0 - 2 + v;
   const bool dom = x >= 0 && x < nx && y >= 0 && y < ny;
@@ -241,20 +255,21 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
   const bool inC = inB && u <= TX + 1 && v <= TY + 1;
   const bool inD = inC && u >= 2 && v >= 2 && u < 2 + iw && v < 2 + jh;
   const unsigned n0 = dom ? (unsigned)x + (unsigned)nx * (unsigned)y : 0u;
-  const int lx = dom ? slab_pos(x, nx, g.npml) : -1;
-  const int ly = dom ? slab_pos(y, ny, g.npml) : -1;
+  const int lx = (AX & 1) && dom ? slab_pos(x, nx, g.npml) : -1;
+  const int ly = (AX & 2) && dom ? slab_pos(y, ny, g.npml) : -1;
   // (E is updated on planes k0 - 1 .. k1: the first step's cone, then the outputs)
   const SrcRange srcr = src_wave(g, n0, inB, k0 - 1, k1);
   const int tn = 2 * g.npml;
-  if (v == 0) {
+  if ((AX & 1) && v == 0) {
     const int xl = x >= 0 && x < nx ? slab_pos(x, nx, g.npml) : -1;
     for (int r = 0; r < P_NROW; ++r) sm.px[r][u] = xl >= 0 ? ldg(g.prof[0], (unsigned)(r * tn + xl)) : T(0);
   }
-  if (u == 0) {
+  if ((AX & 2) && u == 0) {
     const int yl = y >= 0 && y < ny ? slab_pos(y, ny, g.npml) : -1;
     for (int r = 0; r < P_NROW; ++r) sm.py[r][v] = yl >= 0 ? ldg(g.prof[1], (unsigned)(r * tn + yl)) : T(0);
   }
-  for (int q = tid; q < P_NROW * tn; q += NT) sm.pz[q] = ldg(g.prof[2], (unsigned)q);
+  if (AX & 4)
+    for (int q = tid; q < P_NROW * tn; q += NT) sm.pz[q] = ldg(g.prof[2], (unsigned)q);
   const ProfTB2<T, TY> pf{g, sm, u, v};
 
   auto ld_e = [&](int k, T e[3]) {
@@ -311,7 +326,7 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
     // CPML state loaded there is consumed inside it and no wait for it is
     // left at the end of the iteration, where it would also wait for the
     // prefetch and the stores.
-    const int lz = slab_pos(k, nz, g.npml);
+    const int lz = AX & 4 ? slab_pos(k, nz, g.npml) : -1;
     if (inA && kin) {
       auto stage_a = [&](const int l[3]) {
         psi_load(g, 1, l, x, y, k, pshn);
@@ -358,7 +373,7 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
     const int km = k - 1;
     T h2c[3] = {T(0), T(0), T(0)};
     if (inC && k >= k0 && km >= 0 && km < nz) {
-      int l[3] = {lx, ly, slab_pos(km, nz, g.npml)};
+      int l[3] = {lx, ly, AX & 4 ? slab_pos(km, nz, g.npml) : -1};
       h_core_pf<T, true>(pf, l, coef(cp), e1p[0], e1p[1], e1p[2], sm.se1[s1m][0][v + 1][u], e1c[0],
                      sm.se1[s1m][1][v][u + 1], e1c[1], sm.se1[s1m][2][v][u + 1], sm.se1[s1m][2][v + 1][u], h1p, psh[0],
                      psh[1], psh[2], h2c);
@@ -376,7 +391,7 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
     if (inD && km >= k0) {
       const unsigned nst = n0 + sxy * (unsigned)km;
       T e2[3];
-      int l[3] = {lx, ly, slab_pos(km, nz, g.npml)};
+      int l[3] = {lx, ly, AX & 4 ? slab_pos(km, nz, g.npml) : -1};
       e_core_pf<T, true>(pf, l, coef(cp), h2c[0], h2c[1], h2c[2], sm.sh2[0][v - 1][u], h2p[0], sm.sh2[1][v][u - 1],
                         h2p[1], sm.sh2[2][v][u - 1], sm.sh2[2][v - 1][u], e1p, pse[0], pse[1], pse[2], e2);
       e_sources(&g, srcr.first(km), srcr.last(km), nst, step + 1, e2);
@@ -409,42 +424,61 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
 // One tile of a two-step pass by the code its CPML needs: tiles whose region
 // (halo and pipeline planes included) is clear of some slabs leave their code
 // out.  FP64 tiles in the CPML would spill in March's registers; they take
-// the one-plane-at-a-time tile.
-template <typename T, int TY>
+// the one-plane-at-a-time tile.  So do all tiles with the classes' table in
+// memory (NC 0): March, which loads three planes ahead, waits for all of it at
+// each coefficient, four times a plane (us a step, March / tb2_tile / split
+// pass, FP32, 17,000 classes: 203 x 157 x 131 with a CPML 155 / 78 / 86, 384 x
+// 384 x 288 1,500 / 741 / 1,137, without one 1,366 / 723 / 1,101; FP64 320 x
+// 300 x 256 896 / 748 / 1,130).
+template <typename T, int TY, int NC>
 union TileSmem {
-  MarchSmem<T, TY> m;
+  MarchSmem<T, TY, NC> m;
   TB2Smem<T, TY> t;
 };
-template <int TY>
-union TileSmem<float, TY> {
-  MarchSmem<float, TY> m;
+template <int TY, int NC>
+union TileSmem<float, TY, NC> {
+  MarchSmem<float, TY, NC> m;
 };
-template <typename T, typename CI, bool PML, int TY>
-__device__ __forceinline__ void tb2_any(const GridView<T>& g, ColdView<T> cold, TileSmem<T, TY>& sm, int i0, int j0,
+template <int TY>
+union TileSmem<float, TY, 0> {
+  MarchSmem<float, TY, 0> m;
+  TB2Smem<float, TY> t;
+};
+template <typename T, typename CI, bool PML, int TY, int NC, bool TABV>
+__device__ __forceinline__ void tb2_any(const GridView<T>& g, ColdView<T> cold, TileSmem<T, TY, NC>& sm, int i0, int j0,
                                         int iw, int jh, int k0, int k1, int step) {
-  if constexpr (!PML) {
-    March<T, CI, TY, 0>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
+  if constexpr (!PML && NC == 0) {
+    tb2_tile<T, CI, TY, 0, TABV>(g, sm.t, i0, j0, iw, jh, k0, k1, step);
+  } else if constexpr (!PML) {
+    March<T, CI, TY, 0, 0, NC>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
   } else {
     const int n = g.npml;
     const bool cx = i0 - 2 >= n && i0 + 62 <= g.nx - n, cy = j0 - 2 >= n && j0 + TY + 2 <= g.ny - n,
                cz = k0 - 2 >= n && k1 < g.nz - n;
-    if (cx && cy && cz) {
-      March<T, CI, TY, 0>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
+    if constexpr (NC == 0) {
+      if (cx && cy) tb2_tile<T, CI, TY, 4, TABV>(g, sm.t, i0, j0, iw, jh, k0, k1, step);
+      else if (cy) tb2_tile<T, CI, TY, 5, TABV>(g, sm.t, i0, j0, iw, jh, k0, k1, step);
+      else if (cx) tb2_tile<T, CI, TY, 6, TABV>(g, sm.t, i0, j0, iw, jh, k0, k1, step);
+      else tb2_tile<T, CI, TY, 7, TABV>(g, sm.t, i0, j0, iw, jh, k0, k1, step);
+    } else if (cx && cy && cz) {
+      March<T, CI, TY, 0, 0, NC>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
     } else if constexpr (sizeof(T) == 8) {
-      tb2_tile<T, CI, TY>(g, sm.t, i0, j0, iw, jh, k0, k1, step);
+      tb2_tile<T, CI, TY, 7, TABV>(g, sm.t, i0, j0, iw, jh, k0, k1, step);
     } else {
-      if (cx && cy) March<T, CI, TY, 4>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
-      else if (cy) March<T, CI, TY, 5>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
-      else if (cx) March<T, CI, TY, 6>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
-      else March<T, CI, TY, 7>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
+      if (cx && cy) March<T, CI, TY, 4, 0, NC>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
+      else if (cy) March<T, CI, TY, 5, 0, NC>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
+      else if (cx) March<T, CI, TY, 6, 0, NC>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
+      else March<T, CI, TY, 7, 0, NC>(g, cold, sm.m, i0, j0, iw, jh, k0, k1, step);
     }
   }
 }
 
 // Registers a lane may use: FP32 tiles with CPML code take what one block per
-// CU leaves them, tiles without it stay below 80 so that two 12-wave blocks
-// share a CU.
-constexpr int tb2_waves(int size, bool pml, int ty) { return size == 8 ? 1 : pml || ty == 12 ? (ty + 4) / 4 : 6; }
+// CU leaves them; tiles without it, and 8-row ones with their table in memory
+// (64 KB of LDS), stay below 80 so that two 12-wave blocks share a CU.
+constexpr int tb2_waves(int size, bool pml, int ty, int nc) {
+  return size == 8 ? 1 : (nc == 0 && ty == 8) ? 6 : pml || ty == 12 || nc > TB2_NC2 ? (ty + 4) / 4 : 6;
+}
 
 // A whole two-step pass in one launch: blocks 0 .. npb - 1 each record a few
 // probes (sample `step` recomputed from the input set and, with `prev`, the
@@ -453,12 +487,12 @@ constexpr int tb2_waves(int size, bool pml, int ty) { return size == 8 ? 1 : pml
 // last step are left to the next pass or to k_probes after the last one; more
 // than PR_MANY probes are k_probes_tb2's, npb 0.
 // `run`: tiles that an XCD takes in a row (xcd_runs).
-template <typename T, typename CI, bool PML, int TY>
-__global__ __launch_bounds__(64 * (TY + 4), tb2_waves(sizeof(T), PML, TY)) void k_tb2(GridView<T> g, int step, int kz,
-                                                                                   int ntx, int nty, int npb,
-                                                                                   int prev, int run) {
+template <typename T, typename CI, bool PML, int TY, int NC>
+__global__ __launch_bounds__(64 * (TY + 4), tb2_waves(sizeof(T), PML, TY, NC)) void k_tb2(GridView<T> g, int step,
+                                                                                       int kz, int ntx, int nty,
+                                                                                       int npb, int prev, int run) {
   step = gstep(g, step);
-  __shared__ TileSmem<T, TY> sm;
+  __shared__ TileSmem<T, TY, NC> sm;
   constexpr int GRP = 64 * (TY + 4) / PR_NT;  // probes per block
   __shared__ double red[12 * GRP];
   if ((int)blockIdx.x < npb) {  // uniform per block
@@ -472,7 +506,7 @@ __global__ __launch_bounds__(64 * (TY + 4), tb2_waves(sizeof(T), PML, TY)) void 
   const int tile_x = tile % ntx, rest = tile / ntx, k0 = (rest / nty) * kz;
   // the view is the kernel's first argument: read again where it is needed
   const ColdView<T> cold{(typename ColdView<T>::P)__builtin_amdgcn_kernarg_segment_ptr()};
-  tb2_any<T, CI, PML, TY>(g, cold, sm, tile_x * 60, (rest % nty) * TY, 60, TY, k0, min(k0 + kz, g.nz), step);
+  tb2_any<T, CI, PML, TY, NC, false>(g, cold, sm, tile_x * 60, (rest % nty) * TY, 60, TY, k0, min(k0 + kz, g.nz), step);
 }
 
 // Batched two-step pass: as k_tb2 over a tile list that spans every grid
@@ -482,12 +516,12 @@ __global__ __launch_bounds__(64 * (TY + 4), tb2_waves(sizeof(T), PML, TY)) void 
 // grids of 32 to 96 cells a side with an 8-cell CPML: 1179 us a step (1473
 // with one work-queue launch per CPML group and a probe launch); 64 of them
 // 296, 8 of them 47 (80).
-template <typename T, typename CI>
-__global__ __launch_bounds__(768, tb2_waves(sizeof(T), true, 8)) void k_tb2_batch(
+template <typename T, typename CI, int NC>
+__global__ __launch_bounds__(768, tb2_waves(sizeof(T), true, 8, NC)) void k_tb2_batch(
     const GridView<T>* __restrict__ views, const int4* __restrict__ tiles, const int2* __restrict__ plist, int n_probes,
     int npb, const int* __restrict__ d_step, int offset, int prev, int run) {
   const int step = *d_step + offset;
-  __shared__ TileSmem<T, 8> sm;
+  __shared__ TileSmem<T, 8, NC> sm;
   constexpr int GRP = 768 / PR_NT;
   __shared__ double red[12 * GRP];
   if ((int)blockIdx.x < npb) {  // uniform per block
@@ -504,7 +538,7 @@ __global__ __launch_bounds__(768, tb2_waves(sizeof(T), true, 8)) void k_tb2_batc
   const GridView<T> g = uniform_view(views + tx);
   const ColdView<T> cold{(typename ColdView<T>::P)(uintptr_t)(views + tx)};
   const int k0 = tw & 0xffff;
-  tb2_any<T, CI, true, 8>(g, cold, sm, ty & 0xffff, tz & 0xffff, ty >> 16, tz >> 16, k0, k0 + (tw >> 16), step);
+  tb2_any<T, CI, true, 8, NC, true>(g, cold, sm, ty & 0xffff, tz & 0xffff, ty >> 16, tz >> 16, k0, k0 + (tw >> 16), step);
 }
 
 // The batch's probes apart from its pass (as k_probes_tb2).
@@ -826,31 +860,31 @@ hipError_t lists_any(const GridView<T>& g, int cls16, int step, int ty, const in
                : launch_lists<T, uint8_t, 8>(g, step, tiles, counts, st, st2, ev);
 }
 
-template <typename T, typename CI, bool PML, int TY>
+template <typename T, typename CI, bool PML, int TY, int NC>
 hipError_t launch_tb2(const GridView<T>& g, int step, int kz, int run, int prev, hipStream_t st) {
   constexpr int GRP = 64 * (TY + 4) / PR_NT;
   const int ntx = (g.nx + 59) / 60, nty = (g.ny + TY - 1) / TY, ntz = (g.nz + kz - 1) / kz;
   const bool many = g.n_probe > PR_MANY;
   const int npb = many ? 0 : (g.n_probe + GRP - 1) / GRP;
   const long long nb = (long long)ntx * nty * ntz + npb;
-  if (nb > 0x7fffffff || (sizeof(CI) == 1 && g.ncls > 256)) return hipErrorInvalidValue;
+  if (nb > 0x7fffffff || (NC && g.ncls > NC)) return hipErrorInvalidValue;
   if (many) probes_tb2<T, CI, PML, false>(g, MarchDebye<T>{}, step, prev, st);
-  hipLaunchKernelGGL((k_tb2<T, CI, PML, TY>), dim3((unsigned)nb), dim3(64 * (TY + 4)), 0, st, g, step, kz, ntx, nty,
+  hipLaunchKernelGGL((k_tb2<T, CI, PML, TY, NC>), dim3((unsigned)nb), dim3(64 * (TY + 4)), 0, st, g, step, kz, ntx, nty,
                      npb, prev, run);
   return hipGetLastError();
 }
 
-template <typename T, typename CI>
+template <typename T, typename CI, int NC>
 hipError_t step_tb2(const GridView<T>& g, int step, int ty, int kz, int run, int prev, hipStream_t st) {
   const bool pml = g.npml > 0;
   if (ty == 4)
-    return pml ? launch_tb2<T, CI, true, 4>(g, step, kz, run, prev, st)
-               : launch_tb2<T, CI, false, 4>(g, step, kz, run, prev, st);
+    return pml ? launch_tb2<T, CI, true, 4, NC>(g, step, kz, run, prev, st)
+               : launch_tb2<T, CI, false, 4, NC>(g, step, kz, run, prev, st);
   if (ty == 12)
-    return pml ? launch_tb2<T, CI, true, 12>(g, step, kz, run, prev, st)
-               : launch_tb2<T, CI, false, 12>(g, step, kz, run, prev, st);
-  return pml ? launch_tb2<T, CI, true, 8>(g, step, kz, run, prev, st)
-             : launch_tb2<T, CI, false, 8>(g, step, kz, run, prev, st);
+    return pml ? launch_tb2<T, CI, true, 12, NC>(g, step, kz, run, prev, st)
+               : launch_tb2<T, CI, false, 12, NC>(g, step, kz, run, prev, st);
+  return pml ? launch_tb2<T, CI, true, 8, NC>(g, step, kz, run, prev, st)
+             : launch_tb2<T, CI, false, 8, NC>(g, step, kz, run, prev, st);
 }
 
 int launch_tb2_pass(int prec, const void* view, int cls16, int step, int ty, int kz, int run, int prev,
@@ -858,12 +892,18 @@ int launch_tb2_pass(int prec, const void* view, int cls16, int step, int ty, int
   hipStream_t st = (hipStream_t)stream;
   if (prec == 64) {
     const GridView<double>& g = *(const GridView<double>*)view;
-    return (int)(cls16 ? step_tb2<double, uint16_t>(g, step, ty, kz, run, prev, st)
-                       : step_tb2<double, uint8_t>(g, step, ty, kz, run, prev, st));
+    return (int)(cls16 ? step_tb2<double, uint16_t, 0>(g, step, ty, kz, run, prev, st)
+                       : step_tb2<double, uint8_t, 256>(g, step, ty, kz, run, prev, st));
   }
   const GridView<float>& g = *(const GridView<float>*)view;
-  return (int)(cls16 ? step_tb2<float, uint16_t>(g, step, ty, kz, run, prev, st)
-                     : step_tb2<float, uint8_t>(g, step, ty, kz, run, prev, st));
+  // 2-byte ids: the table in LDS as far as it fits (us a step, in memory / in
+  // LDS: 1,300 classes on 203 x 157 x 131 with a CPML 106 / 51, 384 x 384 x 288
+  // with 420 610 / 361; 1,208 on 96 x 96 x 80 24.7 / 15.9)
+  if (cls16 && g.ncls > TB2_NC1) return (int)step_tb2<float, uint16_t, 0>(g, step, ty, kz, run, prev, st);
+  if (!cls16) return (int)step_tb2<float, uint8_t, 256>(g, step, ty, kz, run, prev, st);
+  if (g.ncls <= TB2_NC2 && ty == 8 && g.npml == 0)
+    return (int)launch_tb2<float, uint16_t, false, 8, TB2_NC2>(g, step, kz, run, prev, st);
+  return (int)step_tb2<float, uint16_t, TB2_NC1>(g, step, ty, kz, run, prev, st);
 }
 
 template <typename T>
@@ -960,7 +1000,7 @@ int launch_batch_probes(int prec, const void* views, const void* plist, int n, c
   return (int)hipGetLastError();
 }
 
-template <typename T, typename CI>
+template <typename T, typename CI, int NC>
 hipError_t batch_pass_t(const void* views, const void* tiles, int n_tiles, const void* plist, int n_probes,
                         const int* d_step, int offset, int prev, int run, hipStream_t st) {
   const bool many = n_probes > PR_MANY;
@@ -968,22 +1008,25 @@ hipError_t batch_pass_t(const void* views, const void* tiles, int n_tiles, const
   if (many)
     hipLaunchKernelGGL((k_probes_tb2_batch<T, CI>), dim3((unsigned)n_probes), dim3(PR_NT), 0, st,
                        (const GridView<T>*)views, (const int2*)plist, n_probes, d_step, offset, prev);
-  hipLaunchKernelGGL((k_tb2_batch<T, CI>), dim3((unsigned)(npb + n_tiles)), dim3(768), 0, st,
+  hipLaunchKernelGGL((k_tb2_batch<T, CI, NC>), dim3((unsigned)(npb + n_tiles)), dim3(768), 0, st,
                      (const GridView<T>*)views, (const int4*)tiles, (const int2*)plist, n_probes, npb, d_step, offset,
                      prev, run);
   return hipGetLastError();
 }
 
-int launch_batch_pass(int prec, int cls16, const void* views, const void* tiles, int n_tiles, const void* plist,
+int launch_batch_pass(int prec, int cls16, int ncls, const void* views, const void* tiles, int n_tiles, const void* plist,
                       int n_probes, const int* d_step, int offset, int prev, int run, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   hipError_t e;
+  const auto pass = [&](auto f) {
+    return f(views, tiles, n_tiles, plist, n_probes, d_step, offset, prev, run, st);
+  };
   if (prec == 64)
-    e = cls16 ? batch_pass_t<double, uint16_t>(views, tiles, n_tiles, plist, n_probes, d_step, offset, prev, run, st)
-              : batch_pass_t<double, uint8_t>(views, tiles, n_tiles, plist, n_probes, d_step, offset, prev, run, st);
+    e = pass(cls16 ? batch_pass_t<double, uint16_t, 0> : batch_pass_t<double, uint8_t, 256>);
   else
-    e = cls16 ? batch_pass_t<float, uint16_t>(views, tiles, n_tiles, plist, n_probes, d_step, offset, prev, run, st)
-              : batch_pass_t<float, uint8_t>(views, tiles, n_tiles, plist, n_probes, d_step, offset, prev, run, st);
+    e = pass(cls16 && ncls > TB2_NC1 ? batch_pass_t<float, uint16_t, 0>
+             : !cls16                ? batch_pass_t<float, uint8_t, 256>
+                                     : batch_pass_t<float, uint16_t, TB2_NC1>);
   return (int)e;
 }
 

@@ -24,8 +24,9 @@ namespace mi355fdtd {
 // One block of a tile in the CPML or of 12 rows runs on a CU at a time (up to 16
 // waves of at most 128 registers; FP32 tiles of 8 rows without CPML code stay
 // below 80, and two of 12 waves share a CU; 48 KB of LDS for 8 rows, 58 for 12,
-// 124 and 155 in FP64), and with everything in the caches a plane costs what its
-// instructions cost, so the loop is built to issue few: uniform bases with
+// 124 and 155 in FP64; 72 and 134 with tables of 768 and 2,048 classes), and
+// with everything in the caches a plane costs what its instructions cost, so
+// the loop is built to issue few: uniform bases with
 // one 32-bit offset per plane; points and planes outside the grid are not
 // branched around (their coefficients are the table's zero row); registers
 // rotate by name over three unrolled iterations, not by copies; what is
@@ -42,16 +43,21 @@ namespace mi355fdtd {
 // ---------------------------------------------------------------------------
 
 template <typename T, int TY>
-struct MarchSmem {
+struct MarchRows {
   static constexpr int R = TY + 4;
   static constexpr int PZ = 512 / sizeof(T);  // longest z profile row held here (2 npml)
   T e0[2][R][64];       // E^n (x, z), plane k
   T h1[2][R][64];       // H^{n+1/2} (x, z), plane k
   T e1[2][2][R][64];    // E^{n+1} (x, z), planes k and k-1
   T h2[2][R][64];       // H^{n+3/2} (x, z), plane k-2
-  T stab[257 * K_STRIDE];  // a row of zeros, then the classes' coefficients
   T px[P_NROW][64];     // CPML profile at each lane's x
   T pz[P_NROW * PZ];    // the z table
+};
+// NC: classes whose coefficients fit the LDS table (0: none, they are read from
+// memory at each use).
+template <typename T, int TY, int NC = 256>
+struct MarchSmem : MarchRows<T, TY> {
+  T stab[(NC + 1) * K_STRIDE];  // a row of zeros, then the classes' coefficients
 };
 
 // CPML profile values of a tile's points: a lane's x values in registers
@@ -60,7 +66,7 @@ struct MarchSmem {
 template <typename T, int TY>
 struct ProfMarch {
   static constexpr bool XREG = TY <= 8;
-  const MarchSmem<T, TY>& sm;
+  const MarchRows<T, TY>& sm;
   int tn, u;
   T x[XREG ? P_NROW : 1];
   T y[P_NROW];  // uniform across the wave
@@ -200,15 +206,15 @@ struct MarchRegs {
 // is loaded an iteration before its B; J^{n+1} waits the two iterations from
 // B to D in LDS, in slots that only its own thread touches.  Nodes without a
 // pole term skip all of it.
-template <typename T, typename CI, int TY, int AX, int NP = 0>
+template <typename T, typename CI, int TY, int AX, int NP = 0, int NC = sizeof(CI) == 1 ? 256 : 0>
 struct March {
   static constexpr int TX = 60, NT = 64 * (TY + 4);
-  static constexpr bool LDS_TAB = sizeof(CI) == 1;
+  static constexpr bool LDS_TAB = NC > 0;
   static constexpr bool PML = AX != 0, SX = AX & 1, SY = AX & 2, SZ = AX & 4;
   static constexpr unsigned S = sizeof(T), NONE = 0xFFFFFFFFu;
 
   typedef typename MarchRegs<T>::Pair Pair;
-  MarchSmem<T, TY>& sm;
+  MarchSmem<T, TY, NC>& sm;
   ColdView<T> g;
   const T* fi[6];
   T* fo[6];
@@ -455,7 +461,7 @@ struct March {
     __syncthreads();
   }
 
-  __device__ __forceinline__ March(const GridView<T>& gv, ColdView<T> cold, MarchSmem<T, TY>& sm_, int i0, int j0,
+  __device__ __forceinline__ March(const GridView<T>& gv, ColdView<T> cold, MarchSmem<T, TY, NC>& sm_, int i0, int j0,
                                    int iw, int jh, int k0_, int k1_, int step_,
                                    MarchDebyeSmem<T, TY, NP>* ds_ = nullptr, DebyeArgs<T> db_ = {})
       : sm(sm_), g(cold), nz(gv.nz), np(gv.npml), step(step_), k0(k0_), k1(k1_),
@@ -667,11 +673,17 @@ __device__ __forceinline__ void probe_one(const GridView<T>& g, int p, int step,
 
 // Both samples of a pass with more than PR_MANY probes, in a launch of its own
 // before the pass.  (The pass's own blocks hold the LDS of a tile, one to a CU,
-// and three probes each: the faster way while they are a few rounds.)  Most
-// probes of so many are single values: the first `nlane` blocks take those, a
-// lane each, 1 << lw of them a wave; the others take the rest, a wave each,
-// summed in probe_sum's order (the 0.0 of threads without a term changes no
-// bit).
+// and three probes each: a launch less, and the faster way while they are a few
+// rounds.  us a step, 1,000 and 2,000 values in the pass / 2,060 apart: 48^3
+// 5.8, 8.5 / 8.4, 160^3 26.2, 29.9 / 27.2, 96 x 96 x 80 with a CPML 22.0, 27.9 /
+// 19.5, 100 x 100 x 80 with four poles 35.4, 41.0 / 43.5.)  Most probes of so
+// many are single values: the first `nlane` blocks take those, a lane each, 1
+// << lw of them a wave; the others take the rest, a wave each, summed in
+// probe_sum's order (the 0.0 of threads without a term changes no bit).  Bound
+// by the loads' latency, about eight dependent rounds of them a value.  96 x 96
+// x 80, us a step (a block of 256 a probe): 4,000 values 20.1 (25.6), 20,000
+// 23.1 (62.0), 100,000 47.9 (243); 20,000 loops of four terms 22.8 (39.4),
+// 20,000 lines of 93 53.7 (74.0).
 template <typename T, typename CI, bool PML, bool DB>
 __global__ __launch_bounds__(PR_NT) void k_probes_tb2(GridView<T> g, MarchDebye<T> db, int step, int prev, int nlane,
                                                       int lw) {
