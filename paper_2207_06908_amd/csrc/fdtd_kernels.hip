@@ -225,7 +225,7 @@ template <typename T, typename CI, int TY, int AX, bool TABV>
 __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& sm, int i0, int j0, int iw, int jh,
                                          int k0, int k1, int step) {
   constexpr int TX = 60, NT = 64 * (TY + 4);
-  constexpr bool LDS_TAB = sizeof(CI) == 1;
+  constexpr bool LDS_TAB = sizeof(CI) == 1, WIDE = sizeof(T) == 4;
   const int tid = threadIdx.x, u = tid & 63, v = tid >> 6;
   const int nx = g.nx, ny = g.ny, nz = g.nz;
   const unsigned sxy = (unsigned)g.sxy;
@@ -291,6 +291,28 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
     return (inA && k >= 0 && k < nz) ? (int)ldg(cls, n0 + sxy * (unsigned)k) : 0;
   };
 
+  // E's sources in plane k (every lane of the wave; `on`: this lane's point
+  // takes them), many of them as in March.  FP32 only: an oblique wire, a
+  // source at every edge it touches, in 42 x 36 x 61 nodes of 17,000 classes
+  // 61 us a step, 100 with all of a column's sources read in every plane; FP64
+  // tiles, of which few meet a source, are 6% slower with it.
+  auto sources = [&](int k, bool on, int st, T e[3]) {
+    if (k < srcr.klo || k > srcr.khi) return;  // uniform
+    const unsigned n = on ? n0 + sxy * (unsigned)k : 0xFFFFFFFFu;
+    if (srcr.hi - srcr.lo <= 4) {
+      e_sources(&g, srcr.lo, srcr.hi, n, st, e);
+      return;
+    }
+    for (int s0 = srcr.lo; s0 < srcr.hi; s0 += 64) {
+      const int s = s0 + u;
+      const bool here = s < srcr.hi && (unsigned)ldg(g.src_idx, (unsigned)s) - sxy * (unsigned)k < sxy;
+      for (unsigned long long m = __ballot(here); m; m &= m - 1) {
+        const int q = s0 + __builtin_ctzll(m);
+        e_sources(&g, q, q + 1, n, st, e);
+      }
+    }
+  };
+
   // pipeline registers of this thread's point
   T e0c[3], e0n[3], h0c[3];
   T h1p[3] = {T(0), T(0), T(0)};   // H^{n+1/2}, plane k-1
@@ -351,7 +373,7 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
         psi_load(g, 0, l, x, y, k, psen);
         e_core_pf<T, true>(pf, l, coef(cc), h1c[0], h1c[1], h1c[2], sm.sh1[0][v - 1][u], h1p[0], sm.sh1[1][v][u - 1],
                           h1p[1], sm.sh1[2][v][u - 1], sm.sh1[2][v - 1][u], e0c, psen[0], psen[1], psen[2], e1c);
-        e_sources(&g, srcr.first(k), srcr.last(k), n0 + sxy * (unsigned)k, step, e1c);
+        if constexpr (!WIDE) e_sources(&g, srcr.first(k), srcr.last(k), n0 + sxy * (unsigned)k, step, e1c);
       };
       if (lz >= 0) {
         const int l[3] = {lx, ly, lz};
@@ -361,6 +383,7 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
         stage_b(l);
       }
     }
+    if (WIDE && k >= k0 - 1) sources(k, inB && kin, step, e1c);
     const int s1 = (k + 2) & 1, s1m = s1 ^ 1;
     for (int c = 0; c < 3; ++c) sm.se1[s1][c][v][u] = e1c[c];
     // No barrier here: C reads the neighbours' E^{n+1} of plane k-1 (slot
@@ -388,13 +411,25 @@ __device__ __forceinline__ void tb2_tile(const GridView<T>& g, TB2Smem<T, TY>& s
     for (int c = 0; c < 3; ++c) sm.sh2[c][v][u] = h2c[c];
     __syncthreads();
     // D: E^{n+2}, plane k-1 (the output tile; km < k1 always holds)
-    if (inD && km >= k0) {
-      const unsigned nst = n0 + sxy * (unsigned)km;
-      T e2[3];
-      int l[3] = {lx, ly, AX & 4 ? slab_pos(km, nz, g.npml) : -1};
+    T e2[3];
+    auto stage_d = [&](const int l[3]) {
       e_core_pf<T, true>(pf, l, coef(cp), h2c[0], h2c[1], h2c[2], sm.sh2[0][v - 1][u], h2p[0], sm.sh2[1][v][u - 1],
                         h2p[1], sm.sh2[2][v][u - 1], sm.sh2[2][v - 1][u], e1p, pse[0], pse[1], pse[2], e2);
-      e_sources(&g, srcr.first(km), srcr.last(km), nst, step + 1, e2);
+    };
+    if constexpr (WIDE) {
+      if (inD && km >= k0) {
+        const int l[3] = {lx, ly, AX & 4 ? slab_pos(km, nz, g.npml) : -1};
+        stage_d(l);
+      }
+      if (km >= k0) sources(km, inD, step + 1, e2);
+    }
+    if (inD && km >= k0) {
+      const unsigned nst = n0 + sxy * (unsigned)km;
+      int l[3] = {lx, ly, AX & 4 ? slab_pos(km, nz, g.npml) : -1};
+      if constexpr (!WIDE) {
+        stage_d(l);
+        e_sources(&g, srcr.first(km), srcr.last(km), nst, step + 1, e2);
+      }
       stg(g.fo[0], nst, e2[0]);
       stg(g.fo[1], nst, e2[1]);
       stg(g.fo[2], nst, e2[2]);
