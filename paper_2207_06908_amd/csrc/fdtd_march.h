@@ -54,11 +54,19 @@ struct MarchRows {
   T pz[P_NROW * PZ];    // the z table
 };
 // NC: classes whose coefficients fit the LDS table (0: none, they are read from
-// memory at each use).
-template <typename T, int TY, int NC = 256>
-struct MarchSmem : MarchRows<T, TY> {
+// memory at each use).  A table of up to 256 comes first, where offsets into it
+// need no base (100 x 100 x 80 with four poles 25.0 us a step, 25.8 with the
+// table behind the rows); a larger one comes last, as it would push the rows out
+// of an offset's 64 KB (12 rows, 1,300 classes on 203 x 157 x 131 68 us a step,
+// 104 with the table first).
+template <typename T, int NC>
+struct MarchTab {
   T stab[(NC + 1) * K_STRIDE];  // a row of zeros, then the classes' coefficients
 };
+template <typename T, int TY, int NC = 256, bool FIRST = (NC <= 256)>
+struct MarchSmem : MarchTab<T, NC>, MarchRows<T, TY> {};
+template <typename T, int TY, int NC>
+struct MarchSmem<T, TY, NC, false> : MarchRows<T, TY>, MarchTab<T, NC> {};
 
 // CPML profile values of a tile's points: a lane's x values in registers
 // (tiles of up to 8 rows, which have them to spare) or LDS, the row's y
