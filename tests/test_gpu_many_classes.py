@@ -1,6 +1,7 @@
 """Two-step passes of grids with more than 256 coefficient classes: against the split pass, bit for bit, on either side of
-what the tiles' tables in LDS hold (768 and 2,048 classes), alone and in a batch; and no slower than the split pass where
-they are the default (0.7 of its time with 1,300 classes on 203 x 157 x 131, 0.9 with 17,000)."""
+what the tiles' tables in LDS hold (768 and 2,048 classes), alone and in a batch; and the time against the split pass where
+they are the default (0.7 of its time with 1,300 classes on 203 x 157 x 131, 0.93 to 0.97 with 17,000; with the tables in
+memory 1.45 and 1.8).  Bounds lie between."""
 import numpy as np
 import pytest
 
@@ -64,7 +65,7 @@ def test_many_classes(classes, npml, precision):
         assert np.array_equal(a, o)
 
 
-@pytest.mark.parametrize("mu,bound", [(0.0, 0.9), (0.1, 1.0)])
+@pytest.mark.parametrize("mu,bound", [(0.0, 0.9), (0.1, 1.2)])
 def test_default_pass_with_many_classes(mu, bound):
     import torch
     assert torch.cuda.is_available(), "GPU tests need a GPU"
